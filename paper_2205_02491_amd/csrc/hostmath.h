@@ -18,8 +18,8 @@ struct Coef {
   double alpha, gamma, beta;
 };
 
-void sym_eig_small(std::vector<double> a, int k, std::vector<double>& val,
-                   std::vector<double>& vec);
+void tridiag_nodes(std::vector<double> d, std::vector<double> e, std::vector<double>& val,
+                   std::vector<double>& first);
 
 // alpha/beta are steps x nv, step-major (entry j*nv + r)
 Bounds lanczos_bounds(const std::vector<double>& alpha, const std::vector<double>& beta, int nv,
