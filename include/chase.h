@@ -177,7 +177,8 @@ typedef struct chase_stats {
   int64_t matvecs_low;   /* filter matrix-vector products in low precision   */
   double t_all;          /* seconds, whole solve (Table 2 columns)           */
   double t_lanczos, t_filter, t_qr, t_rr, t_resid;
-  double t_filter_kernels; /* summed HIP-event time of the filter GEMMs       */
+  double t_filter_kernels; /* HIP-event time of the filter GEMMs, summed over
+                              the passes (first GEMM to last)               */
   int64_t filter_launches; /* number of filter GEMM launches                 */
   double filter_flops;     /* algorithmic filter FLOPs (8 n^2 per complex mv) */
   double b_sup, mu_1, mu_ne; /* final spectral bounds                         */

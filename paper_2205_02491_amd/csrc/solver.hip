@@ -273,8 +273,41 @@ void gemm_nn(chase_handle_s* h, int64_t M, int64_t N, int64_t K, const void* A, 
 // ------------------------------------------------------------------ filter
 struct FilterTiming {
   int64_t matvecs = 0;
-  double ktime = 0.0;  // seconds of filter GEMMs (HIP events)
+  double ktime = 0.0;  // seconds of filter GEMMs (HIP events), if timed
   int64_t launches = 0;
+  bool timed = false;
+};
+
+void ensure_events(chase_handle_s* h, size_t count) {
+  while (h->evs.size() < count) {
+    hipEvent_t e;
+    CHASE_HIP(hipEventCreate(&e));
+    h->evs.push_back(e);
+  }
+}
+
+// Device time of a filter pass: one event before its first GEMM, one after
+// its last (and one where the precision changes), and none unless the caller
+// wants the time.  A pair around every GEMM put 10 us between two launches,
+// twice the time of a step of a small problem.
+struct PassClock {
+  chase_handle_s* h;
+  hipStream_t st;
+  bool on;
+  int n = 0;
+  PassClock(chase_handle_s* hh, hipStream_t s, bool timed) : h(hh), st(s), on(timed) {
+    if (on) ensure_events(h, 3);
+  }
+  void mark() {
+    if (on) CHASE_HIP(hipEventRecord(h->evs[n++], st));
+  }
+  // after the stream was synchronised: seconds between marks i and i + 1
+  double span(int i) const {
+    if (!on || i + 1 >= n) return 0.0;
+    float ms = 0.f;
+    CHASE_HIP(hipEventElapsedTime(&ms, h->evs[i], h->evs[i + 1]));
+    return ms * 1e-3;
+  }
 };
 
 Prec to_prec(int p) {
@@ -371,12 +404,7 @@ void run_filter(chase_handle_s* h, const void* H, int64_t ldh, void* X, int64_t 
     // their last value, which the adjoint never reads)
     copy_cols(h->cplx, X, ldx, h->tape, n, n, k, st);
   }
-  const size_t need_ev = 2 * (size_t)mmax;
-  while (h->evs.size() < need_ev) {
-    hipEvent_t e;
-    CHASE_HIP(hipEventCreate(&e));
-    h->evs.push_back(e);
-  }
+  PassClock clock(h, st, ft.timed);
   std::unique_ptr<Bf16Steps> bsteps;
   if (is_split_bf16(prec)) bsteps.reset(new Bf16Steps(h));
   for (int s = 1; s <= mmax; ++s) {
@@ -399,12 +427,11 @@ void run_filter(chase_handle_s* h, const void* H, int64_t ldh, void* X, int64_t 
       const int a1 = step_first_col(deg, k, s + 1);
       bsteps->prepare(g, cols, (s < mmax && a1 < k && s + 1 < fp64_from) ? a1 - a0 : -1, st);
     }
-    CHASE_HIP(hipEventRecord(h->evs[2 * (s - 1)], st));
+    if (s == 1 || s == fp64_from) clock.mark();
     if (low && prec != PREC_F64)
       gemm(h->cplx, prec, OP_N, OP_N, EPI_CHEB, g, st);
     else
       fp64_step(h, g, st);
-    CHASE_HIP(hipEventRecord(h->evs[2 * (s - 1) + 1], st));
     if (bsteps && low) bsteps->advance(g);
     FilterTiming& fs = low ? ft : *ft64;
     fs.matvecs += cols;
@@ -413,14 +440,10 @@ void run_filter(chase_handle_s* h, const void* H, int64_t ldh, void* X, int64_t 
       copy_cols(h->cplx, off(dst, a0 * ldd, h->esz), ldd,
                 off(h->tape, ((int64_t)s * k + a0) * n, h->esz), n, n, cols, st);
   }
+  clock.mark();
   CHASE_HIP(hipStreamSynchronize(st));
-  for (int s = 1; s <= mmax; ++s) {
-    const int a0 = (int)(std::lower_bound(deg, deg + k, s) - deg);
-    if (k - a0 <= 0) continue;
-    float ms = 0.f;
-    CHASE_HIP(hipEventElapsedTime(&ms, h->evs[2 * (s - 1)], h->evs[2 * (s - 1) + 1]));
-    (s < fp64_from ? ft : *ft64).ktime += ms * 1e-3;
-  }
+  if (fp64_from > 1) ft.ktime += clock.span(0);
+  if (fp64_from <= mmax) ft64->ktime += clock.span(fp64_from > 1 ? 1 : 0);
   if (tape) {
     h->tape_deg.assign(deg, deg + k);
     h->tape_coef = cf;
@@ -469,11 +492,7 @@ void run_filter_defect(chase_handle_s* h, const void* H, int64_t ldh, void* V, i
     lda = n;
     a_f32 = 1;
   }
-  while (h->evs.size() < 2 * (size_t)mmax) {
-    hipEvent_t e;
-    CHASE_HIP(hipEventCreate(&e));
-    h->evs.push_back(e);
-  }
+  PassClock clock(h, st, ft.timed);
   // D_1 = alpha_1 r ; D_0 = 0
   axpby_cols(h->cplx, h->d_coef + k, R, ldr, nullptr, W1, n, n, k, st);
   fill_zero(W2, (int64_t)n * k * (int64_t)h->esz, st);
@@ -498,26 +517,20 @@ void run_filter_defect(chase_handle_s* h, const void* H, int64_t ldh, void* V, i
       const int a1 = step_first_col(deg, k, s + 1);
       bsteps->prepare(g, cols, (s < mmax && a1 < k) ? a1 - a0 : -1, st);
     }
-    CHASE_HIP(hipEventRecord(h->evs[2 * (s - 1)], st));
+    if (s == 2) clock.mark();
     if (prec == PREC_F64)
       fp64_step(h, g, st);
     else
       gemm(h->cplx, prec, OP_N, OP_N, EPI_CHEB, g, st);
-    CHASE_HIP(hipEventRecord(h->evs[2 * (s - 1) + 1], st));
     if (bsteps) bsteps->advance(g);
     ft.matvecs += cols;
     ft.launches += 1;
   }
+  clock.mark();
   // p(H) v = T_m(theta) v + D_m  (degrees are even: D_m is in W2)
   axpby_cols(h->cplx, nullptr, W2, n, h->d_coef, V, ldv, n, k, st);
   CHASE_HIP(hipStreamSynchronize(st));
-  for (int s = 2; s <= mmax; ++s) {
-    const int a0 = (int)(std::lower_bound(deg, deg + k, s) - deg);
-    if (k - a0 <= 0) continue;
-    float ms = 0.f;
-    CHASE_HIP(hipEventElapsedTime(&ms, h->evs[2 * (s - 1)], h->evs[2 * (s - 1) + 1]));
-    ft.ktime += ms * 1e-3;
-  }
+  ft.ktime += clock.span(0);
 }
 
 void ensure_tape(chase_handle_s* h, int k, int mmax) {
@@ -790,11 +803,7 @@ void lanczos_outputs(const Bounds& bd, const std::vector<double>& a, const std::
 Bounds do_lanczos(chase_handle_s* h, const void* H, int64_t ldh, const void* S, int nv, int steps,
                   std::vector<double>* a_out, std::vector<double>* b_out, std::vector<int>* lens,
                   hipStream_t st, double* gemv_s = nullptr) {
-  while (h->evs.size() < 2 * (size_t)steps) {
-    hipEvent_t e;
-    CHASE_HIP(hipEventCreate(&e));
-    h->evs.push_back(e);
-  }
+  if (gemv_s) ensure_events(h, 2 * (size_t)steps);
   h->lz.gemv_ev = gemv_s ? h->evs.data() : nullptr;
   Bounds bd;
   try {
@@ -938,6 +947,7 @@ void solve_impl(chase_handle_s* h, const void* H, int64_t ldh, double tol, int d
   bool converged = false;
   std::vector<int> perm(ne);
   FilterTiming ft64, ftlo;
+  ft64.timed = ftlo.timed = true;
   // After Rayleigh-Ritz on the active block [L, L+ka): residuals, precision
   // switches, locking of the converged prefix, and unless done the bounds,
   // degrees and sort for the next filter.  Returns true when the solve stops.
