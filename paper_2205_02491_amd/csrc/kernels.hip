@@ -341,11 +341,15 @@ __global__ __launch_bounds__(TPB) void max_defect_k(const double* __restrict__ A
 // HBM (column-major, coalesced along rows).  The columns of H are split over
 // gridDim.y slices; each slice writes its partial sums, which the reduction
 // kernel adds in a fixed order (deterministic).
-constexpr int LZ_ROWS_PER_THREAD = 2;
-constexpr int LZ_ROWS = TPB * LZ_ROWS_PER_THREAD;
 constexpr int LZ_COLS_STAGE = 64;
 
-template <bool CPLX, int NV>
+// Rows of H per workgroup: two a thread, or one for matrices that would
+// otherwise give a few dozen workgroups (n=1000: 32 of them, 19 us a step;
+// with 256 rows and down to 32 columns each 128 of them, 13 us).
+constexpr int64_t LZ_SMALL_N = 4096;
+int lz_rows(int64_t n) { return n < LZ_SMALL_N ? TPB : 2 * TPB; }
+
+template <bool CPLX, int NV, int LZ_ROWS_PER_THREAD>
 __global__ __launch_bounds__(TPB) void lz_gemv_k(const double* __restrict__ H, int64_t ldh,
                                                  int64_t n, const double* __restrict__ Q,
                                                  double* __restrict__ part, int64_t cols_per) {
@@ -353,7 +357,7 @@ __global__ __launch_bounds__(TPB) void lz_gemv_k(const double* __restrict__ H, i
   // occupancy high enough to keep HBM busy)
   const int W = CPLX ? 2 : 1;
   __shared__ double qs[LZ_COLS_STAGE][NV][2];
-  const int64_t r0 = (int64_t)blockIdx.x * LZ_ROWS;
+  const int64_t r0 = (int64_t)blockIdx.x * (TPB * LZ_ROWS_PER_THREAD);
   const int64_t c0 = (int64_t)blockIdx.y * cols_per;
   const int64_t c1 = c0 + cols_per < n ? c0 + cols_per : n;
   double accr[LZ_ROWS_PER_THREAD][NV], acci[LZ_ROWS_PER_THREAD][NV];
@@ -450,120 +454,8 @@ __global__ __launch_bounds__(TPB) void lz_gemv_k(const double* __restrict__ H, i
   }
 }
 
-// block-wide sum of nv values per thread into out[blockIdx.x*nv + v]
-__device__ inline void block_sum_store(double* vals, int nv, double* out) {
-  __shared__ double red[TPB / 64][8];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int v = 0; v < nv; ++v) {
-    double x = vals[v];
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-    if (lane == 0) red[wave][v] = x;
-  }
-  __syncthreads();
-  if ((int)threadIdx.x < nv) {
-    double s = 0;
-    for (int w = 0; w < TPB / 64; ++w) s += red[w][threadIdx.x];
-    out[(int64_t)blockIdx.x * nv + threadIdx.x] = s;
-  }
-}
-
-// W = sum of gemv partials - beta_prev * Q_prev ; dotp = Re(Q_cur^H W) partials
-template <bool CPLX>
-__global__ __launch_bounds__(TPB) void lz_reduce_k(const double* __restrict__ part, int splits,
-                                                   int64_t n, int nv,
-                                                   const double* __restrict__ qprev,
-                                                   const double* __restrict__ qcur,
-                                                   const double* __restrict__ beta_prev,
-                                                   double* __restrict__ w, double* dotp) {
-  const int W = CPLX ? 2 : 1;
-  double dots[8];
-  for (int v = 0; v < 8; ++v) dots[v] = 0.0;
-  for (int64_t i = blockIdx.x * (int64_t)TPB + threadIdx.x; i < n; i += (int64_t)gridDim.x * TPB) {
-    for (int v = 0; v < nv; ++v) {
-      double sr = 0, si = 0;
-      for (int z = 0; z < splits; ++z) {
-        const double* p = part + (((int64_t)z * nv + v) * n + i) * W;
-        sr += p[0];
-        if (CPLX) si += p[1];
-      }
-      const int64_t o = (i + (int64_t)v * n) * W;
-      const double bp = beta_prev ? beta_prev[v] : 0.0;
-      sr -= bp * qprev[o];
-      if (CPLX) si -= bp * qprev[o + 1];
-      w[o] = sr;
-      if (CPLX) w[o + 1] = si;
-      dots[v] += qcur[o] * sr + (CPLX ? qcur[o + 1] * si : 0.0);
-    }
-  }
-  block_sum_store(dots, nv, dotp);
-}
-
-// alpha = sum(dotp); W -= alpha * Q_cur (skipped when with_alpha == 0);
-// nrmp = partial ||W||^2
-template <bool CPLX>
-__global__ __launch_bounds__(TPB) void lz_orth_k(const double* __restrict__ dotp, int nblk,
-                                                 int64_t n, int nv, int with_alpha,
-                                                 const double* __restrict__ qcur,
-                                                 double* __restrict__ w, double* alpha_out,
-                                                 double* nrmp) {
-  const int W = CPLX ? 2 : 1;
-  double alpha[8], nrm[8];
-  for (int v = 0; v < 8; ++v) {
-    alpha[v] = 0.0;
-    nrm[v] = 0.0;
-  }
-  if (with_alpha) {
-    for (int v = 0; v < nv; ++v) {
-      double s = 0;
-      for (int b = 0; b < nblk; ++b) s += dotp[(int64_t)b * nv + v];
-      alpha[v] = s;
-    }
-    if (blockIdx.x == 0 && (int)threadIdx.x < nv) alpha_out[threadIdx.x] = alpha[threadIdx.x];
-  }
-  for (int64_t i = blockIdx.x * (int64_t)TPB + threadIdx.x; i < n; i += (int64_t)gridDim.x * TPB) {
-    for (int v = 0; v < nv; ++v) {
-      const int64_t o = (i + (int64_t)v * n) * W;
-      double xr = w[o], xi = CPLX ? w[o + 1] : 0.0;
-      if (with_alpha) {
-        xr -= alpha[v] * qcur[o];
-        if (CPLX) xi -= alpha[v] * qcur[o + 1];
-        w[o] = xr;
-        if (CPLX) w[o + 1] = xi;
-      }
-      nrm[v] += xr * xr + xi * xi;
-    }
-  }
-  block_sum_store(nrm, nv, nrmp);
-}
-
-// beta = sqrt(sum(nrmp)); Q_next = W / beta (0 if beta == 0)
-template <bool CPLX>
-__global__ __launch_bounds__(TPB) void lz_normalize_k(const double* __restrict__ nrmp, int nblk,
-                                                      int64_t n, int nv,
-                                                      const double* __restrict__ w,
-                                                      double* __restrict__ qnext,
-                                                      double* beta_out) {
-  const int W = CPLX ? 2 : 1;
-  double inv[8];
-  for (int v = 0; v < nv; ++v) {
-    double s = 0;
-    for (int b = 0; b < nblk; ++b) s += nrmp[(int64_t)b * nv + v];
-    const double beta = sqrt(s);
-    inv[v] = beta > 0.0 ? 1.0 / beta : 0.0;
-    if (blockIdx.x == 0 && threadIdx.x == 0 && beta_out) beta_out[v] = beta;
-  }
-  for (int64_t i = blockIdx.x * (int64_t)TPB + threadIdx.x; i < n; i += (int64_t)gridDim.x * TPB) {
-    for (int v = 0; v < nv; ++v) {
-      const int64_t o = (i + (int64_t)v * n) * W;
-      qnext[o] = w[o] * inv[v];
-      if (CPLX) qnext[o + 1] = w[o + 1] * inv[v];
-    }
-  }
-}
-
-// ------------------------------------------------------------------ CG helpers
-// (eigenvector adjoint: batched conjugate gradients, one system per column)
-// Block-wide sum of one value per thread (fixed order: deterministic).
+// Block-wide sum of one value per thread (fixed order: deterministic), the
+// same in every thread.
 __device__ inline double block_sum1(double x) {
   __shared__ double red1[TPB / 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -576,6 +468,100 @@ __device__ inline double block_sum1(double x) {
   return s;
 }
 
+constexpr int LZ_VEC_BLOCKS = 128;
+static_assert(LZ_VEC_BLOCKS <= TPB, "one thread per partial sum");
+
+// Sum of the nblk <= LZ_VEC_BLOCKS partial sums of one vector, in every thread.
+__device__ inline double lz_total(const double* p, int nblk) {
+  return block_sum1((int)threadIdx.x < nblk ? p[threadIdx.x] : 0.0);
+}
+
+// The vector kernels of a Lanczos step run one workgroup per 256 rows and
+// vector (blockIdx.y), and sum the partial sums of the kernel before with one
+// thread each: with the four vectors and the partial sums in loops inside the
+// threads, 31 workgroups took 61 us a step at n=8000, a third of the product
+// with H (162 us); now 16 us.
+
+// W = sum of gemv partials - beta_prev * Q_prev ; dotp = Re(Q_cur^H W) partials
+template <bool CPLX>
+__global__ __launch_bounds__(TPB) void lz_reduce_k(const double* __restrict__ part, int splits,
+                                                   int64_t n, int nv,
+                                                   const double* __restrict__ qprev,
+                                                   const double* __restrict__ qcur,
+                                                   const double* __restrict__ beta_prev,
+                                                   double* __restrict__ w, double* dotp) {
+  const int W = CPLX ? 2 : 1;
+  const int v = blockIdx.y;
+  const double bp = beta_prev ? beta_prev[v] : 0.0;
+  double dot = 0.0;
+  for (int64_t i = blockIdx.x * (int64_t)TPB + threadIdx.x; i < n; i += (int64_t)gridDim.x * TPB) {
+    double sr = 0, si = 0;
+#pragma unroll 8
+    for (int z = 0; z < splits; ++z) {
+      const double* p = part + (((int64_t)z * nv + v) * n + i) * W;
+      sr += p[0];
+      if (CPLX) si += p[1];
+    }
+    const int64_t o = (i + (int64_t)v * n) * W;
+    sr -= bp * qprev[o];
+    if (CPLX) si -= bp * qprev[o + 1];
+    w[o] = sr;
+    if (CPLX) w[o + 1] = si;
+    dot += qcur[o] * sr + (CPLX ? qcur[o + 1] * si : 0.0);
+  }
+  dot = block_sum1(dot);
+  if (threadIdx.x == 0) dotp[(int64_t)v * gridDim.x + blockIdx.x] = dot;
+}
+
+// alpha = sum(dotp); W -= alpha * Q_cur (skipped when with_alpha == 0);
+// nrmp = partial ||W||^2
+template <bool CPLX>
+__global__ __launch_bounds__(TPB) void lz_orth_k(const double* __restrict__ dotp, int64_t n,
+                                                 int with_alpha, const double* __restrict__ qcur,
+                                                 double* __restrict__ w, double* alpha_out,
+                                                 double* nrmp) {
+  const int W = CPLX ? 2 : 1;
+  const int v = blockIdx.y;
+  double alpha = 0.0, nrm = 0.0;
+  if (with_alpha) {
+    alpha = lz_total(dotp + (int64_t)v * gridDim.x, gridDim.x);
+    if (blockIdx.x == 0 && threadIdx.x == 0) alpha_out[v] = alpha;
+  }
+  for (int64_t i = blockIdx.x * (int64_t)TPB + threadIdx.x; i < n; i += (int64_t)gridDim.x * TPB) {
+    const int64_t o = (i + (int64_t)v * n) * W;
+    double xr = w[o], xi = CPLX ? w[o + 1] : 0.0;
+    if (with_alpha) {
+      xr -= alpha * qcur[o];
+      if (CPLX) xi -= alpha * qcur[o + 1];
+      w[o] = xr;
+      if (CPLX) w[o + 1] = xi;
+    }
+    nrm += xr * xr + xi * xi;
+  }
+  nrm = block_sum1(nrm);
+  if (threadIdx.x == 0) nrmp[(int64_t)v * gridDim.x + blockIdx.x] = nrm;
+}
+
+// beta = sqrt(sum(nrmp)); Q_next = W / beta (0 if beta == 0)
+template <bool CPLX>
+__global__ __launch_bounds__(TPB) void lz_normalize_k(const double* __restrict__ nrmp, int64_t n,
+                                                      const double* __restrict__ w,
+                                                      double* __restrict__ qnext,
+                                                      double* beta_out) {
+  const int W = CPLX ? 2 : 1;
+  const int v = blockIdx.y;
+  const double beta = sqrt(lz_total(nrmp + (int64_t)v * gridDim.x, gridDim.x));
+  const double inv = beta > 0.0 ? 1.0 / beta : 0.0;
+  if (blockIdx.x == 0 && threadIdx.x == 0 && beta_out) beta_out[v] = beta;
+  for (int64_t i = blockIdx.x * (int64_t)TPB + threadIdx.x; i < n; i += (int64_t)gridDim.x * TPB) {
+    const int64_t o = (i + (int64_t)v * n) * W;
+    qnext[o] = w[o] * inv;
+    if (CPLX) qnext[o + 1] = w[o + 1] * inv;
+  }
+}
+
+// ------------------------------------------------------------------ CG helpers
+// (eigenvector adjoint: batched conjugate gradients, one system per column)
 // out[j] = Re(x_j^H y_j); one block per column
 template <int W>
 __global__ __launch_bounds__(TPB) void col_dots_k(const double* __restrict__ X, int64_t ldx,
@@ -669,16 +655,14 @@ __global__ void sym_divdiff_k(const double* __restrict__ M, int64_t ldm,
   }
 }
 
-constexpr int LZ_VEC_BLOCKS = 128;
-
 // Column splits of the block GEMV: about 512 workgroups, two per CU of the
 // 256-CU MI355X, all resident at once (each streams a long range of
 // columns).  Measured at n=20000 with nontemporal loads: 6.7-6.9 TB/s with
 // 480 workgroups, 5.9 TB/s with ~2048 (two rounds of resident workgroups).
 int lz_splits(int64_t n) {
-  const int64_t row_blocks = (n + LZ_ROWS - 1) / LZ_ROWS;
+  const int64_t row_blocks = (n + lz_rows(n) - 1) / lz_rows(n);
   int64_t s = 512 / row_blocks;
-  const int64_t smax = (n + 63) / 64;
+  const int64_t smax = n < LZ_SMALL_N ? (n + 31) / 32 : (n + 63) / 64;
   if (s > smax) s = smax;
   if (s > 64) s = 64;
   if (s < 1) s = 1;
@@ -976,7 +960,8 @@ void lanczos_run(bool cplx, const void* Hv, int64_t ldh, int64_t n, const void* 
   double* part = static_cast<double*>(b.wpart);
   const int splits = b.max_splits;
   const int64_t cols_per = (n + splits - 1) / splits;
-  const int row_blocks = (int)((n + LZ_ROWS - 1) / LZ_ROWS);
+  const bool small = n < LZ_SMALL_N;
+  const int row_blocks = (int)((n + lz_rows(n) - 1) / lz_rows(n));
   const int vb = (int)std::min<int64_t>(LZ_VEC_BLOCKS, (n + TPB - 1) / TPB);
 
   // q_1 = s / ||s|| ; q_0 = 0
@@ -985,28 +970,33 @@ void lanczos_run(bool cplx, const void* Hv, int64_t ldh, int64_t n, const void* 
   fill_zero(qprev, (int64_t)n * nv * W * 8, st);
   auto orth = [&](int with_alpha, double* alpha_out) {
     if (cplx)
-      hipLaunchKernelGGL(lz_orth_k<true>, dim3(vb), dim3(TPB), 0, st, b.dotp, vb, n, nv,
-                         with_alpha, qcur, w, alpha_out, b.nrmp);
+      hipLaunchKernelGGL(lz_orth_k<true>, dim3(vb, nv), dim3(TPB), 0, st, b.dotp, n, with_alpha,
+                         qcur, w, alpha_out, b.nrmp);
     else
-      hipLaunchKernelGGL(lz_orth_k<false>, dim3(vb), dim3(TPB), 0, st, b.dotp, vb, n, nv,
-                         with_alpha, qcur, w, alpha_out, b.nrmp);
+      hipLaunchKernelGGL(lz_orth_k<false>, dim3(vb, nv), dim3(TPB), 0, st, b.dotp, n, with_alpha,
+                         qcur, w, alpha_out, b.nrmp);
   };
   auto normalize = [&](double* dst, double* beta_out) {
     if (cplx)
-      hipLaunchKernelGGL(lz_normalize_k<true>, dim3(vb), dim3(TPB), 0, st, b.nrmp, vb, n, nv, w,
-                         dst, beta_out);
+      hipLaunchKernelGGL(lz_normalize_k<true>, dim3(vb, nv), dim3(TPB), 0, st, b.nrmp, n, w, dst,
+                         beta_out);
     else
-      hipLaunchKernelGGL(lz_normalize_k<false>, dim3(vb), dim3(TPB), 0, st, b.nrmp, vb, n, nv, w,
-                         dst, beta_out);
+      hipLaunchKernelGGL(lz_normalize_k<false>, dim3(vb, nv), dim3(TPB), 0, st, b.nrmp, n, w, dst,
+                         beta_out);
   };
   auto gemv = [&](const double* q) {
-#define CHASE_LZ_GEMV(NVC)                                                                   \
-  if (cplx)                                                                                \
-    hipLaunchKernelGGL((lz_gemv_k<true, NVC>), dim3(row_blocks, splits), dim3(TPB), 0, st, H, \
-                       ldh, n, q, part, cols_per);                                          \
-  else                                                                                     \
-    hipLaunchKernelGGL((lz_gemv_k<false, NVC>), dim3(row_blocks, splits), dim3(TPB), 0, st,   \
-                       H, ldh, n, q, part, cols_per);
+#define CHASE_LZ_LAUNCH(CPLX, NVC, RPT)                                                       \
+  hipLaunchKernelGGL((lz_gemv_k<CPLX, NVC, RPT>), dim3(row_blocks, splits), dim3(TPB), 0, st, \
+                     H, ldh, n, q, part, cols_per)
+#define CHASE_LZ_GEMV(NVC)                 \
+  if (cplx && small)                       \
+    CHASE_LZ_LAUNCH(true, NVC, 1);         \
+  else if (cplx)                           \
+    CHASE_LZ_LAUNCH(true, NVC, 2);         \
+  else if (small)                          \
+    CHASE_LZ_LAUNCH(false, NVC, 1);        \
+  else                                     \
+    CHASE_LZ_LAUNCH(false, NVC, 2);
     switch (nv) {
       case 1: CHASE_LZ_GEMV(1) break;
       case 2: CHASE_LZ_GEMV(2) break;
@@ -1018,6 +1008,7 @@ void lanczos_run(bool cplx, const void* Hv, int64_t ldh, int64_t n, const void* 
       default: CHASE_LZ_GEMV(8) break;
     }
 #undef CHASE_LZ_GEMV
+#undef CHASE_LZ_LAUNCH
   };
   orth(0, nullptr);
   normalize(qcur, nullptr);
@@ -1027,10 +1018,10 @@ void lanczos_run(bool cplx, const void* Hv, int64_t ldh, int64_t n, const void* 
     if (b.gemv_ev) CHASE_HIP(hipEventRecord(b.gemv_ev[2 * j + 1], st));
     const double* bprev = j > 0 ? b.beta + (int64_t)(j - 1) * nv : nullptr;
     if (cplx)
-      hipLaunchKernelGGL(lz_reduce_k<true>, dim3(vb), dim3(TPB), 0, st, part, splits, n, nv,
+      hipLaunchKernelGGL(lz_reduce_k<true>, dim3(vb, nv), dim3(TPB), 0, st, part, splits, n, nv,
                          qprev, qcur, bprev, w, b.dotp);
     else
-      hipLaunchKernelGGL(lz_reduce_k<false>, dim3(vb), dim3(TPB), 0, st, part, splits, n, nv,
+      hipLaunchKernelGGL(lz_reduce_k<false>, dim3(vb, nv), dim3(TPB), 0, st, part, splits, n, nv,
                          qprev, qcur, bprev, w, b.dotp);
     orth(1, b.alpha + (int64_t)j * nv);
     // q_{j+1} overwrites q_{j-1}
