@@ -138,10 +138,11 @@ void gemm(bool cplx, Prec prec, Op opa, Op opb, Epi epi, const GemmArgs& g,
 int gemm_row_tiles(int64_t M);
 // Split-K plan for an M x N result with long K: number of slices and the
 // per-slice K length; workspace elements needed = splits * M * N.
-void splitk_plan(int64_t M, int64_t N, int64_t K, int* splits, int64_t* kslice,
+void splitk_plan(bool cplx, int64_t M, int64_t N, int64_t K, int* splits, int64_t* kslice,
                  bool tri = false);
-// Edge of the square tiles of the split-K products (the unit of `tri`).
-int splitk_tile();
+// Edge of the square tiles of the split-K products with M rows and inner
+// dimension K (the unit of `tri`).
+int splitk_tile(bool cplx, int64_t M, int64_t K);
 
 // ------------------------------------------------------------------ misc kernels
 void fill_zero(void* p, int64_t bytes, hipStream_t st);

@@ -22,12 +22,15 @@
 //
 // Measured per filter step against the earlier kernel (128 x 64 and 128 x 128
 // tiles staged through double-buffered LDS, one K range per tile), complex:
-// n=20000, 1300 columns 54.7 -> 43.8 ms (95 TFLOP/s algorithmic, 91% of the
-// three-product FP64 peak); 1000 x 140 220 -> 28 us; 256 x 16 57 -> 5 us; real:
-// 5003 x 173 798 -> 155 us.  Two waves per SIMD are needed (one: 62-74 TFLOP/s
-// with larger wave tiles), and the wait counters must be exact: a prologue
-// of conditional loads made the compiler wait for every load in flight at the
-// head of the loop and cost 5%.
+// n=20000, 1300 columns 54.7 -> 47.4 ms (88 TFLOP/s algorithmic, 84% of the
+// three-product FP64 peak); 1000 x 140 220 -> 22 us; 256 x 16 57 -> 5 us; real:
+// 5003 x 173 798 -> 157 us.  At full size the clock is power limited: on
+// operands with 16-bit mantissas the same kernel reaches 95 TFLOP/s, and what
+// moves fewer bytes between the caches is faster (two waves that share their
+// B fragments through the vector cache: 83 -> 88).  Two waves per SIMD are
+// needed (one: 62-74 TFLOP/s with larger wave tiles), and the wait counters
+// must be exact: a prologue of conditional loads made the compiler wait for
+// every load in flight at the head of the loop and cost 5%.
 //
 // A complex product is three real MFMAs (Gauss: re*re, im*im,
 // (re+im)*(re+im)) in the filter and the other long products, four
@@ -38,6 +41,8 @@
 // Workgroup ids are remapped so that each of the 8 XCDs (private L2) works on
 // a contiguous range of tiles, i.e. on the same few row panels of A.
 #include "common.h"
+
+#include <algorithm>
 
 namespace chase {
 namespace {
@@ -552,9 +557,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK, OCC) void gemm_kernel(GemmArgs g
 }
 
 template <typename TA, typename TC, bool CPLX, int OPA, int OPB, int EPI, bool G3, int FM, int FN,
-          int WK = 8, int OCC = 1>
+          int WK = 8, int OCC = 1, int WM = 1>
 void launch(const GemmArgs& g, hipStream_t st) {
-  constexpr int TBM = FM * 16, TBN = FN * 16;
+  constexpr int TBM = WM * FM * 16, TBN = FN * 16;
   const int64_t tiles_m = (g.M + TBM - 1) / TBM;
   const int64_t tiles_n = (g.N + TBN - 1) / TBN;
   int64_t ntiles = tiles_m * tiles_n;
@@ -565,8 +570,8 @@ void launch(const GemmArgs& g, hipStream_t st) {
   CHASE_REQUIRE(ntiles <= INT32_MAX - 8, "too many output tiles");
   const int grid_x = (int)((ntiles + 7) / 8 * 8);
   dim3 grid(grid_x, 1, EPI == EPI_SPLITK ? g.splits : 1);
-  hipLaunchKernelGGL((gemm_kernel<TA, TC, CPLX, OPA, OPB, EPI, G3, FM, FN, 1, 1, WK, 2, OCC>), grid,
-                     dim3(64 * WK), 0, st, g, (int)tiles_n, (int)ntiles);
+  hipLaunchKernelGGL((gemm_kernel<TA, TC, CPLX, OPA, OPB, EPI, G3, FM, FN, WM, 1, WK, 2, OCC>), grid,
+                     dim3(64 * WM * WK), 0, st, g, (int)tiles_n, (int)ntiles);
   CHASE_HIP(hipGetLastError());
 }
 
@@ -579,12 +584,15 @@ struct Tile {
   int tm, tn;
   double rate;
 };
+inline int64_t tiles_of(int64_t M, int64_t N, int tm, int tn) {
+  return ((M + tm - 1) / tm) * ((N + tn - 1) / tn);
+}
 template <int N>
 int pick(const Tile (&t)[N], int64_t M, int64_t N_) {
   int best = 0;
   double cost = 0.0;
   for (int i = 0; i < N; ++i) {
-    const int64_t tiles = ((M + t[i].tm - 1) / t[i].tm) * ((N_ + t[i].tn - 1) / t[i].tn);
+    const int64_t tiles = tiles_of(M, N_, t[i].tm, t[i].tn);
     const double c = (double)((tiles + NCU - 1) / NCU) * t[i].tm * t[i].tn / t[i].rate;
     if (i == 0 || c < cost) {
       best = i;
@@ -594,38 +602,85 @@ int pick(const Tile (&t)[N], int64_t M, int64_t N_) {
   return best;
 }
 
-// Complex, three-product form.
+// Complex, three-product form.  Rates: TFLOP/s (algorithmic) on the 20000 x
+// 1300 filter step.  The smaller tiles earn their place where a dimension is
+// ragged or the chip is not full: 1000 x 140 takes 22 us with 48 x 16 (189
+// tiles), 28 with 32 x 32 (160) or 32 x 16 (288), 41 with 48 x 32 (105).
 template <int EPI>
 void gauss_f64(const GemmArgs& g, hipStream_t st) {
-  // TFLOP/s (algorithmic) on the 20000 x 1300 filter step
-  static constexpr Tile t[] = {{48, 32, 95}, {32, 32, 90}, {32, 16, 67}, {16, 16, 42}};
+  static constexpr Tile t[] = {{96, 32, 88}, {48, 32, 83}, {32, 32, 79},
+                               {48, 16, 74}, {32, 16, 62}, {16, 16, 42}};
   switch (pick(t, g.M, g.N)) {
-    case 0: return launch<double, double, true, OP_N, OP_N, EPI, true, 3, 2>(g, st);
-    case 1: return launch<double, double, true, OP_N, OP_N, EPI, true, 2, 2>(g, st);
-    case 2: return launch<double, double, true, OP_N, OP_N, EPI, true, 2, 1>(g, st);
+    case 0: return launch<double, double, true, OP_N, OP_N, EPI, true, 3, 2, 4, 1, 2>(g, st);
+    case 1:
+      // two workgroups of 4 waves a compute unit: one runs while the other
+      // reduces and stores (82 -> 83); a single one needs 8 for two waves a
+      // SIMD
+      if (tiles_of(g.M, g.N, 48, 32) <= NCU)
+        return launch<double, double, true, OP_N, OP_N, EPI, true, 3, 2>(g, st);
+      return launch<double, double, true, OP_N, OP_N, EPI, true, 3, 2, 4, 2>(g, st);
+    case 2: return launch<double, double, true, OP_N, OP_N, EPI, true, 2, 2>(g, st);
+    case 3: return launch<double, double, true, OP_N, OP_N, EPI, true, 3, 1>(g, st);
+    case 4: return launch<double, double, true, OP_N, OP_N, EPI, true, 2, 1>(g, st);
     default: return launch<double, double, true, OP_N, OP_N, EPI, true, 1, 1>(g, st);
   }
 }
 
-// Complex, four-product form.
+// Waves per workgroup of the four-product and residual forms' 32 x 32 tiles:
+// 8 while the tiles do not fill the chip; with 1024 tiles or more (four 4-wave
+// workgroups a compute unit), fewer waves split K, so that more workgroups
+// overlap one's reduction and stores with another's products.  8000 x 260 x
+// 260: 87 us with 8, 78 with 4; rank-96 update of order 3000: 201 / 138 / 126
+// us with 8 / 4 / 2, rank-960: 1084 / 982 / 1005.
+inline int waves_of(const GemmArgs& g) {
+  if (tiles_of(g.M, g.N, 32, 32) < 4 * NCU) return 8;
+  return g.K <= 192 ? 2 : 4;
+}
+
+// Complex, four-product form.  Rates: 20000 x 1300 x 1300.
 template <int OPA, int OPB, int EPI>
 void four_f64(const GemmArgs& g, hipStream_t st) {
-  static constexpr Tile t[] = {{32, 32, 70}, {16, 16, 45}};
-  switch (pick(t, g.M, g.N)) {
-    case 0: return launch<double, double, true, OPA, OPB, EPI, false, 2, 2>(g, st);
-    default: return launch<double, double, true, OPA, OPB, EPI, false, 1, 1>(g, st);
+  static constexpr Tile t[] = {{32, 32, 66}, {16, 16, 45}, {64, 32, 71}};
+  constexpr int OCC = OPB == OP_C ? 3 : 4;
+  const int p = pick(t, g.M, g.N);
+  if (p == 1) return launch<double, double, true, OPA, OPB, EPI, false, 1, 1>(g, st);
+  // the larger tile for long blocks times a factor only: the rank-k updates
+  // (OPB = C) are short and bound by C
+  if constexpr (OPB == OP_N) {
+    if (p == 2) return launch<double, double, true, OPA, OPB, EPI, false, 4, 2, 4, 2>(g, st);
+  }
+  switch (waves_of(g)) {
+    case 2: return launch<double, double, true, OPA, OPB, EPI, false, 2, 2, 2, OCC>(g, st);
+    case 4: return launch<double, double, true, OPA, OPB, EPI, false, 2, 2, 4, OCC>(g, st);
+    default: return launch<double, double, true, OPA, OPB, EPI, false, 2, 2>(g, st);
   }
 }
 
+// Real.  Rates: TFLOP/s on a 10000 x 1024 filter step; 2000 x 100 takes 21 us
+// with 64 x 16 (224 tiles), 23 with 32 x 32 (252), 37 with 64 x 32 (128).
 template <int OPA, int OPB, int EPI>
 void real_f64(const GemmArgs& g, hipStream_t st) {
-  // TFLOP/s on a 10000 x 1024 filter step
-  static constexpr Tile t[] = {{64, 64, 69}, {64, 32, 68}, {32, 32, 50}, {16, 16, 25}};
   // pairs of rows (or columns) are loaded together: at least two of them
-  switch (g.M < 2 || g.N < 2 ? 3 : pick(t, g.M, g.N)) {
-    case 0: return launch<double, double, false, OPA, OPB, EPI, false, 4, 4>(g, st);
-    case 1: return launch<double, double, false, OPA, OPB, EPI, false, 4, 2, 4, 3>(g, st);
-    case 2: return launch<double, double, false, OPA, OPB, EPI, false, 2, 2>(g, st);
+  if (g.M < 2 || g.N < 2)
+    return launch<double, double, false, OPA, OPB, EPI, false, 1, 1>(g, st);
+  // rank-k updates: short K, see waves_of (order 2000, rank 100: 33 us with
+  // 64 x 32 tiles and 4 waves, 28 with 32 x 32 and 2)
+  if (g.K <= 192 && waves_of(g) == 2)
+    return launch<double, double, false, OPA, OPB, EPI, false, 2, 2, 2, 4>(g, st);
+  static constexpr Tile t[] = {{128, 64, 70}, {64, 64, 67}, {64, 32, 62}, {64, 16, 55},
+                               {32, 32, 48},  {32, 16, 41}, {16, 16, 24}};
+  switch (pick(t, g.M, g.N)) {
+    case 0: return launch<double, double, false, OPA, OPB, EPI, false, 4, 4, 2, 2, 2>(g, st);
+    case 1:
+      // a single workgroup a compute unit needs 8 waves for two a SIMD (5003
+      // x 173: 161 us with 4, 157 with 8)
+      if (tiles_of(g.M, g.N, 64, 64) <= NCU)
+        return launch<double, double, false, OPA, OPB, EPI, false, 4, 4>(g, st);
+      return launch<double, double, false, OPA, OPB, EPI, false, 4, 4, 4, 2>(g, st);
+    case 2: return launch<double, double, false, OPA, OPB, EPI, false, 4, 2, 4, 3>(g, st);
+    case 3: return launch<double, double, false, OPA, OPB, EPI, false, 4, 1>(g, st);
+    case 4: return launch<double, double, false, OPA, OPB, EPI, false, 2, 2>(g, st);
+    case 5: return launch<double, double, false, OPA, OPB, EPI, false, 2, 1>(g, st);
     default: return launch<double, double, false, OPA, OPB, EPI, false, 1, 1>(g, st);
   }
 }
@@ -642,7 +697,6 @@ void cheb_f32(const GemmArgs& g, hipStream_t st) {
 }
 
 constexpr int kResidRows = 32;  // row tile of EPI_RESID
-constexpr int kSplitTile = 32;  // square tile of EPI_SPLITK
 
 template <bool CPLX>
 void dispatch(Prec prec, Op opa, Op opb, Epi epi, const GemmArgs& g, hipStream_t st) {
@@ -672,12 +726,21 @@ void dispatch(Prec prec, Op opa, Op opb, Epi epi, const GemmArgs& g, hipStream_t
         // single row (the lanes' row pairs need two) runs on 16-row tiles.
         if (!CPLX && g.M < 2)
           return launch<double, double, CPLX, OP_N, OP_N, EPI_RESID, false, 1, 1>(g, st);
-        return launch<double, double, CPLX, OP_N, OP_N, EPI_RESID, false, 2, 2>(g, st);
+        if (waves_of(g) == 8)
+          return launch<double, double, CPLX, OP_N, OP_N, EPI_RESID, false, 2, 2>(g, st);
+        return launch<double, double, CPLX, OP_N, OP_N, EPI_RESID, false, 2, 2, 4, 4>(g, st);
       default: break;
     }
   } else if (opa == OP_C && opb == OP_N) {
-    if (epi == EPI_SPLITK)
-      return launch<double, double, CPLX, OP_C, OP_N, EPI_SPLITK, false, 2, 2>(g, st);
+    if (epi == EPI_SPLITK) {
+      if constexpr (CPLX) {
+        return launch<double, double, CPLX, OP_C, OP_N, EPI_SPLITK, false, 2, 2>(g, st);
+      } else {
+        if (splitk_tile(CPLX, g.M, g.K) == 64)
+          return launch<double, double, CPLX, OP_C, OP_N, EPI_SPLITK, false, 4, 4, 4, 2>(g, st);
+        return launch<double, double, CPLX, OP_C, OP_N, EPI_SPLITK, false, 2, 2>(g, st);
+      }
+    }
   } else if (opa == OP_N && opb == OP_C && epi == EPI_STORE) {
     if constexpr (CPLX)
       return four_f64<OP_N, OP_C, EPI_STORE>(g, st);
@@ -690,14 +753,26 @@ void dispatch(Prec prec, Op opa, Op opb, Epi epi, const GemmArgs& g, hipStream_t
 }  // namespace
 
 int gemm_row_tiles(int64_t M) { return (int)((M + kResidRows - 1) / kResidRows); }
-int splitk_tile() { return kSplitTile; }
 
-// About 512 workgroups (two per compute unit), slices of at least 256 (32 per
-// wave of a workgroup).  tri: the tiles on and above the diagonal only.
-void splitk_plan(int64_t M, int64_t N, int64_t K, int* splits, int64_t* kslice, bool tri) {
-  const int64_t tm = (M + kSplitTile - 1) / kSplitTile;
-  const int64_t tiles = tri ? tm * (tm + 1) / 2 : tm * ((N + kSplitTile - 1) / kSplitTile);
-  int64_t s = (2 * NCU + tiles - 1) / tiles;
+// Square tile of the split-K products: 32 for complex data; real data reaches
+// 60 TFLOP/s with 64 and 36 with 32 (20000 x 1300), as long as the tiles and
+// the K slices of 256 give every compute unit a workgroup.
+int splitk_tile(bool cplx, int64_t M, int64_t K) {
+  const int64_t tm = (M + 63) / 64;
+  return cplx || M <= 32 || tm * (tm + 1) / 2 * (K / 256) < NCU ? 32 : 64;
+}
+
+// Slices: about 1024 workgroups of a few waves, at least four slices where
+// the tiles alone are no more than that (the last, partly filled round costs
+// less: 20000 x 1300 complex 2.56 ms with one slice, 2.14 with four), but not more than 4096 in all; each slice at least 256 long.  tri:
+// the tiles on and above the diagonal only.
+void splitk_plan(bool cplx, int64_t M, int64_t N, int64_t K, int* splits, int64_t* kslice,
+                 bool tri) {
+  const int64_t T = splitk_tile(cplx, M, K);
+  const int64_t tm = (M + T - 1) / T;
+  const int64_t tiles = tri ? tm * (tm + 1) / 2 : tm * ((N + T - 1) / T);
+  int64_t s = std::max((4 * NCU + tiles - 1) / tiles,
+                       std::min<int64_t>(4, (16 * NCU + tiles - 1) / tiles));
   const int64_t smax = (K + 255) / 256;
   if (s > smax) s = smax;
   if (s < 1) s = 1;

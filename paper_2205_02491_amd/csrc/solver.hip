@@ -152,14 +152,14 @@ void rb_check(rocblas_status s, const char* what) {
     throw Error(CHASE_ERR_HIP, std::string(what) + " failed: " + rocblas_status_to_string(s));
 }
 
-size_t splitk_ws_elems(int ne) {
+size_t splitk_ws_elems(bool cplx, int ne) {
   size_t mx = 0;
   for (int k = 1; k <= ne; ++k) {
     int s;
     int64_t ks;
     // K is at least ne (the library's projections have K = n >= ne); the
     // Hermitian products computed as triangles have the most slices
-    splitk_plan(k, k, INT64_MAX / 4, &s, &ks, true);
+    splitk_plan(cplx, k, k, INT64_MAX / 4, &s, &ks, true);
     mx = std::max(mx, (size_t)s * k * k);
   }
   return mx;
@@ -178,7 +178,7 @@ Sizes sizes(chase_dtype dt, int64_t n, int nev, int nex, const chase_opts& o) {
   const size_t esz = cplx ? 16 : 8;
   const int64_t ne = nev + nex;
   s.blocks = 3 * (size_t)n * ne * esz + 2 * (size_t)ne * ne * esz;
-  s.ws = splitk_ws_elems((int)ne) * esz;
+  s.ws = splitk_ws_elems(cplx, (int)ne) * esz;
   s.small = (size_t)ne * 8 * 5 + (size_t)gemm_row_tiles(n) * ne * 8 + 64 + (size_t)ne * 4 +
             (size_t)ne * esz;
   s.lz = lanczos_bytes(cplx, n, o.lanczos_vecs, o.lanczos_steps, &s.lz_splits);
@@ -247,14 +247,15 @@ void gram(chase_handle_s* h, const void* A, int64_t lda, const void* B, int64_t 
   const bool tri = herm && k1 == k2;
   int splits;
   int64_t ks;
-  splitk_plan(k1, k2, K, &splits, &ks, tri);
+  splitk_plan(h->cplx, k1, k2, K, &splits, &ks, tri);
   CHASE_REQUIRE((size_t)splits * k1 * k2 <= h->ws_elems, "split-K workspace too small");
   GemmArgs g = gargs(k1, k2, K, A, lda, B, ldb, h->ws, k1);
   g.splits = splits;
   g.kslice = ks;
   g.tri = tri ? 1 : 0;
   gemm(h->cplx, PREC_F64, OP_C, OP_N, EPI_SPLITK, g, st);
-  splitk_reduce(h->cplx, h->ws, splits, k1, k2, C, ldc, herm, st, tri ? splitk_tile() : 0);
+  splitk_reduce(h->cplx, h->ws, splits, k1, k2, C, ldc, herm, st,
+                tri ? splitk_tile(h->cplx, k1, K) : 0);
 }
 
 // C = A B; tri_row0 >= 0: column j of B is zero below row tri_row0 + j
@@ -1279,7 +1280,7 @@ chase_status chase_create(chase_handle_t* out, chase_dtype dtype, int64_t n, int
     h->Z = dev_alloc(h, (size_t)n * ne * h->esz);
     h->G = dev_alloc(h, (size_t)ne * ne * h->esz);
     h->R = dev_alloc(h, (size_t)ne * ne * h->esz);
-    h->ws_elems = splitk_ws_elems((int)ne);
+    h->ws_elems = splitk_ws_elems(h->cplx, (int)ne);
     h->ws = dev_alloc(h, h->ws_elems * h->esz);
     h->d_scale = static_cast<double*>(dev_alloc(h, ne * 8));
     h->d_evals = static_cast<double*>(dev_alloc(h, ne * 8));
