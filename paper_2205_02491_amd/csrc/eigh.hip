@@ -25,6 +25,7 @@ constexpr int JB = 16;       // indices per block
 constexpr int JM = 2 * JB;   // order of a pair's subproblem
 constexpr int JLD = JM + 1;  // LDS leading dimension (padded against bank conflicts)
 constexpr int JT = 256;      // threads per workgroup
+constexpr int JPT = 2 * JT;  // threads per workgroup of the pair solves
 constexpr int JCG = JT / JM; // column groups of the tile stores (8)
 constexpr int NPART = 256;   // workgroups of the norm reduction
 
@@ -66,13 +67,20 @@ __host__ __device__ inline int rr_player(int m, int r, int j) {
   return j == 0 ? 0 : (j - 1 + r) % (m - 1) + 1;
 }
 
+// Player of an inner round (m = JM, 0 <= r < JM - 1) without a division.
+__device__ __forceinline__ int inner_player(int r, int j) {
+  const int p = j - 1 + r;
+  return j == 0 ? 0 : p >= JM - 1 ? p - (JM - 2) : p + 1;
+}
+
 // Rotation that zeroes the (a, b) entry of the 2 x 2 Hermitian
 // [[app, apq], [conj(apq), aqq]]: with apq = g ph (g = |apq|, |ph| = 1),
 // u = [[cs, sn], [-sn conj(ph), cs conj(ph)]] = diag(1, conj(ph)) R, R the
-// real rotation [[cs, sn], [-sn, cs]], and u^H A u is diagonal.  t = sn / cs
-// is the root of smaller magnitude of t^2 + 2 tau t - 1 = 0, tau = (aqq -
-// app) / (2 g), written as t = sign(d) 2 g / (|d| + sqrt(d^2 + 4 g^2)),
-// d = aqq - app (one square root and one division on the dependent path).
+// real rotation [[cs, sn], [-sn, cs]] by the smaller of the two angles, and
+// u^H A u is diagonal: with d = aqq - app and h = sqrt(d^2 + 4 g^2), the double
+// angle has cosine |d| / h and sine 2 g / h, so cs^2 = (1 + |d| / h) / 2 and
+// sn = sign(d) g / (h cs): two reciprocal square roots on the dependent path,
+// no division.
 // Entries with g <= thr are left alone (identity).
 template <class T>
 __device__ __forceinline__ int jac_rotation(double app, double aqq, T apq, double thr, double& cs,
@@ -85,11 +93,12 @@ __device__ __forceinline__ int jac_rotation(double app, double aqq, T apq, doubl
     return 0;
   }
   const double d = aqq - app;
+  const double rh = rsqrt(fma(d, d, 4.0 * g2));
   const double rg = rsqrt(g2);
-  const double r = sqrt(fma(d, d, 4.0 * g2));
-  const double t = copysign(2.0 * g2 * rg, d) / (fabs(d) + r);
-  cs = rsqrt(fma(t, t, 1.0));
-  sn = t * cs;
+  const double c2 = fma(0.5 * fabs(d), rh, 0.5);  // cs^2, in [1/2, 1]
+  const double rc = rsqrt(c2);
+  cs = c2 * rc;
+  sn = copysign(g2 * rg * rh * rc, d);
   ph = apq * rg;
   return 1;
 }
@@ -99,20 +108,31 @@ __device__ __forceinline__ int jac_rotation(double app, double aqq, T apq, doubl
 // players: JB disjoint rotations per inner round, applied together), and
 // write the accumulated unitary U (column-major, JM x JM) and whether any
 // rotation was made.  Indices >= k are padding: zero rows and columns that
-// never rotate.  S and U: JM x JLD arrays in LDS.
+// never rotate.  S0, S1 and U: JM x JLD arrays in LDS.
+//
+// Bound by the chain of the 2JB - 1 dependent inner rounds: one workgroup per
+// pair, a few dozen on the chip.  In an inner round 16 threads compute the
+// rotations and publish them; then waves 0 - 3 update S, one 2 x 2 block a
+// thread, beside waves 4 - 7, which update U.  A launch takes 25 us at k = 140
+// and 33 us at k = 260 (complex; 35 and 42 with S and U updated in turn by the
+// same four waves and a tangent-form rotation).  Slower: every thread
+// computing its own rotations (28; 33 with both overlapped), which saves the
+// exchange but repeats the square roots in all waves.  Rotating only across
+// the two blocks after a sweep's first round halves the inner rounds (21 us)
+// but takes 38% more sweeps.
 template <class T>
 __device__ void pair_body(const T* __restrict__ G, int64_t ldg, int k, int nb, int round,
                           int pair, double thr, T* __restrict__ ubuf, int* __restrict__ flags,
                           T* S, T* U) {
   __shared__ double rcs[JB], rsn[JB];
   __shared__ T rph[JB];
-  __shared__ int ra[JB], rb[JB], rrot[JB];
-  __shared__ int any;
+  __shared__ int rrot[JB];
+  __shared__ int any, turn;
   const int tid = threadIdx.x;
   const int bp = rr_player(nb, round, pair), bq = rr_player(nb, round, nb - 1 - pair);
   auto gidx = [&](int l) { return l < JB ? bp * JB + l : bq * JB + (l - JB); };
   if (tid == 0) any = 0;
-  for (int e = tid; e < JM * JM; e += JT) {
+  for (int e = tid; e < JM * JM; e += JPT) {
     const int r = e % JM, c = e / JM;
     const int gr = gidx(r), gc = gidx(c);
     T v = from_real<T>(0.0);
@@ -121,9 +141,11 @@ __device__ void pair_body(const T* __restrict__ G, int64_t ldg, int k, int nb, i
     U[c * JLD + r] = from_real<T>(r == c ? 1.0 : 0.0);
   }
   __syncthreads();
+  const int half = tid / JT, t = tid % JT;
+  const int j = t / JB, i = t % JB;
   for (int rr = 0; rr < JM - 1; ++rr) {
     if (tid < JB) {
-      const int a = rr_player(JM, rr, tid), b = rr_player(JM, rr, JM - 1 - tid);
+      const int a = inner_player(rr, tid), b = inner_player(rr, JM - 1 - tid);
       double cs, sn;
       T ph;
       const int rot = jac_rotation(real_(S[a * JLD + a]), real_(S[b * JLD + b]), S[b * JLD + a],
@@ -131,50 +153,56 @@ __device__ void pair_body(const T* __restrict__ G, int64_t ldg, int k, int nb, i
       rcs[tid] = cs;
       rsn[tid] = sn;
       rph[tid] = ph;
-      ra[tid] = a;
-      rb[tid] = b;
       rrot[tid] = rot;
-      if (rot) any = 1;
+      const bool some = __any(rot);
+      if (tid == 0) {
+        turn = some;
+        if (some) any = 1;
+      }
     }
+    const int aj = inner_player(rr, j), bj = inner_player(rr, JM - 1 - j);
+    const int ai = inner_player(rr, i), bi = inner_player(rr, JM - 1 - i);
     __syncthreads();
-    // S <- u^H S u on the 2 x 2 blocks (rows of pair i, columns of pair j)
-    for (int e = tid; e < JB * JB; e += JT) {
-      const int j = e / JB, i = e % JB;
-      const int ai = ra[i], bi = rb[i], aj = ra[j], bj = rb[j];
-      const double ci = rcs[i], si = rsn[i], cj = rcs[j], sj = rsn[j];
-      const T pi_ = rph[i], pjc = conj_(rph[j]);
-      // u_i^H M u_j = R_i^T (D_i^H M D_j) R_j: phases first, then the real
-      // rotations
-      const T m00 = S[aj * JLD + ai];
-      const T m01 = S[bj * JLD + ai] * pjc;
-      const T m10 = pi_ * S[aj * JLD + bi];
-      const T m11 = S[bj * JLD + bi] * (pi_ * pjc);
-      const T r00 = m00 * cj - m01 * sj, r01 = m00 * sj + m01 * cj;
-      const T r10 = m10 * cj - m11 * sj, r11 = m10 * sj + m11 * cj;
-      T n00 = r00 * ci - r10 * si, n01 = r01 * ci - r11 * si;
-      T n10 = r00 * si + r10 * ci, n11 = r01 * si + r11 * ci;
-      if (i == j) {
-        // the pivot block: exactly diagonal and real after its rotation
-        n00 = from_real<T>(real_(n00));
-        n11 = from_real<T>(real_(n11));
-        if (rrot[i]) {
-          n01 = from_real<T>(0.0);
-          n10 = from_real<T>(0.0);
+    if (turn) {  // the same in every thread
+      const double cj = rcs[j], sj = rsn[j];
+      const T pjc = conj_(rph[j]);
+      if (half == 0) {
+        // S <- u^H S u on the 2 x 2 block (rows of pair i, columns of pair j)
+        const double ci = rcs[i], si = rsn[i];
+        const T pi_ = rph[i];
+        // u_i^H M u_j = R_i^T (D_i^H M D_j) R_j: phases first, then the real
+        // rotations
+        const T m00 = S[aj * JLD + ai];
+        const T m01 = S[bj * JLD + ai] * pjc;
+        const T m10 = pi_ * S[aj * JLD + bi];
+        const T m11 = S[bj * JLD + bi] * (pi_ * pjc);
+        const T r00 = m00 * cj - m01 * sj, r01 = m00 * sj + m01 * cj;
+        const T r10 = m10 * cj - m11 * sj, r11 = m10 * sj + m11 * cj;
+        T n00 = r00 * ci - r10 * si, n01 = r01 * ci - r11 * si;
+        T n10 = r00 * si + r10 * ci, n11 = r01 * si + r11 * ci;
+        if (i == j) {
+          // the pivot block: exactly diagonal and real after its rotation
+          n00 = from_real<T>(real_(n00));
+          n11 = from_real<T>(real_(n11));
+          if (rrot[i]) {
+            n01 = from_real<T>(0.0);
+            n10 = from_real<T>(0.0);
+          }
+        }
+        S[aj * JLD + ai] = n00;
+        S[bj * JLD + ai] = n01;
+        S[aj * JLD + bi] = n10;
+        S[bj * JLD + bi] = n11;
+      } else {
+        // U <- U u on the columns of pair j, rows i and i + JB
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int rho = i + h * JB;
+          const T u0 = U[aj * JLD + rho], u1 = U[bj * JLD + rho] * pjc;
+          U[aj * JLD + rho] = u0 * cj - u1 * sj;
+          U[bj * JLD + rho] = u0 * sj + u1 * cj;
         }
       }
-      S[aj * JLD + ai] = n00;
-      S[bj * JLD + ai] = n01;
-      S[aj * JLD + bi] = n10;
-      S[bj * JLD + bi] = n11;
-    }
-    // U <- U u on the columns of each pair
-    for (int e = tid; e < JM * JB; e += JT) {
-      const int rho = e % JM, j = e / JM;
-      const int aj = ra[j], bj = rb[j];
-      const double cj = rcs[j], sj = rsn[j];
-      const T u0 = U[aj * JLD + rho], u1 = U[bj * JLD + rho] * conj_(rph[j]);
-      U[aj * JLD + rho] = u0 * cj - u1 * sj;
-      U[bj * JLD + rho] = u0 * sj + u1 * cj;
     }
     __syncthreads();
   }
@@ -183,33 +211,34 @@ __device__ void pair_body(const T* __restrict__ G, int64_t ldg, int k, int nb, i
   // inner round, and applying a non-unitary J^H G J shifts the eigenvalues by
   // that much in every round; the step brings it back to rounding level.
   // M = U^H U goes into S (no longer needed).
-  const int i = tid % JM, cg = tid / JM;
+  const int row = tid % JM, cg = tid / JM;
+  constexpr int PCG = JPT / JM, PM = JM / PCG;  // columns per thread
   if (any) {
 #pragma unroll
-    for (int m = 0; m < JM / JCG; ++m) {
-      const int c = cg + JCG * m;
+    for (int m = 0; m < PM; ++m) {
+      const int c = cg + PCG * m;
       T acc = from_real<T>(0.0);
 #pragma unroll 4
-      for (int l = 0; l < JM; ++l) mac(acc, conj_(U[i * JLD + l]), U[c * JLD + l]);
-      S[c * JLD + i] = acc;
+      for (int l = 0; l < JM; ++l) mac(acc, conj_(U[row * JLD + l]), U[c * JLD + l]);
+      S[c * JLD + row] = acc;
     }
     __syncthreads();
-    T nu[JM / JCG];
+    T nu[PM];
 #pragma unroll
-    for (int m = 0; m < JM / JCG; ++m) {
-      const int c = cg + JCG * m;
+    for (int m = 0; m < PM; ++m) {
+      const int c = cg + PCG * m;
       T acc = from_real<T>(0.0);
 #pragma unroll 4
-      for (int l = 0; l < JM; ++l) mac(acc, U[l * JLD + i], S[c * JLD + l]);
-      nu[m] = U[c * JLD + i] * 1.5 - acc * 0.5;
+      for (int l = 0; l < JM; ++l) mac(acc, U[l * JLD + row], S[c * JLD + l]);
+      nu[m] = U[c * JLD + row] * 1.5 - acc * 0.5;
     }
     __syncthreads();
 #pragma unroll
-    for (int m = 0; m < JM / JCG; ++m) U[(cg + JCG * m) * JLD + i] = nu[m];
+    for (int m = 0; m < PM; ++m) U[(cg + PCG * m) * JLD + row] = nu[m];
     __syncthreads();
   }
   T* Uo = ubuf + (int64_t)pair * JM * JM;
-  for (int e = tid; e < JM * JM; e += JT) Uo[e] = U[(e / JM) * JLD + (e % JM)];
+  for (int e = tid; e < JM * JM; e += JPT) Uo[e] = U[(e / JM) * JLD + (e % JM)];
   if (tid == 0) flags[pair] = any;
 }
 
@@ -269,7 +298,7 @@ __device__ void vtile_body(T* __restrict__ V, int64_t ldv, int k, int nb, int ro
   auto gb = [&](int l) { return l < JB ? b0 * JB + l : b1 * JB + (l - JB); };
   const T* Ub = ubuf + (int64_t)b * JM * JM;
   const int64_t r0 = (int64_t)chunk * JM;
-  for (int e = tid; e < JM * JM; e += JT) {
+  for (int e = tid; e < JM * JM; e += JPT) {
     const int r = e % JM, c = e / JM;
     const int gc = gb(c);
     T v = from_real<T>(0.0);
@@ -278,6 +307,7 @@ __device__ void vtile_body(T* __restrict__ V, int64_t ldv, int k, int nb, int ro
     Bs[r * JLD + c] = Ub[e];
   }
   __syncthreads();
+  if (tid >= JT) return;  // four waves, one quadrant each
   T out[4];
   tile_mma(Xs, Bs, out);
   const int64_t row = r0 + mma_row();
@@ -294,7 +324,7 @@ __device__ void vtile_body(T* __restrict__ V, int64_t ldv, int k, int nb, int ro
 // The two halves touch disjoint memory (G is only read, V only by the
 // second), so they run side by side.
 template <class T>
-__global__ __launch_bounds__(JT) void jac_stage1_k(const T* __restrict__ G, int64_t ldg,
+__global__ __launch_bounds__(JPT) void jac_stage1_k(const T* __restrict__ G, int64_t ldg,
                                                    T* __restrict__ V, int64_t ldv, int k, int nb,
                                                    int round, int npairs, double thr,
                                                    T* __restrict__ ubuf, int* __restrict__ flags,
@@ -508,7 +538,7 @@ struct JacobiRunner {
         const bool pairs = r < nb - 1, vupd = r > 0;
         const int cur = r & 1, prev = (r + 1) & 1;
         hipLaunchKernelGGL(jac_stage1_k<T>, dim3((pairs ? P : 0) + (vupd ? tiles_v : 0)),
-                           dim3(JT), 0, st, static_cast<const T*>(Gt), ldg, Vt, ldv, k, nb, r,
+                           dim3(JPT), 0, st, static_cast<const T*>(Gt), ldg, Vt, ldv, k, nb, r,
                            pairs ? P : 0, thr, ubuf[cur], flags[cur], r - 1,
                            static_cast<const T*>(ubuf[prev]),
                            static_cast<const int*>(flags[prev]));
