@@ -2,7 +2,6 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
-#include <rocblas/rocblas.h>
 
 #include <cstdint>
 #include <stdexcept>
@@ -239,7 +238,7 @@ void crt_prepare_h(bool cplx, const void* H, int64_t ldh, int64_t n, const CrtBa
 // One filter step with the EPI_CHEB epilogue (GemmArgs as for gemm(); A must
 // be the H whose planes hbuf holds), products on the INT8 matrix cores.
 void crt_cheb(bool cplx, const GemmArgs& g, const CrtBasis& B, const void* hbuf, void* xbuf,
-              int kmax, rocblas_handle rb, hipStream_t st);
+              int kmax, hipStream_t st);
 
 // ------------------------------------------------------------------ Cholesky
 // A = R^H R for the Hermitian positive definite k x k matrix A (ld lda,

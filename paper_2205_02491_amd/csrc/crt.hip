@@ -19,14 +19,13 @@
 // the conjugate of column i, which makes the conversion of H read contiguous
 // memory.  The residue planes of H are built once per solve; those of the
 // block at every step.  The N (complex: 3N) INT8 products of a step are one
-// strided-batched rocBLAS call; the reconstruction kernel applies the
-// Chebyshev step of Eq. (3) (and the defect-correction term) on the way out.
+// launch, whose epilogue reduces each INT32 product modulo its plane's modulus
+// to a byte; the reconstruction kernel applies the Chebyshev step of Eq. (3)
+// (and the defect-correction term) on the way out.
 #include "common.h"
 
-#include <rocblas/rocblas.h>
-
 #include <cmath>
-#include <vector>
+#include <utility>
 
 namespace chase {
 namespace {
@@ -60,6 +59,226 @@ __device__ __forceinline__ int exp2_above(double v) {
   int e = 0;
   if (v > 0.0) (void)frexp(v, &e);
   return e;
+}
+
+// Plane layout: rows of H's planes and columns of the block's are contiguous
+// along K and padded with zeros to ld(n) = n rounded up to 16 bytes, so that
+// every 16-byte piece is aligned and lies within one row.
+constexpr int64_t plane_ld(int64_t n) { return (n + 15) / 16 * 16; }
+
+// ------------------------------------------------------------------ INT8 products
+// Residues of the P products C_p = A_p B_p: A_p the n x n plane of H (row-major),
+// B_p the n x cols plane of the block (column-major); out[p][j ld + i] = C_p(i,
+// j) mod m_p in [0, m_p), one byte (a quarter of the INT32 products' bytes, here
+// and where the reconstruction reads them).
+//
+// Eight waves, 4 x 2 of 64 rows x 16 FN columns, share a tile of 256 rows x 32
+// FN columns; a wave's part is 4 x FN MFMAs of 16 x 16 x 64.  Both operands go
+// global -> LDS by the direct LDS loads (16 bytes a lane, no registers) in K
+// chunks of 128 bytes, into GST stages.  A row's eight pieces are XOR-swizzled
+// so that the 16 rows a read touches fall into different banks.  Fragment f of
+// a wave holds rows 16 (l / 4) + 4 f + l % 4 (l = lane % 16): then the four
+// fragments' accumulators of a lane are 16 consecutive rows of one column, and
+// their residues go out as one 16-byte store.
+//
+// Bound by the rate at which a compute unit's tiles arrive (the planes of H
+// are beyond the caches), so the largest tile wins: 14 moduli, complex, n=4000
+// with 260 columns 309 us (1130 TOP/s; 480 us the library's batched GEMM, which
+// also wrote INT32), n=20000 with 1300 23.8 ms (1833 TOP/s).  Slower: half as
+// deep chunks in four stages (347 us: half cache lines), operands staged in
+// registers (396), H's fragments straight from memory (318 - 412).
+typedef int i4v __attribute__((ext_vector_type(4)));
+
+constexpr int GKC = 128;  // K chunk (bytes)
+constexpr int GPC = GKC / 16;
+constexpr int GTM = 256;  // rows of a tile
+constexpr int GNT = 512;
+
+// source of the block's pieces past the end of K
+__device__ const i4v crt_zero_piece = {0, 0, 0, 0};
+
+template <int FN, int GST>
+__global__ __launch_bounds__(GNT, 2) void crt_gemm_k(const int8_t* __restrict__ Ap,
+                                                     const int8_t* __restrict__ Bp, int n, int ld,
+                                                     int cols, CrtBasis basis, int per_mod,
+                                                     uint8_t* __restrict__ out, int tiles_m,
+                                                     int tiles_n, int ntiles) {
+  constexpr int FM = 4;
+  constexpr int BN = 32 * FN;                  // columns of the tile
+  constexpr int ABLK = GTM / 8, BBLK = BN / 8;    // wave loads of 1 KB: 8 rows each
+  constexpr int LOADS = (ABLK + BBLK + 7) / 8;    // per wave and chunk
+  constexpr int STAGE = (GTM + BN) * GKC;
+  __shared__ __attribute__((aligned(256))) char lds[GST * STAGE];
+  // XCD-aware order: each XCD works on a contiguous range of tiles, column
+  // tiles fastest, so that those sharing rows of H run together on one L2
+  const int per_xcd = gridDim.x >> 3;
+  const int t = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (t >= ntiles) return;
+  const int tn = t % tiles_n, tmp = t / tiles_n;
+  const int tm = tmp % tiles_m, plane = tmp / tiles_m;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int l16 = lane & 15, lk = lane >> 4;
+  const int8_t* A = Ap + (int64_t)plane * n * ld;
+  const int8_t* B = Bp + (int64_t)plane * cols * ld;
+  const int n0 = tn * BN;
+
+  // The piece a lane copies into its place (row lane / 4, slot lane % 4 of a
+  // block of 16 rows): piece p of a row sits in slot p ^ key, an involution.
+  // Rows and columns past the end are clamped: their products are not stored.
+  auto akey = [](int r) { return ((r >> 1) & 1) | ((r >> 3) & 6); };
+  auto bkey = [](int r) { return (r >> 1) & 7; };
+  const int8_t* src[LOADS];
+  int kpos[LOADS];
+  bool isb[LOADS];
+#pragma unroll
+  for (int e = 0; e < LOADS; ++e) {
+    int blk = wave + 8 * e;
+    if (blk >= ABLK + BBLK) blk = ABLK + BBLK - 1;  // again the last block
+    isb[e] = blk >= ABLK;
+    const int r = (isb[e] ? blk - ABLK : blk) * 8 + (lane >> 3);
+    const int piece = (lane & 7) ^ (isb[e] ? bkey(r) : akey(r));
+    if (isb[e]) {
+      const int j = n0 + r;
+      src[e] = B + (int64_t)(j < cols ? j : cols - 1) * ld + 16 * piece;
+    } else {
+      const int i = tm * GTM + r;
+      src[e] = A + (int64_t)(i < n ? i : n - 1) * ld + 16 * piece;
+    }
+    kpos[e] = 16 * piece;
+  }
+  const int chunks = (ld + GKC - 1) / GKC;
+  auto issue = [&](int c) {
+    // past the last chunk the copies repeat it, into a stage nobody reads, so
+    // that the number in flight stays what the waits below count
+    const int cc = c < chunks ? c : chunks - 1;
+    const int k0 = cc * GKC;
+    char* base = lds + (c % GST) * STAGE;
+#pragma unroll
+    for (int e = 0; e < LOADS; ++e) {
+      int blk = wave + 8 * e;
+      if (blk >= ABLK + BBLK) blk = ABLK + BBLK - 1;
+      const int8_t* p = src[e] + k0;
+      if (k0 + kpos[e] >= ld)  // the last chunk: zeros for B, any bytes for A
+        p = isb[e] ? reinterpret_cast<const int8_t*>(&crt_zero_piece) : src[e] - kpos[e];
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)p,
+                                       (__attribute__((address_space(3))) void*)(base + blk * 1024),
+                                       16, 0, 0);
+    }
+  };
+
+  i4v acc[FM][FN];
+#pragma unroll
+  for (int f = 0; f < FM; ++f)
+#pragma unroll
+    for (int g = 0; g < FN; ++g) acc[f][g] = i4v{0, 0, 0, 0};
+
+  // byte offsets of this lane's pieces within a stage
+  int ao[FM], bo[FN];
+#pragma unroll
+  for (int f = 0; f < FM; ++f) {
+    const int r = wm * 64 + 16 * (l16 >> 2) + 4 * f + (l16 & 3);
+    ao[f] = r * GKC + 16 * (lk ^ akey(r));
+  }
+#pragma unroll
+  for (int g = 0; g < FN; ++g) {
+    const int r = wn * (16 * FN) + 16 * g + l16;
+    bo[g] = GTM * GKC + r * GKC + 16 * (lk ^ bkey(r));
+  }
+
+  constexpr int AHEAD = GST - 1;
+  constexpr int INFLIGHT = (AHEAD - 1) * LOADS;  // copies of the later chunks
+  static_assert(INFLIGHT < 64, "vmcnt range");
+#pragma unroll
+  for (int c = 0; c < AHEAD; ++c) issue(c);
+  for (int c = 0; c < chunks; ++c) {
+    // chunk c has landed, and every wave is done with chunk c - 1's stage,
+    // which chunk c + AHEAD then fills
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt((INFLIGHT & 15) | (7 << 4) | ((INFLIGHT >> 4) << 14));
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    issue(c + AHEAD);
+    const char* st = lds + (c % GST) * STAGE;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      i4v av[FM];
+#pragma unroll
+      for (int f = 0; f < FM; ++f) av[f] = *reinterpret_cast<const i4v*>(st + (ao[f] ^ (64 * h)));
+#pragma unroll
+      for (int g = 0; g < FN; ++g) {
+        const i4v bv = *reinterpret_cast<const i4v*>(st + (bo[g] ^ (64 * h)));
+#pragma unroll
+        for (int f = 0; f < FM; ++f)
+          acc[f][g] = __builtin_amdgcn_mfma_i32_16x16x64_i8(av[f], bv, acc[f][g], 0, 0, 0);
+      }
+    }
+  }
+  // no copy may land in LDS after the workgroup has ended
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x70);  // vmcnt(0) lgkmcnt(0)
+  asm volatile("" ::: "memory");
+
+  // residues: acc[f][g][r] is row i0 + 4 f + r of column 16 g + l16
+  const int m = basis.m[plane / per_mod];
+  const double minv = 1.0 / (double)m;
+  const int i0 = tm * GTM + wm * 64 + 16 * lk;
+#pragma unroll
+  for (int g = 0; g < FN; ++g) {
+    const int j = n0 + wn * (16 * FN) + 16 * g + l16;
+    if (j >= cols || i0 >= ld) continue;
+    i4v w;
+#pragma unroll
+    for (int f = 0; f < FM; ++f) {
+      uint32_t x = 0;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) x |= (uint32_t)ures32(acc[f][g][r], m, minv) << (8 * r);
+      w[f] = (int)x;
+    }
+    *reinterpret_cast<i4v*>(out + ((int64_t)plane * cols + j) * ld + i0) = w;
+  }
+}
+
+template <int FN, int GST>
+void crt_gemm_launch(const int8_t* A, const int8_t* B, int64_t n, int cols, const CrtBasis& basis,
+                     int per_mod, uint8_t* out, hipStream_t st) {
+  const int64_t tm = (n + GTM - 1) / GTM, tn = (cols + 32 * FN - 1) / (32 * FN);
+  const int64_t nt = tm * tn * per_mod * basis.n_mod;
+  CHASE_REQUIRE(nt <= INT32_MAX - 8, "INT8 products: too many tiles");
+  hipLaunchKernelGGL((crt_gemm_k<FN, GST>), dim3((unsigned)((nt + 7) / 8 * 8)), dim3(GNT), 0, st, A, B,
+                     (int)n, (int)plane_ld(n), cols, basis, per_mod, out, (int)tm, (int)tn, (int)nt);
+  CHASE_HIP(hipGetLastError());
+}
+
+void crt_gemm(const int8_t* A, const int8_t* B, int64_t n, int cols, const CrtBasis& basis,
+              int per_mod, uint8_t* out, hipStream_t st) {
+  // column tile with the least work on the busiest of the 256 compute units:
+  // rounds of tiles times columns, over the rate (TOP/s on n=20000) its width
+  // reaches
+  static constexpr struct {
+    int fn;
+    double rate;
+  } tiles[] = {{9, 2030}, {8, 2007}, {6, 1711}, {4, 1521}, {2, 1132}, {1, 646}};
+  int fn = 0;
+  double cost = 0.0;
+  for (const auto& t : tiles) {
+    const int64_t nt = (n + GTM - 1) / GTM * ((cols + 32 * t.fn - 1) / (32 * t.fn)) * per_mod *
+                       basis.n_mod;
+    const double c = (double)((nt + 255) / 256) * t.fn / t.rate;
+    if (fn == 0 || c < cost) {
+      fn = t.fn;
+      cost = c;
+    }
+  }
+  switch (fn) {
+    case 9: return crt_gemm_launch<9, 2>(A, B, n, cols, basis, per_mod, out, st);
+    case 8: return crt_gemm_launch<8, 2>(A, B, n, cols, basis, per_mod, out, st);
+    case 6: return crt_gemm_launch<6, 2>(A, B, n, cols, basis, per_mod, out, st);
+    case 4: return crt_gemm_launch<4, 3>(A, B, n, cols, basis, per_mod, out, st);
+    case 2: return crt_gemm_launch<2, 3>(A, B, n, cols, basis, per_mod, out, st);
+    default: return crt_gemm_launch<1, 3>(A, B, n, cols, basis, per_mod, out, st);
+  }
 }
 
 // sigma[i] = pa - e_i, 2^(e_i - 1) <= max_j |H_ij| (real and imaginary parts)
@@ -99,86 +318,28 @@ __global__ __launch_bounds__(TPB) void crt_colexp_k(const double* __restrict__ X
   if (threadIdx.x == 0) tau[j] = red[0] > 0.0 ? pb - exp2_above(red[0]) : 0;
 }
 
-// Residue planes of H, row-major (element (i, j) at i n + j: the column-major
-// transpose, the A operand of a transposed GEMM).  Complex: planes 3t+0 (Re),
+// Residue planes of H, row-major (element (i, j) at i ld + j).  Complex: planes 3t+0 (Re),
 // 3t+1 (Im), 3t+2 (Re + Im) of modulus t; real: plane t.  Row i of H is
 // conj(column i): Re H_ij = Re H[j + i ldh], Im H_ij = -Im H[j + i ldh].
+// Four consecutive entries per thread: the residues of each plane go out as
+// one packed 32-bit store (byte e = entry e; entries past n are zero).
 template <bool CPLX>
 __global__ __launch_bounds__(TPB) void crt_hplanes_k(const double* __restrict__ H, int64_t ldh,
-                                                     int64_t n, const int* __restrict__ sigma,
-                                                     CrtBasis B, int8_t* __restrict__ planes) {
-  const int64_t i = blockIdx.y;
-  const int64_t j = (int64_t)blockIdx.x * TPB + threadIdx.x;
-  if (j >= n) return;
-  const int s = sigma[i];
-  const int64_t o = i * n + j;
-  const int64_t plane = n * n;
-  if constexpr (CPLX) {
-    const double re = rint(ldexp(H[2 * (j + i * ldh)], s));
-    const double im = rint(ldexp(-H[2 * (j + i * ldh) + 1], s));
-    const double sm = re + im;
-    for (int t = 0; t < B.n_mod; ++t) {
-      const int m = B.m[t];
-      const double minv = 1.0 / (double)m;
-      planes[(3 * t + 0) * plane + o] = (int8_t)bres(re, m, minv);
-      planes[(3 * t + 1) * plane + o] = (int8_t)bres(im, m, minv);
-      planes[(3 * t + 2) * plane + o] = (int8_t)bres(sm, m, minv);
-    }
-  } else {
-    const double v = rint(ldexp(H[j + i * ldh], s));
-    for (int t = 0; t < B.n_mod; ++t)
-      planes[t * plane + o] = (int8_t)bres(v, B.m[t], 1.0 / (double)B.m[t]);
-  }
-}
-
-// Residue planes of the block X (n x cols, column-major, ld n per plane).
-template <bool CPLX>
-__global__ __launch_bounds__(TPB) void crt_xplanes_k(const double* __restrict__ X, int64_t ldx,
-                                                     int64_t n, int cols,
-                                                     const int* __restrict__ tau, CrtBasis B,
-                                                     int8_t* __restrict__ planes) {
-  const int64_t j = blockIdx.y;
-  const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
-  if (i >= n) return;
-  const int s = tau[j];
-  const int64_t o = j * n + i;
-  const int64_t plane = n * (int64_t)cols;
-  if constexpr (CPLX) {
-    const double re = rint(ldexp(X[2 * (i + j * ldx)], s));
-    const double im = rint(ldexp(X[2 * (i + j * ldx) + 1], s));
-    const double sm = re + im;
-    for (int t = 0; t < B.n_mod; ++t) {
-      const int m = B.m[t];
-      const double minv = 1.0 / (double)m;
-      planes[(3 * t + 0) * plane + o] = (int8_t)bres(re, m, minv);
-      planes[(3 * t + 1) * plane + o] = (int8_t)bres(im, m, minv);
-      planes[(3 * t + 2) * plane + o] = (int8_t)bres(sm, m, minv);
-    }
-  } else {
-    const double v = rint(ldexp(X[i + j * ldx], s));
-    for (int t = 0; t < B.n_mod; ++t)
-      planes[t * plane + o] = (int8_t)bres(v, B.m[t], 1.0 / (double)B.m[t]);
-  }
-}
-
-// Four consecutive entries per thread (n a multiple of 4): the residues of
-// each plane go out as one packed 32-bit store (byte e = entry e).
-template <bool CPLX>
-__global__ __launch_bounds__(TPB) void crt_hplanes4_k(const double* __restrict__ H, int64_t ldh,
                                                       int64_t n, const int* __restrict__ sigma,
                                                       CrtBasis B, int8_t* __restrict__ planes) {
   const int64_t i = blockIdx.y;
   const int64_t j0 = 4 * ((int64_t)blockIdx.x * TPB + threadIdx.x);
-  if (j0 >= n) return;
+  const int64_t ld = plane_ld(n);
+  if (j0 >= ld) return;
   const int s = sigma[i];
-  const int64_t o = i * n + j0;
-  const int64_t plane = n * n;
+  const int64_t o = i * ld + j0;
+  const int64_t plane = n * ld;
   if constexpr (CPLX) {
     double re[4], im[4], sm[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      re[e] = rint(ldexp(H[2 * (j0 + e + i * ldh)], s));
-      im[e] = rint(ldexp(-H[2 * (j0 + e + i * ldh) + 1], s));
+      re[e] = j0 + e < n ? rint(ldexp(H[2 * (j0 + e + i * ldh)], s)) : 0.0;
+      im[e] = j0 + e < n ? rint(ldexp(-H[2 * (j0 + e + i * ldh) + 1], s)) : 0.0;
       sm[e] = re[e] + im[e];
     }
     for (int t = 0; t < B.n_mod; ++t) {
@@ -198,7 +359,8 @@ __global__ __launch_bounds__(TPB) void crt_hplanes4_k(const double* __restrict__
   } else {
     double v[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = rint(ldexp(H[j0 + e + i * ldh], s));
+    for (int e = 0; e < 4; ++e)
+      v[e] = j0 + e < n ? rint(ldexp(H[j0 + e + i * ldh], s)) : 0.0;
     for (int t = 0; t < B.n_mod; ++t) {
       uint32_t w = 0;
 #pragma unroll
@@ -209,23 +371,25 @@ __global__ __launch_bounds__(TPB) void crt_hplanes4_k(const double* __restrict__
   }
 }
 
+// Residue planes of the block X (n x cols, column-major, ld per plane).
 template <bool CPLX>
-__global__ __launch_bounds__(TPB) void crt_xplanes4_k(const double* __restrict__ X, int64_t ldx,
+__global__ __launch_bounds__(TPB) void crt_xplanes_k(const double* __restrict__ X, int64_t ldx,
                                                       int64_t n, int cols,
                                                       const int* __restrict__ tau, CrtBasis B,
                                                       int8_t* __restrict__ planes) {
   const int64_t j = blockIdx.y;
   const int64_t i0 = 4 * ((int64_t)blockIdx.x * TPB + threadIdx.x);
-  if (i0 >= n) return;
+  const int64_t ld = plane_ld(n);
+  if (i0 >= ld) return;
   const int s = tau[j];
-  const int64_t o = j * n + i0;
-  const int64_t plane = n * (int64_t)cols;
+  const int64_t o = j * ld + i0;
+  const int64_t plane = ld * (int64_t)cols;
   if constexpr (CPLX) {
     double re[4], im[4], sm[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      re[e] = rint(ldexp(X[2 * (i0 + e + j * ldx)], s));
-      im[e] = rint(ldexp(X[2 * (i0 + e + j * ldx) + 1], s));
+      re[e] = i0 + e < n ? rint(ldexp(X[2 * (i0 + e + j * ldx)], s)) : 0.0;
+      im[e] = i0 + e < n ? rint(ldexp(X[2 * (i0 + e + j * ldx) + 1], s)) : 0.0;
       sm[e] = re[e] + im[e];
     }
     for (int t = 0; t < B.n_mod; ++t) {
@@ -245,7 +409,8 @@ __global__ __launch_bounds__(TPB) void crt_xplanes4_k(const double* __restrict__
   } else {
     double v[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = rint(ldexp(X[i0 + e + j * ldx], s));
+    for (int e = 0; e < 4; ++e)
+      v[e] = i0 + e < n ? rint(ldexp(X[i0 + e + j * ldx], s)) : 0.0;
     for (int t = 0; t < B.n_mod; ++t) {
       uint32_t w = 0;
 #pragma unroll
@@ -270,83 +435,48 @@ __device__ __forceinline__ float fmod_m(float x, float m, float minv) {
   return r;
 }
 
+// (m_0 m_1 ... m_{s-1}) mod m_t
+constexpr int radix_mod(int s, int t) {
+  int p = 1;
+  for (int i = 0; i < s; ++i) p = p * (kModuli[i] % kModuli[t]) % kModuli[t];
+  return p;
+}
+
+// One digit: (v_0 + m_0 v_1 + m_0 m_1 v_2 + ...) mod m_t as a sum with the
+// radices already reduced modulo m_t, and one reduction at its end.
+template <int T, int... S>
+__device__ __forceinline__ float known_digits(const float* v, std::integer_sequence<int, S...>) {
+  float acc = 0.f;
+  ((acc = fmaf(v[S], (float)radix_mod(S, T), acc)), ...);
+  return acc;
+}
+template <int NM, int T>
+__device__ __forceinline__ void garner_digit(const int (&r)[NM], float (&v)[NM],
+                                             const CrtBasis& B) {
+  const float m = (float)kModuli[T], minv = 1.0f / (float)kModuli[T];
+  float d = fmod_m((float)r[T] - known_digits<T>(v, std::make_integer_sequence<int, T>{}), m, minv);
+  d = fmod_m(d * (float)B.inv[T], m, minv);
+  if (d > (m - 1.f) * 0.5f) d -= m;
+  v[T] = d;
+}
+template <int NM, int... T>
+__device__ __forceinline__ void garner_digits(const int (&r)[NM], float (&v)[NM],
+                                              const CrtBasis& B, std::integer_sequence<int, T...>) {
+  (garner_digit<NM, T>(r, v, B), ...);
+}
+
 template <int NM>
 __device__ __forceinline__ double garner(const int (&r)[NM], const CrtBasis& B) {
-  // every intermediate is an integer below 2^17 in magnitude, exact in FP32,
-  // whose multiply-adds run at full rate (32-bit integer multiplies do not)
+  // every intermediate is an integer below 2^19 in magnitude (15 digits of at
+  // most 128 times radices below 256), exact in FP32, whose multiply-adds run
+  // at full rate (32-bit integer multiplies do not).  Reducing after every
+  // digit, Horner's way, took 65 us for 4000 x 260 complex entries
   float v[NM];
-#pragma unroll
-  for (int t = 0; t < NM; ++t) {
-    const float m = (float)kModuli[t], minv = 1.0f / (float)kModuli[t];
-    // (v_0 + m_0 (v_1 + ... + m_{t-2} v_{t-1})) mod m_t
-    float acc = 0.f;
-#pragma unroll
-    for (int s = t - 1; s >= 0; --s) acc = fmod_m(fmaf(acc, (float)kModuli[s], v[s]), m, minv);
-    float d = fmod_m((float)r[t] - acc, m, minv);
-    d = fmod_m(d * (float)B.inv[t], m, minv);
-    if (d > (m - 1.f) * 0.5f) d -= m;
-    v[t] = d;
-  }
+  garner_digits<NM>(r, v, B, std::make_integer_sequence<int, NM>{});
   double x = 0.0;
 #pragma unroll
   for (int t = NM - 1; t >= 0; --t) x = fma(x, (double)kModuli[t], (double)v[t]);
   return x;
-}
-
-// out(i, j) = alpha (C(i, j) - gamma Xs(i, j)) + beta out(i, j)
-//             [+ colcoef[j] F(i, j)],  C = H Xs from the INT32 residue products.
-template <bool CPLX, int NM>
-__global__ __launch_bounds__(TPB) void crt_cheb_k(const int32_t* __restrict__ P, int64_t n,
-                                                  int cols, CrtBasis B,
-                                                  const int* __restrict__ sigma,
-                                                  const int* __restrict__ tau, GemmArgs g) {
-  const int64_t j = blockIdx.y;
-  const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
-  if (i >= n) return;
-  const int64_t plane = n * (int64_t)cols;
-  const int64_t o = j * n + i;
-  const int e = -(sigma[i] + tau[j]);
-  const double* Xs = static_cast<const double*>(g.B);
-  double* Cd = static_cast<double*>(g.C);
-  const int64_t oc = i + j * g.ldc;
-  if constexpr (CPLX) {
-    int rr[NM], ri[NM];
-#pragma unroll
-    for (int t = 0; t < NM; ++t) {
-      const int m = kModuli[t];
-      const double minv = 1.0 / (double)m;
-      const int p1 = ures32(P[(3 * t + 0) * plane + o], m, minv);
-      const int p2 = ures32(P[(3 * t + 1) * plane + o], m, minv);
-      const int p3 = ures32(P[(3 * t + 2) * plane + o], m, minv);
-      rr[t] = (p1 - p2 + m) % m;
-      ri[t] = (p3 - p1 - p2 + 2 * m) % m;
-    }
-    double vr = ldexp(garner<NM>(rr, B), e), vi = ldexp(garner<NM>(ri, B), e);
-    vr = g.alpha * (vr - g.gamma * Xs[2 * (i + j * g.ldb)]);
-    vi = g.alpha * (vi - g.gamma * Xs[2 * (i + j * g.ldb) + 1]);
-    if (g.beta != 0.0) {
-      vr += g.beta * Cd[2 * oc];
-      vi += g.beta * Cd[2 * oc + 1];
-    }
-    if (g.colcoef) {
-      const double cj = g.colcoef[j];
-      const double* Fd = static_cast<const double*>(g.F);
-      vr += cj * Fd[2 * (i + j * g.ldf)];
-      vi += cj * Fd[2 * (i + j * g.ldf) + 1];
-    }
-    Cd[2 * oc] = vr;
-    Cd[2 * oc + 1] = vi;
-  } else {
-    int r[NM];
-#pragma unroll
-    for (int t = 0; t < NM; ++t)
-      r[t] = ures32(P[t * plane + o], kModuli[t], 1.0 / (double)kModuli[t]);
-    double v = ldexp(garner<NM>(r, B), e);
-    v = g.alpha * (v - g.gamma * Xs[i + j * g.ldb]);
-    if (g.beta != 0.0) v += g.beta * Cd[oc];
-    if (g.colcoef) v += g.colcoef[j] * static_cast<const double*>(g.F)[i + j * g.ldf];
-    Cd[oc] = v;
-  }
 }
 
 // The epilogue of one entry: out = alpha (c - gamma Xs) + beta out [+ cj F].
@@ -379,41 +509,42 @@ __device__ __forceinline__ void cheb_store(const GemmArgs& g, int64_t i, int64_t
   }
 }
 
-// Four consecutive rows per thread (n a multiple of 4): 16-byte loads of the
-// INT32 products; the residues of the four entries are kept packed (one
-// byte each) until each entry's reconstruction.
+// out(i, j) = alpha (C(i, j) - gamma Xs(i, j)) + beta out(i, j)
+//             [+ colcoef[j] F(i, j)],  C = H Xs from the products' residues.
+// Four consecutive rows per thread (one 32-bit load per plane), the residues
+// kept packed, one byte each, until each entry's reconstruction.
 template <bool CPLX, int NM>
-__global__ __launch_bounds__(TPB) void crt_cheb4_k(const int32_t* __restrict__ P, int64_t n,
-                                                   int cols, CrtBasis B,
-                                                   const int* __restrict__ sigma,
-                                                   const int* __restrict__ tau, GemmArgs g) {
-  typedef int i4v __attribute__((ext_vector_type(4)));
+__global__ __launch_bounds__(TPB) void crt_cheb_k(const uint8_t* __restrict__ P, int64_t n,
+                                                  int cols, CrtBasis B,
+                                                  const int* __restrict__ sigma,
+                                                  const int* __restrict__ tau, GemmArgs g) {
   const int64_t j = blockIdx.y;
   const int64_t i0 = 4 * ((int64_t)blockIdx.x * TPB + threadIdx.x);
   if (i0 >= n) return;
-  const int64_t plane = n * (int64_t)cols;
-  const int64_t o = j * n + i0;
+  const int64_t ld = plane_ld(n);
+  const int64_t plane = ld * (int64_t)cols;
+  const int64_t o = j * ld + i0;
+  auto residues = [&](int p) { return *reinterpret_cast<const uint32_t*>(P + p * plane + o); };
   uint32_t pr[NM], pi[NM];
 #pragma unroll
   for (int t = 0; t < NM; ++t) {
     const int m = kModuli[t];
-    const double minv = 1.0 / (double)m;
     uint32_t wr = 0, wi = 0;
     if constexpr (CPLX) {
-      const i4v a = *reinterpret_cast<const i4v*>(P + (3 * t + 0) * plane + o);
-      const i4v b = *reinterpret_cast<const i4v*>(P + (3 * t + 1) * plane + o);
-      const i4v c = *reinterpret_cast<const i4v*>(P + (3 * t + 2) * plane + o);
+      const uint32_t a = residues(3 * t), b = residues(3 * t + 1), c = residues(3 * t + 2);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int p1 = ures32(a[e], m, minv), p2 = ures32(b[e], m, minv);
-        const int p3 = ures32(c[e], m, minv);
-        wr |= (uint32_t)((p1 - p2 + m) % m) << (8 * e);
-        wi |= (uint32_t)((p3 - p1 - p2 + 2 * m) % m) << (8 * e);
+        const int p1 = (a >> (8 * e)) & 0xff, p2 = (b >> (8 * e)) & 0xff;
+        const int p3 = (c >> (8 * e)) & 0xff;
+        int re = p1 - p2, im = p3 - p1 - p2;  // in (-m, m) and (-2m, m)
+        re += re < 0 ? m : 0;
+        im += im < 0 ? m : 0;
+        im += im < 0 ? m : 0;
+        wr |= (uint32_t)re << (8 * e);
+        wi |= (uint32_t)im << (8 * e);
       }
     } else {
-      const i4v a = *reinterpret_cast<const i4v*>(P + t * plane + o);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) wr |= (uint32_t)ures32(a[e], m, minv) << (8 * e);
+      wr = residues(t);
     }
     pr[t] = wr;
     pi[t] = wi;
@@ -424,6 +555,7 @@ __global__ __launch_bounds__(TPB) void crt_cheb4_k(const int32_t* __restrict__ P
 #pragma unroll 1
   for (int e = 0; e < 4; ++e) {
     const int64_t i = i0 + e;
+    if (i >= n) break;
     const int sc = -(sigma[i] + ej);
     int r[NM];
 #pragma unroll
@@ -440,21 +572,15 @@ __global__ __launch_bounds__(TPB) void crt_cheb4_k(const int32_t* __restrict__ P
 }
 
 template <bool CPLX, int NM>
-void launch_cheb(const int32_t* prod, int64_t n, int cols, const CrtBasis& B, const int* sigma,
+void launch_cheb(const uint8_t* prod, int64_t n, int cols, const CrtBasis& B, const int* sigma,
                  const int* tau, const GemmArgs& g, hipStream_t st) {
-  if (n % 4 == 0) {
-    const dim3 grid((unsigned)((n / 4 + TPB - 1) / TPB), (unsigned)cols);
-    hipLaunchKernelGGL((crt_cheb4_k<CPLX, NM>), grid, dim3(TPB), 0, st, prod, n, cols, B, sigma,
-                       tau, g);
-  } else {
-    const dim3 grid((unsigned)((n + TPB - 1) / TPB), (unsigned)cols);
-    hipLaunchKernelGGL((crt_cheb_k<CPLX, NM>), grid, dim3(TPB), 0, st, prod, n, cols, B, sigma,
-                       tau, g);
-  }
+  const dim3 grid((unsigned)(((n + 3) / 4 + TPB - 1) / TPB), (unsigned)cols);
+  hipLaunchKernelGGL((crt_cheb_k<CPLX, NM>), grid, dim3(TPB), 0, st, prod, n, cols, B, sigma, tau,
+                     g);
 }
 
 template <bool CPLX>
-void launch_cheb_nm(const int32_t* prod, int64_t n, int cols, const CrtBasis& B,
+void launch_cheb_nm(const uint8_t* prod, int64_t n, int cols, const CrtBasis& B,
                     const int* sigma, const int* tau, const GemmArgs& g, hipStream_t st) {
   switch (B.n_mod) {
     case 8: return launch_cheb<CPLX, 8>(prod, n, cols, B, sigma, tau, g, st);
@@ -512,13 +638,13 @@ inline size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 // byte offsets within the buffers: H planes | row exponents;
 // block planes | INT32 products | column exponents
 inline size_t h_planes_bytes(bool cplx, int64_t n, int n_mod) {
-  return align256((size_t)(cplx ? 3 : 1) * n_mod * n * n);
+  return align256((size_t)(cplx ? 3 : 1) * n_mod * n * plane_ld(n));
 }
 inline size_t x_planes_bytes(bool cplx, int64_t n, int kmax, int n_mod) {
-  return align256((size_t)(cplx ? 3 : 1) * n_mod * n * kmax);
+  return align256((size_t)(cplx ? 3 : 1) * n_mod * plane_ld(n) * kmax);
 }
 inline size_t x_prod_bytes(bool cplx, int64_t n, int kmax, int n_mod) {
-  return align256((size_t)(cplx ? 3 : 1) * n_mod * n * kmax * 4);
+  return align256((size_t)(cplx ? 3 : 1) * n_mod * plane_ld(n) * kmax * 4);
 }
 }  // namespace
 
@@ -536,74 +662,44 @@ void crt_prepare_h(bool cplx, const void* H, int64_t ldh, int64_t n, const CrtBa
   int8_t* planes = static_cast<int8_t*>(hbuf);
   int* sigma = reinterpret_cast<int*>(planes + h_planes_bytes(cplx, n, B.n_mod));
   const double* Hd = static_cast<const double*>(H);
-  const bool v4 = n % 4 == 0;
-  const dim3 grid((unsigned)(((v4 ? n / 4 : n) + TPB - 1) / TPB), (unsigned)n);
+  const dim3 grid((unsigned)((plane_ld(n) / 4 + TPB - 1) / TPB), (unsigned)n);
   if (cplx) {
     hipLaunchKernelGGL(crt_rowexp_k<true>, dim3((unsigned)n), dim3(TPB), 0, st, Hd, ldh, n, B.pa,
                        sigma);
-    if (v4)
-      hipLaunchKernelGGL(crt_hplanes4_k<true>, grid, dim3(TPB), 0, st, Hd, ldh, n,
-                         static_cast<const int*>(sigma), B, planes);
-    else
-      hipLaunchKernelGGL(crt_hplanes_k<true>, grid, dim3(TPB), 0, st, Hd, ldh, n,
-                         static_cast<const int*>(sigma), B, planes);
+    hipLaunchKernelGGL(crt_hplanes_k<true>, grid, dim3(TPB), 0, st, Hd, ldh, n,
+                       static_cast<const int*>(sigma), B, planes);
   } else {
     hipLaunchKernelGGL(crt_rowexp_k<false>, dim3((unsigned)n), dim3(TPB), 0, st, Hd, ldh, n, B.pa,
                        sigma);
-    if (v4)
-      hipLaunchKernelGGL(crt_hplanes4_k<false>, grid, dim3(TPB), 0, st, Hd, ldh, n,
-                         static_cast<const int*>(sigma), B, planes);
-    else
-      hipLaunchKernelGGL(crt_hplanes_k<false>, grid, dim3(TPB), 0, st, Hd, ldh, n,
-                         static_cast<const int*>(sigma), B, planes);
+    hipLaunchKernelGGL(crt_hplanes_k<false>, grid, dim3(TPB), 0, st, Hd, ldh, n,
+                       static_cast<const int*>(sigma), B, planes);
   }
   CHASE_HIP(hipGetLastError());
 }
 
 void crt_cheb(bool cplx, const GemmArgs& g, const CrtBasis& B, const void* hbuf, void* xbuf,
-              int kmax, rocblas_handle rb, hipStream_t st) {
+              int kmax, hipStream_t st) {
   const int64_t n = g.M;
   const int cols = (int)g.N;
   CHASE_REQUIRE(g.K == n && cols >= 1 && cols <= kmax, "INT8 filter step: shape");
-  const int P = (cplx ? 3 : 1) * B.n_mod;
   const int8_t* hplanes = static_cast<const int8_t*>(hbuf);
   const int* sigma = reinterpret_cast<const int*>(hplanes + h_planes_bytes(cplx, n, B.n_mod));
   int8_t* xplanes = static_cast<int8_t*>(xbuf);
-  int32_t* prod =
-      reinterpret_cast<int32_t*>(xplanes + x_planes_bytes(cplx, n, kmax, B.n_mod));
-  int* tau = reinterpret_cast<int*>(reinterpret_cast<char*>(prod) +
-                                    x_prod_bytes(cplx, n, kmax, B.n_mod));
+  uint8_t* prod = reinterpret_cast<uint8_t*>(xplanes + x_planes_bytes(cplx, n, kmax, B.n_mod));
+  int* tau = reinterpret_cast<int*>(prod + x_prod_bytes(cplx, n, kmax, B.n_mod));
   const double* Xs = static_cast<const double*>(g.B);
-  const bool v4 = n % 4 == 0;
-  const dim3 grid((unsigned)(((v4 ? n / 4 : n) + TPB - 1) / TPB), (unsigned)cols);
+  const dim3 grid((unsigned)((plane_ld(n) / 4 + TPB - 1) / TPB), (unsigned)cols);
   if (cplx) {
     hipLaunchKernelGGL(crt_colexp_k<true>, dim3(cols), dim3(TPB), 0, st, Xs, g.ldb, n, B.pb, tau);
-    if (v4)
-      hipLaunchKernelGGL(crt_xplanes4_k<true>, grid, dim3(TPB), 0, st, Xs, g.ldb, n, cols,
-                         static_cast<const int*>(tau), B, xplanes);
-    else
-      hipLaunchKernelGGL(crt_xplanes_k<true>, grid, dim3(TPB), 0, st, Xs, g.ldb, n, cols,
-                         static_cast<const int*>(tau), B, xplanes);
+    hipLaunchKernelGGL(crt_xplanes_k<true>, grid, dim3(TPB), 0, st, Xs, g.ldb, n, cols,
+                       static_cast<const int*>(tau), B, xplanes);
   } else {
     hipLaunchKernelGGL(crt_colexp_k<false>, dim3(cols), dim3(TPB), 0, st, Xs, g.ldb, n, B.pb, tau);
-    if (v4)
-      hipLaunchKernelGGL(crt_xplanes4_k<false>, grid, dim3(TPB), 0, st, Xs, g.ldb, n, cols,
-                         static_cast<const int*>(tau), B, xplanes);
-    else
-      hipLaunchKernelGGL(crt_xplanes_k<false>, grid, dim3(TPB), 0, st, Xs, g.ldb, n, cols,
-                         static_cast<const int*>(tau), B, xplanes);
+    hipLaunchKernelGGL(crt_xplanes_k<false>, grid, dim3(TPB), 0, st, Xs, g.ldb, n, cols,
+                       static_cast<const int*>(tau), B, xplanes);
   }
   CHASE_HIP(hipGetLastError());
-  // P exact integer products, one per (modulus, Gauss term): H planes are
-  // row-major, i.e. the transposed operand of a column-major GEMM
-  const int32_t one = 1, zero = 0;
-  const rocblas_status rs = rocblas_gemm_strided_batched_ex(
-      rb, rocblas_operation_transpose, rocblas_operation_none, n, cols, n, &one, hplanes,
-      rocblas_datatype_i8_r, n, n * n, xplanes, rocblas_datatype_i8_r, n, n * (int64_t)cols,
-      &zero, prod, rocblas_datatype_i32_r, n, n * (int64_t)cols, prod, rocblas_datatype_i32_r, n,
-      n * (int64_t)cols, P, rocblas_datatype_i32_r, rocblas_gemm_algo_standard, 0, 0);
-  if (rs != rocblas_status_success)
-    throw Error(CHASE_ERR_HIP, std::string("rocblas INT8 GEMM: ") + rocblas_status_to_string(rs));
+  crt_gemm(hplanes, xplanes, n, cols, B, cplx ? 3 : 1, prod, st);
   if (cplx)
     launch_cheb_nm<true>(prod, n, cols, B, sigma, tau, g, st);
   else

@@ -369,7 +369,7 @@ void split_h(chase_handle_s* h, const void* H, int64_t ldh, hipStream_t st) {
 // prepared from the same H, crt_prepare_h).
 void fp64_step(chase_handle_s* h, const GemmArgs& g, hipStream_t st) {
   if (h->crt_h)
-    crt_cheb(h->cplx, g, h->crt, h->crt_h, h->crt_x, h->ne, h->rb, st);
+    crt_cheb(h->cplx, g, h->crt, h->crt_h, h->crt_x, h->ne, st);
   else
     gemm(h->cplx, PREC_F64, OP_N, OP_N, EPI_CHEB, g, st);
 }

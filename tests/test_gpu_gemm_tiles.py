@@ -101,3 +101,23 @@ def test_ritz_and_rank_update_tile_edges(pk, cplx, n, k):
     ref = d0 + (v * gl) @ v.conj().T
     lim = 8 * (k + 2) * 2.0 ** -53 * (np.abs(d0) + (np.abs(v) * np.abs(gl)) @ np.abs(v).T)
     assert np.all(np.abs(to_np(dh) - ref) <= lim)
+
+
+@pytest.mark.parametrize("cplx", [True, False])
+@pytest.mark.parametrize("n,k", [(5, 2), (16, 3), (63, 17), (65, 33), (127, 65), (129, 40),
+                                 (256, 97), (257, 130), (600, 289), (513, 200)])
+def test_int8_products_tile_edges(pk, cplx, n, k):
+    """FP64 products on INT8 at the edges of their tiles (256 rows, 32 to 288
+    columns), of the 128-byte K chunks and of the 16-byte rows: the bar of the
+    FP64 filter (its integer forms of 46 bits or more round less)."""
+    announce(f"tile edges: int8 filter n={n} k={k} cplx={cplx}")
+    g = np.random.Generator(np.random.PCG64(43 * n + k))
+    h, x = _hermitian(g, n, cplx), gen.gaussian(g, (n, k), cplx)
+    deg = np.sort(2 * g.integers(1, 5, size=k)).astype(np.int32)
+    y_ref, _ = oracle.chebyshev_filter(h, x, deg, 1.05, -1.02, -0.5)
+    xt = to_gpu(x)
+    with pk.Handle(n, max(1, k - 1), 1, xt.dtype, pk.default_opts(fp64_emulation=14)) as hd:
+        y, _ = pk.chase_filter(to_gpu(h), xt, deg, 1.05, -1.02, -0.5, handle=hd)
+    y = to_np(y)
+    err = np.max(np.abs(y - y_ref), axis=0) / np.max(np.abs(y_ref), axis=0)
+    assert err.max() < 1e-12, (int(err.argmax()), float(err.max()))
