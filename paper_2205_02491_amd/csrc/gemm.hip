@@ -557,9 +557,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK, OCC) void gemm_kernel(GemmArgs g
 }
 
 template <typename TA, typename TC, bool CPLX, int OPA, int OPB, int EPI, bool G3, int FM, int FN,
-          int WK = 8, int OCC = 1, int WM = 1>
+          int WK = 8, int OCC = 1, int WM = 1, int WN = 1>
 void launch(const GemmArgs& g, hipStream_t st) {
-  constexpr int TBM = WM * FM * 16, TBN = FN * 16;
+  constexpr int TBM = WM * FM * 16, TBN = WN * FN * 16;
   const int64_t tiles_m = (g.M + TBM - 1) / TBM;
   const int64_t tiles_n = (g.N + TBN - 1) / TBN;
   int64_t ntiles = tiles_m * tiles_n;
@@ -570,8 +570,8 @@ void launch(const GemmArgs& g, hipStream_t st) {
   CHASE_REQUIRE(ntiles <= INT32_MAX - 8, "too many output tiles");
   const int grid_x = (int)((ntiles + 7) / 8 * 8);
   dim3 grid(grid_x, 1, EPI == EPI_SPLITK ? g.splits : 1);
-  hipLaunchKernelGGL((gemm_kernel<TA, TC, CPLX, OPA, OPB, EPI, G3, FM, FN, WM, 1, WK, 2, OCC>), grid,
-                     dim3(64 * WM * WK), 0, st, g, (int)tiles_n, (int)ntiles);
+  hipLaunchKernelGGL((gemm_kernel<TA, TC, CPLX, OPA, OPB, EPI, G3, FM, FN, WM, WN, WK, 2, OCC>),
+                     grid, dim3(64 * WM * WN * WK), 0, st, g, (int)tiles_n, (int)ntiles);
   CHASE_HIP(hipGetLastError());
 }
 
@@ -685,13 +685,25 @@ void real_f64(const GemmArgs& g, hipStream_t st) {
   }
 }
 
-// FP32 products of the filter step (A stored as TA, B in FP64).
+// FP32 products of the filter step (A stored as TA, B in FP64).  Rates:
+// TFLOP/s (algorithmic) on the complex 20000 x 1300 step; 8000 x 260 takes 1.03
+// ms with 96 x 48 tiles, 1.08 with 64 x 32, 1.70 with 128 x 64.
 template <typename TA, bool CPLX>
 void cheb_f32(const GemmArgs& g, hipStream_t st) {
-  static constexpr Tile t[] = {{64, 32, 100}, {32, 32, 80}, {16, 16, 40}};
-  switch (g.M < 2 ? 2 : pick(t, g.M, g.N)) {
-    case 0: return launch<TA, float, CPLX, OP_N, OP_N, EPI_CHEB, true, 4, 2>(g, st);
-    case 1: return launch<TA, float, CPLX, OP_N, OP_N, EPI_CHEB, true, 2, 2>(g, st);
+  // pairs of rows are loaded together (real data): at least two of them
+  if (g.M < 2) return launch<TA, float, CPLX, OP_N, OP_N, EPI_CHEB, true, 1, 1>(g, st);
+  static constexpr Tile t[] = {{128, 64, 150}, {64, 32, 146}, {32, 32, 96}, {32, 16, 81},
+                               {16, 16, 47}, {96, 48, 146}};
+  switch (pick(t, g.M, g.N)) {
+    case 0: return launch<TA, float, CPLX, OP_N, OP_N, EPI_CHEB, true, 4, 2, 2, 1, 2, 2>(g, st);
+    case 5:
+      // an odd number of row fragments: complex data only (no row pairs)
+      if constexpr (CPLX)
+        return launch<TA, float, CPLX, OP_N, OP_N, EPI_CHEB, true, 3, 3, 4, 1, 2>(g, st);
+      [[fallthrough]];
+    case 1: return launch<TA, float, CPLX, OP_N, OP_N, EPI_CHEB, true, 4, 2, 4, 2>(g, st);
+    case 2: return launch<TA, float, CPLX, OP_N, OP_N, EPI_CHEB, true, 2, 2>(g, st);
+    case 3: return launch<TA, float, CPLX, OP_N, OP_N, EPI_CHEB, true, 2, 1>(g, st);
     default: return launch<TA, float, CPLX, OP_N, OP_N, EPI_CHEB, true, 1, 1>(g, st);
   }
 }
