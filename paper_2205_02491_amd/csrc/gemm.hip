@@ -605,11 +605,15 @@ int pick(const Tile (&t)[N], int64_t M, int64_t N_) {
 // Complex, three-product form.  Rates: TFLOP/s (algorithmic) on the 20000 x
 // 1300 filter step.  The smaller tiles earn their place where a dimension is
 // ragged or the chip is not full: 1000 x 140 takes 22 us with 48 x 16 (189
-// tiles), 28 with 32 x 32 (160) or 32 x 16 (288), 41 with 48 x 32 (105).
+// tiles), 28 with 32 x 32 (160) or 32 x 16 (288), 41 with 48 x 32 (105); 3000 x
+// 96 takes 92 us with 80 x 16 (228), 104 with 48 x 32 (189), 142 with 32 x 32.
+// Splitting K over workgroups as well, the last one to arrive adding up the
+// partial tiles, took 2 to 4 times as long as the best of these: the
+// device-wide fences it needs write back the L2s.
 template <int EPI>
 void gauss_f64(const GemmArgs& g, hipStream_t st) {
-  static constexpr Tile t[] = {{96, 32, 88}, {48, 32, 83}, {32, 32, 79},
-                               {48, 16, 74}, {32, 16, 62}, {16, 16, 42}};
+  static constexpr Tile t[] = {{96, 32, 88}, {48, 32, 83}, {32, 32, 79}, {48, 16, 74},
+                               {32, 16, 62}, {16, 16, 42}, {80, 16, 74}};
   switch (pick(t, g.M, g.N)) {
     case 0: return launch<double, double, true, OP_N, OP_N, EPI, true, 3, 2, 4, 1, 2>(g, st);
     case 1:
@@ -622,6 +626,7 @@ void gauss_f64(const GemmArgs& g, hipStream_t st) {
     case 2: return launch<double, double, true, OP_N, OP_N, EPI, true, 2, 2>(g, st);
     case 3: return launch<double, double, true, OP_N, OP_N, EPI, true, 3, 1>(g, st);
     case 4: return launch<double, double, true, OP_N, OP_N, EPI, true, 2, 1>(g, st);
+    case 6: return launch<double, double, true, OP_N, OP_N, EPI, true, 5, 1>(g, st);
     default: return launch<double, double, true, OP_N, OP_N, EPI, true, 1, 1>(g, st);
   }
 }
@@ -668,7 +673,7 @@ void real_f64(const GemmArgs& g, hipStream_t st) {
   if (g.K <= 192 && waves_of(g) == 2)
     return launch<double, double, false, OPA, OPB, EPI, false, 2, 2, 2, 4>(g, st);
   static constexpr Tile t[] = {{128, 64, 70}, {64, 64, 67}, {64, 32, 62}, {64, 16, 55},
-                               {32, 32, 48},  {32, 16, 41}, {16, 16, 24}};
+                               {32, 32, 48},  {32, 16, 41}, {16, 16, 24}, {96, 32, 64}};
   switch (pick(t, g.M, g.N)) {
     case 0: return launch<double, double, false, OPA, OPB, EPI, false, 4, 4, 2, 2, 2>(g, st);
     case 1:
@@ -681,6 +686,7 @@ void real_f64(const GemmArgs& g, hipStream_t st) {
     case 3: return launch<double, double, false, OPA, OPB, EPI, false, 4, 1>(g, st);
     case 4: return launch<double, double, false, OPA, OPB, EPI, false, 2, 2>(g, st);
     case 5: return launch<double, double, false, OPA, OPB, EPI, false, 2, 1>(g, st);
+    case 7: return launch<double, double, false, OPA, OPB, EPI, false, 6, 2>(g, st);
     default: return launch<double, double, false, OPA, OPB, EPI, false, 1, 1>(g, st);
   }
 }
