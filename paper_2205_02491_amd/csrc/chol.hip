@@ -8,7 +8,7 @@
 //  - chol_panel_k: every workgroup factors the CB x CB diagonal block in
 //    LDS (the same arithmetic in each, so they agree bit for bit), then
 //    solves R11^H X = A12 for its own PC columns of the row panel, staged
-//    through LDS, one column per thread held in registers (forward
+//    through LDS, each column held in the registers of a quad of lanes (forward
 //    substitution).  Workgroup 0 also stores R11.
 //  - chol_update_k: A22 -= R12^H R12 on the upper triangle, in UT x UT
 //    tiles staged through LDS.
@@ -22,6 +22,7 @@
 #include "common.h"
 
 #include <algorithm>
+#include <utility>
 
 namespace chase {
 namespace {
@@ -30,7 +31,8 @@ constexpr int CB = 32;        // panel rows
 constexpr int CLD = CB + 1;   // LDS leading dimension of the diagonal block
 constexpr int CT = 256;       // threads per workgroup
 constexpr int CG = CT / CB;   // column groups of the (row, column-group) thread map
-constexpr int PC = 128;       // row-panel columns per workgroup
+constexpr int PQ = 4;         // threads per row-panel column (one quad of lanes)
+constexpr int PC = CT / PQ;   // row-panel columns per workgroup
 constexpr int PLD = PC + 1;
 constexpr int UT = 32;        // trailing-update tile
 constexpr int ULD = UT + 1;
@@ -67,6 +69,38 @@ __device__ __forceinline__ void mac_conj(cd& acc, cd a, cd b) {
   acc.x = fma(a.y, b.y, acc.x);
   acc.y = fma(a.x, b.y, acc.y);
   acc.y = fma(-a.y, b.x, acc.y);
+}
+
+// Value of lane Q of each quad of lanes.
+template <int Q>
+__device__ __forceinline__ double quad_bcast(double a) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(a), Q * 0x55, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(a), Q * 0x55, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+template <int Q>
+__device__ __forceinline__ cd quad_bcast(cd a) {
+  return {quad_bcast<Q>(a.x), quad_bcast<Q>(a.y)};
+}
+
+// Step L of the row panel's substitution: row L is final after its scaling;
+// the rows below take conj(R11(L, i)) x_L off.
+template <class T, int L>
+__device__ __forceinline__ void solve_row(T (&x)[CB / PQ], const T* D, const double* rdg, int q) {
+  constexpr int M = L / PQ, Q = L % PQ;
+  const T xs = scaled(x[M], rdg[L]);
+  if (q == Q) x[M] = xs;
+  const T xl = quad_bcast<Q>(xs);
+#pragma unroll
+  for (int m = M; m < CB / PQ; ++m) {
+    const int i = m * PQ + q;
+    if (m > M || q > Q) msub_conj(x[m], D[L + i * CLD], xl);
+  }
+}
+template <class T, int... L>
+__device__ __forceinline__ void solve_rows(T (&x)[CB / PQ], const T* D, const double* rdg, int q,
+                                           std::integer_sequence<int, L...>) {
+  (solve_row<T, L>(x, D, rdg, q), ...);
 }
 
 // Panel j0: factor the diagonal block and solve the row panel.  Grid:
@@ -143,19 +177,25 @@ __global__ __launch_bounds__(CT) void chol_panel_k(T* __restrict__ A, int64_t ld
     for (int c = tg; c < nb; c += CG)
       if (ti <= c) A[(int64_t)(j0 + ti) + (int64_t)(j0 + c) * lda] = D[ti + c * CLD];
   // Row panel: column c of A12 becomes R11^{-H} a_c (forward substitution,
-  // column-oriented, in registers).
-  if (tid < pc) {
-    T x[CB];
+  // column-oriented, in registers).  Lane q of a column's quad holds its rows q,
+  // q + 4, ...; the finished row goes to the other three by a quad broadcast.
+  // One thread per column spent 11 us on the 496 multiply-adds and factor reads
+  // of a column, the longest phase of the launch; a quad 3 us.
+  {
+    const int c = tid / PQ, q = tid % PQ;
+    T x[CB / PQ];
+    if (c < pc) {
 #pragma unroll
-    for (int i = 0; i < CB; ++i) x[i] = P[i * PLD + tid];
+      for (int m = 0; m < CB / PQ; ++m) x[m] = P[(m * PQ + q) * PLD + c];
+    } else {
 #pragma unroll
-    for (int l = 0; l < CB; ++l) {
-      x[l] = scaled(x[l], rdg[l]);
-#pragma unroll
-      for (int i = l + 1; i < CB; ++i) msub_conj(x[i], D[l + i * CLD], x[l]);
+      for (int m = 0; m < CB / PQ; ++m) x[m] = from_real<T>(0.0);
     }
+    solve_rows<T>(x, D, rdg, q, std::make_integer_sequence<int, CB>{});
+    if (c < pc) {
 #pragma unroll
-    for (int i = 0; i < CB; ++i) P[i * PLD + tid] = x[i];
+      for (int m = 0; m < CB / PQ; ++m) P[(m * PQ + q) * PLD + c] = x[m];
+    }
   }
   __syncthreads();
   for (int c = tg; c < pc; c += CG) A[(int64_t)(j0 + ti) + (c0 + c) * lda] = P[ti * PLD + c];
