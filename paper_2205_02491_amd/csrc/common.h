@@ -169,6 +169,12 @@ void diag_real(bool cplx, const void* A, int64_t lda, int64_t k, double* out,
 // res[j] = sqrt(sum_t partial[t][j]) * inv_scale
 void resid_finish(const double* partial, int tiles, int64_t N, double inv_scale, double* res,
                   hipStream_t st);
+// a[i a_stride] and b[i] (i < k; either may be null) to pinned[0, k) and
+// pinned[k, 2 k), and the two int words (or 0) behind them: host memory the
+// GPU writes, valid after the stream was synchronised.  A copy of a few bytes
+// to pageable memory costs 20 to 50 us each.
+void report(const double* a, int64_t a_stride, const double* b, int k, const int* word0,
+            const int* word1, double* pinned, hipStream_t st);
 // V = V * diag(g) (columns scaled by real g)
 void scale_cols(bool cplx, void* V, int64_t ldv, int64_t n, int64_t k, const double* g,
                 hipStream_t st);
@@ -250,18 +256,19 @@ void cholesky_upper(bool cplx, void* A, int64_t lda, int k, int* d_info, hipStre
 // ------------------------------------------------------------------ Jacobi eigensolver
 // Device workspace of the block Jacobi eigensolver for orders up to kmax.
 size_t jacobi_ws_bytes(bool cplx, int kmax);
+// Doubles of pinned host memory the norms need.
+constexpr int kJacobiPinned = 512;
 // Squared Frobenius norms of a k x k matrix: off2 off the diagonal, dia2 on it
-// (synchronises the stream).
-void jacobi_norms(bool cplx, const void* G, int64_t ldg, int k, void* ws, int kmax, double* off2,
+// (through `pinned`; synchronises the stream).
+void jacobi_norms(bool cplx, const void* G, int64_t ldg, int k, double* pinned, double* off2,
                   double* dia2, hipStream_t st);
 // Eigen-decomposition of the Hermitian k x k G (destroyed) by block-cyclic
 // Jacobi until off2 <= tol^2 (off2 + dia2) (the norms of G on entry, from
 // jacobi_norms); V (k x k) is scratch, W (may be G) receives the
-// eigenvectors and d_evals / evals_host the eigenvalues, ascending; d_perm
-// holds k ints.  Returns the sweeps; throws CHASE_ERR_NUMERIC after
-// max_sweeps.
+// eigenvectors and d_evals the eigenvalues, ascending; d_perm holds k ints.
+// Returns the sweeps; throws CHASE_ERR_NUMERIC after max_sweeps.
 int jacobi_heev(bool cplx, void* G, int64_t ldg, int k, void* V, int64_t ldv, void* W,
-                int64_t ldw, double* d_evals, int* d_perm, void* ws, int kmax, double* evals_host,
+                int64_t ldw, double* d_evals, int* d_perm, void* ws, int kmax, double* pinned,
                 hipStream_t st, double off2, double dia2, double tol, int max_sweeps);
 
 // ------------------------------------------------------------------ Lanczos

@@ -15,8 +15,6 @@
 
 #include <algorithm>
 #include <cmath>
-#include <numeric>
-#include <vector>
 
 namespace chase {
 namespace {
@@ -454,6 +452,29 @@ __global__ __launch_bounds__(JT) void jac_norms_k(const T* __restrict__ G, int64
   }
 }
 
+// Sort of the k values w: thread j counts those that come before w[j] (ties
+// and NaN, taken as the largest, in index order), which is its place.
+__global__ __launch_bounds__(JT) void jac_sort_k(const double* __restrict__ w, int k,
+                                                 double* __restrict__ sorted,
+                                                 int* __restrict__ perm) {
+  __shared__ double tile[JT];
+  const int j = blockIdx.x * JT + threadIdx.x;
+  auto key = [](double x) { return x == x ? x : INFINITY; };
+  const double wj = j < k ? w[j] : 0.0, kj = key(wj);
+  int rank = 0;
+  for (int i0 = 0; i0 < k; i0 += JT) {
+    __syncthreads();
+    if (i0 + (int)threadIdx.x < k) tile[threadIdx.x] = key(w[i0 + threadIdx.x]);
+    __syncthreads();
+    const int m = min(JT, k - i0);
+    for (int i = 0; i < m; ++i) rank += tile[i] < kj || (tile[i] == kj && i0 + i < j);
+  }
+  if (j < k) {
+    sorted[rank] = wj;
+    perm[rank] = j;
+  }
+}
+
 template <class T>
 __global__ void jac_eye_k(T* __restrict__ V, int64_t ldv, int k) {
   const int64_t total = (int64_t)k * k;
@@ -491,33 +512,30 @@ struct JacLayout {
 
 template <class T>
 struct JacobiRunner {
-  static void norms(const void* G, int64_t ldg, int k, double* d_part, double* off2,
+  // the partial sums go straight to host memory
+  static void norms(const void* G, int64_t ldg, int k, double* pinned, double* off2,
                     double* dia2, hipStream_t st) {
-    std::vector<double> h(2 * NPART, 0.0);
     hipLaunchKernelGGL(jac_norms_k<T>, dim3(NPART), dim3(JT), 0, st, static_cast<const T*>(G),
-                       ldg, k, d_part);
+                       ldg, k, pinned);
     CHASE_HIP(hipGetLastError());
-    CHASE_HIP(hipMemcpyAsync(h.data(), d_part, h.size() * sizeof(double), hipMemcpyDeviceToHost,
-                             st));
     CHASE_HIP(hipStreamSynchronize(st));
     double o = 0.0, d = 0.0;
     for (int w = 0; w < NPART; ++w) {
-      o += h[2 * w];
-      d += h[2 * w + 1];
+      o += pinned[2 * w];
+      d += pinned[2 * w + 1];
     }
     *off2 = o;
     *dia2 = d;
   }
 
   static int run(void* G, int64_t ldg, int k, void* V, int64_t ldv, void* ws,
-                 const JacLayout& lay, double tol, int max_sweeps, double off2, double dia2,
-                 hipStream_t st) {
+                 const JacLayout& lay, double* pinned, double tol, int max_sweeps, double off2,
+                 double dia2, hipStream_t st) {
     const int nb = jac_blocks(k), P = nb / 2;
     char* base = static_cast<char*>(ws);
     T* ubuf[2] = {reinterpret_cast<T*>(base + lay.ubuf[0]), reinterpret_cast<T*>(base + lay.ubuf[1])};
     int* flags[2] = {reinterpret_cast<int*>(base + lay.flags[0]),
                      reinterpret_cast<int*>(base + lay.flags[1])};
-    double* d_part = reinterpret_cast<double*>(base + lay.part);
     const int tiles_g = P * (P + 1) / 2;
     const int tiles_v = ((k + JM - 1) / JM) * P;
     T* Gt = static_cast<T*>(G);
@@ -550,7 +568,7 @@ struct JacobiRunner {
       CHASE_HIP(hipGetLastError());
       ++sweeps;
       double d2;
-      norms(G, ldg, k, d_part, &off2, &d2, st);
+      norms(G, ldg, k, pinned, &off2, &d2, st);
       if (!std::isfinite(off2)) throw Error(CHASE_ERR_NUMERIC, "non-finite entries in Jacobi");
     }
     return sweeps;
@@ -561,18 +579,18 @@ struct JacobiRunner {
 
 size_t jacobi_ws_bytes(bool cplx, int kmax) { return JacLayout(cplx, kmax).total; }
 
-void jacobi_norms(bool cplx, const void* G, int64_t ldg, int k, void* ws, int kmax,
-                  double* off2, double* dia2, hipStream_t st) {
-  CHASE_REQUIRE(k >= 1 && k <= kmax, "Jacobi eigensolver: order out of range");
-  double* d_part = reinterpret_cast<double*>(static_cast<char*>(ws) + JacLayout(cplx, kmax).part);
+void jacobi_norms(bool cplx, const void* G, int64_t ldg, int k, double* pinned, double* off2,
+                  double* dia2, hipStream_t st) {
+  CHASE_REQUIRE(k >= 1, "Jacobi eigensolver: order out of range");
+  static_assert(kJacobiPinned >= 2 * NPART, "pinned partial sums");
   if (cplx)
-    JacobiRunner<cd>::norms(G, ldg, k, d_part, off2, dia2, st);
+    JacobiRunner<cd>::norms(G, ldg, k, pinned, off2, dia2, st);
   else
-    JacobiRunner<double>::norms(G, ldg, k, d_part, off2, dia2, st);
+    JacobiRunner<double>::norms(G, ldg, k, pinned, off2, dia2, st);
 }
 
 int jacobi_heev(bool cplx, void* G, int64_t ldg, int k, void* V, int64_t ldv, void* W,
-                int64_t ldw, double* d_evals, int* d_perm, void* ws, int kmax, double* evals_host,
+                int64_t ldw, double* d_evals, int* d_perm, void* ws, int kmax, double* pinned,
                 hipStream_t st, double off2, double dia2, double tol, int max_sweeps) {
   CHASE_REQUIRE(k >= 1 && k <= kmax, "Jacobi eigensolver: order out of range");
   CHASE_REQUIRE(ldg >= k && ldv >= k && ldw >= k, "Jacobi eigensolver: leading dimension < k");
@@ -582,25 +600,18 @@ int jacobi_heev(bool cplx, void* G, int64_t ldg, int k, void* V, int64_t ldv, vo
   const JacLayout lay(cplx, kmax);
   int sweeps;
   if (cplx)
-    sweeps = JacobiRunner<cd>::run(G, ldg, k, V, ldv, ws, lay, tol, max_sweeps, off2, dia2, st);
+    sweeps = JacobiRunner<cd>::run(G, ldg, k, V, ldv, ws, lay, pinned, tol, max_sweeps, off2, dia2,
+                                   st);
   else
-    sweeps = JacobiRunner<double>::run(G, ldg, k, V, ldv, ws, lay, tol, max_sweeps, off2, dia2, st);
+    sweeps = JacobiRunner<double>::run(G, ldg, k, V, ldv, ws, lay, pinned, tol, max_sweeps, off2,
+                                       dia2, st);
   // eigenvalues: the diagonal, ascending (stable), eigenvectors gathered to match
   double* d_diag = reinterpret_cast<double*>(static_cast<char*>(ws) + lay.diag);
   diag_real(cplx, G, ldg, k, d_diag, st);
-  std::vector<double> w(k);
-  CHASE_HIP(hipMemcpyAsync(w.data(), d_diag, (size_t)k * 8, hipMemcpyDeviceToHost, st));
-  CHASE_HIP(hipStreamSynchronize(st));
-  std::vector<int> perm(k);
-  std::iota(perm.begin(), perm.end(), 0);
-  std::stable_sort(perm.begin(), perm.end(), [&](int x, int y) { return w[x] < w[y]; });
-  for (int j = 0; j < k; ++j) evals_host[j] = w[perm[j]];
-  CHASE_HIP(hipMemcpyAsync(d_perm, perm.data(), (size_t)k * sizeof(int), hipMemcpyHostToDevice,
-                           st));
-  CHASE_HIP(hipMemcpyAsync(d_evals, evals_host, (size_t)k * 8, hipMemcpyHostToDevice, st));
+  hipLaunchKernelGGL(jac_sort_k, dim3((unsigned)((k + JT - 1) / JT)), dim3(JT), 0, st, d_diag, k,
+                     d_evals, d_perm);
+  CHASE_HIP(hipGetLastError());
   gather_cols(cplx, V, ldv, W, ldw, k, k, d_perm, st);
-  // the host arrays above must outlive the copies
-  CHASE_HIP(hipStreamSynchronize(st));
   return sweeps;
 }
 

@@ -152,16 +152,6 @@ __global__ void diag_real_k(const double* __restrict__ A, int64_t lda, int64_t k
     out[j] = A[(j + j * lda) * W];
 }
 
-__global__ void resid_finish_k(const double* __restrict__ partial, int tiles, int64_t N,
-                               double inv_scale, double* __restrict__ res) {
-  for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < N;
-       j += (int64_t)gridDim.x * blockDim.x) {
-    double s = 0;
-    for (int t = 0; t < tiles; ++t) s += partial[(int64_t)t * N + j];
-    res[j] = sqrt(s) * inv_scale;
-  }
-}
-
 template <bool CPLX>
 __global__ void scale_cols_k(double* __restrict__ V, int64_t ldv, int64_t n, int64_t k,
                              const double* __restrict__ g) {
@@ -476,6 +466,34 @@ __device__ inline double lz_total(const double* p, int nblk) {
   return block_sum1((int)threadIdx.x < nblk ? p[threadIdx.x] : 0.0);
 }
 
+// Column j's norm from its partial sums, one workgroup per column (a thread
+// per column added up the 250 row tiles of n=8000 one after the other: 62 us).
+__global__ __launch_bounds__(TPB) void resid_finish_k(const double* __restrict__ partial,
+                                                      int tiles, int64_t N, double inv_scale,
+                                                      double* __restrict__ res) {
+  const int64_t j = blockIdx.x;
+  double s = 0;
+  for (int t = threadIdx.x; t < tiles; t += TPB) s += partial[(int64_t)t * N + j];
+  s = block_sum1(s);
+  if (threadIdx.x == 0) res[j] = sqrt(s) * inv_scale;
+}
+
+// What the host needs of a step, written by the GPU into the handle's pinned
+// buffer: a[i a_stride] and b[i] (i < k), then the two int words.
+__global__ void report_k(const double* a, int64_t a_stride, const double* b, int k,
+                         const int* word0, const int* word1, double* out) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < k) {
+    if (a) out[i] = a[i * a_stride];
+    if (b) out[k + i] = b[i];
+  }
+  if (i == 0) {
+    int* w = reinterpret_cast<int*>(out + 2 * (int64_t)k);
+    w[0] = word0 ? *word0 : 0;
+    w[1] = word1 ? *word1 : 0;
+  }
+}
+
 // The vector kernels of a Lanczos step run one workgroup per 256 rows and
 // vector (blockIdx.y), and sum the partial sums of the kernel before with one
 // thread each: with the four vectors and the partial sums in loops inside the
@@ -775,8 +793,16 @@ void diag_real(bool cplx, const void* A, int64_t lda, int64_t k, double* out, hi
 
 void resid_finish(const double* partial, int tiles, int64_t N, double inv_scale, double* res,
                   hipStream_t st) {
-  hipLaunchKernelGGL(resid_finish_k, dim3(blocks_for(N, TPB, 1024)), dim3(TPB), 0, st, partial,
-                     tiles, N, inv_scale, res);
+  if (N <= 0) return;
+  hipLaunchKernelGGL(resid_finish_k, dim3((unsigned)N), dim3(TPB), 0, st, partial, tiles, N,
+                     inv_scale, res);
+  CHASE_HIP(hipGetLastError());
+}
+
+void report(const double* a, int64_t a_stride, const double* b, int k, const int* word0,
+            const int* word1, double* pinned, hipStream_t st) {
+  hipLaunchKernelGGL(report_k, dim3((unsigned)((k + TPB - 1) / TPB)), dim3(TPB), 0, st, a,
+                     a_stride, b, k, word0, word1, pinned);
   CHASE_HIP(hipGetLastError());
 }
 

@@ -73,6 +73,7 @@ struct chase_handle_s {
   std::vector<hipEvent_t> evs;
   hipEvent_t eig_ev[2] = {nullptr, nullptr};  // around the small eigensolve
   std::vector<void*> allocs;
+  double* pin = nullptr;  // pinned host memory the GPU reports small results to
 };
 
 // Work buffers of chase_lanczos_noalloc: a fixed device array (one copy per
@@ -627,14 +628,11 @@ void qr_step(chase_handle_s* h, void* X, int64_t ldx, int k, int L, void* Wb, ch
     householder_qr(h, X, ldx, k, L, Wb, stats, st);
   };
   auto sync_info = [&](bool want_diag) {
-    CHASE_HIP(hipMemcpyAsync(&hinfo[0], h->d_info, sizeof(int), hipMemcpyDeviceToHost, st));
-    CHASE_HIP(hipMemcpyAsync(&hinfo[1], h->d_flags, sizeof(int), hipMemcpyDeviceToHost, st));
-    if (want_diag) {
-      diag_real(cplx, R, ldr, k, h->d_res, st);
-      CHASE_HIP(hipMemcpyAsync(diag.data(), h->d_res, k * sizeof(double),
-                               hipMemcpyDeviceToHost, st));
-    }
+    report(want_diag ? static_cast<const double*>(R) : nullptr, (ldr + 1) * (cplx ? 2 : 1), nullptr,
+           k, h->d_info, h->d_flags, h->pin, st);
     CHASE_HIP(hipStreamSynchronize(st));
+    if (want_diag) std::copy(h->pin, h->pin + k, diag.begin());
+    std::memcpy(hinfo, h->pin + 2 * (size_t)k, sizeof(hinfo));
   };
   while (clean < 2) {
     gram(h, cur, ldc, cur, ldc, n, k, k, R, ldr, true, st);
@@ -694,7 +692,7 @@ constexpr int kJacobiMaxSweeps = 60;
 int small_eig(chase_handle_s* h, int k, int method, hipStream_t st) {
   double off2 = 0.0, dia2 = 0.0;
   if (method != CHASE_EIG_LIBRARY) {
-    jacobi_norms(h->cplx, h->G, k, k, h->jac_ws, h->ne, &off2, &dia2, st);
+    jacobi_norms(h->cplx, h->G, k, k, h->pin, &off2, &dia2, st);
     if (method == CHASE_EIG_AUTO)
       method = off2 <= kAutoJacobiOff * kAutoJacobiOff * (off2 + dia2) ? CHASE_EIG_JACOBI
                                                                         : CHASE_EIG_LIBRARY;
@@ -702,9 +700,8 @@ int small_eig(chase_handle_s* h, int k, int method, hipStream_t st) {
   if (method == CHASE_EIG_JACOBI) {
     // callers check the library solver's info word: Jacobi reports by throwing
     fill_zero(h->d_info, sizeof(int), st);
-    std::vector<double> ev(k);
     return jacobi_heev(h->cplx, h->G, k, k, h->R, k, h->G, k, h->d_evals, h->d_perm, h->jac_ws,
-                       h->ne, ev.data(), st, off2, dia2, kJacobiTol, kJacobiMaxSweeps);
+                       h->ne, h->pin, st, off2, dia2, kJacobiTol, kJacobiMaxSweeps);
   }
   if (h->cplx)
     rb_check(rocsolver_zheevd(h->rb, rocblas_evect_original, rocblas_fill_upper, k,
@@ -718,8 +715,10 @@ int small_eig(chase_handle_s* h, int k, int method, hipStream_t st) {
   return -1;
 }
 
-// Q (n x k, ld ldq) orthonormal -> Ritz vectors; ritz/res on the device
-// (h->d_evals, h->d_res).  Scratch: P (n x k, ld n), Zb (n x k, ld n).
+// Q (n x k, ld ldq) orthonormal -> Ritz vectors; Ritz values and residuals on
+// the device (h->d_evals, h->d_res) and, with the eigensolver's info word, in
+// h->pin (see report).  Scratch: P (n x k, ld n), Zb (n x k, ld n).  Returns
+// with the stream synchronised.
 void rr_step(chase_handle_s* h, const void* H, int64_t ldh, void* Q, int64_t ldq, int k,
              double norm_scale, void* P, void* Zb, double* t_rr, double* t_resid,
              hipStream_t st, void* Rout = nullptr, int64_t ldr = 0, double* t_eig = nullptr,
@@ -751,8 +750,10 @@ void rr_step(chase_handle_s* h, const void* H, int64_t ldh, void* Q, int64_t ldq
   if (t_eig) CHASE_HIP(hipEventRecord(h->eig_ev[1], st));
   // Ritz vectors Z = Q W
   gemm_nn(h, n, k, k, Q, ldq, h->G, k, Zb, n, st);
-  CHASE_HIP(hipStreamSynchronize(st));
-  auto t1 = clk::now();
+  if (t_resid) {
+    ensure_events(h, 2);
+    CHASE_HIP(hipEventRecord(h->evs[0], st));
+  }
   // residual: (P W) - Z diag(theta), column norms, without a second HEMM
   GemmArgs g = gargs(n, k, k, P, n, h->G, k, nullptr, 0);
   g.lambda = h->d_evals;
@@ -764,10 +765,18 @@ void rr_step(chase_handle_s* h, const void* H, int64_t ldh, void* Q, int64_t ldq
   gemm(cplx, PREC_F64, OP_N, OP_N, EPI_RESID, g, st);
   resid_finish(h->d_partial, gemm_row_tiles(n), k, 1.0 / norm_scale, h->d_res, st);
   copy_cols(cplx, Zb, n, Q, ldq, n, k, st);
+  report(h->d_evals, 1, h->d_res, k, h->d_info, nullptr, h->pin, st);
+  if (t_resid) CHASE_HIP(hipEventRecord(h->evs[1], st));
   CHASE_HIP(hipStreamSynchronize(st));
   auto t2 = clk::now();
-  if (t_rr) *t_rr += secs(t0, t1);
-  if (t_resid) *t_resid += secs(t1, t2);
+  double resid_s = 0.0;
+  if (t_resid) {
+    float ms = 0.f;
+    CHASE_HIP(hipEventElapsedTime(&ms, h->evs[0], h->evs[1]));
+    resid_s = ms * 1e-3;
+    *t_resid += resid_s;
+  }
+  if (t_rr) *t_rr += secs(t0, t2) - resid_s;
   if (t_eig) {
     float ms = 0.f;
     CHASE_HIP(hipEventElapsedTime(&ms, h->eig_ev[0], h->eig_ev[1]));
@@ -775,10 +784,10 @@ void rr_step(chase_handle_s* h, const void* H, int64_t ldh, void* Q, int64_t ldq
   }
 }
 
-void check_info(chase_handle_s* h, hipStream_t st, const char* what) {
+// info: the eigensolver's info word (first word behind 2 k reported doubles)
+void check_info(const chase_handle_s* h, int k, const char* what) {
   int info = 0;
-  CHASE_HIP(hipMemcpyAsync(&info, h->d_info, sizeof(int), hipMemcpyDeviceToHost, st));
-  CHASE_HIP(hipStreamSynchronize(st));
+  std::memcpy(&info, h->pin + 2 * (size_t)k, sizeof(info));
   if (info != 0)
     throw Error(CHASE_ERR_NUMERIC, std::string(what) + " did not converge (info=" +
                                        std::to_string(info) + ")");
@@ -972,12 +981,9 @@ void solve_impl(chase_handle_s* h, const void* H, int64_t ldh, double tol, int d
   // switches, locking of the converged prefix, and unless done the bounds,
   // degrees and sort for the next filter.  Returns true when the solve stops.
   auto after_rr = [&](int it, int ka, int n64) -> bool {
-    check_info(h, st, "Hermitian eigensolver");
-    CHASE_HIP(hipMemcpyAsync(&lam[L], h->d_evals, ka * sizeof(double), hipMemcpyDeviceToHost, st));
-    std::vector<double> r_new(ka);
-    CHASE_HIP(hipMemcpyAsync(r_new.data(), h->d_res, ka * sizeof(double), hipMemcpyDeviceToHost,
-                             st));
-    CHASE_HIP(hipStreamSynchronize(st));
+    check_info(h, ka, "Hermitian eigensolver");
+    std::copy(h->pin, h->pin + ka, lam.begin() + L);
+    const std::vector<double> r_new(h->pin + ka, h->pin + 2 * ka);
     for (int a = 0; a < ka; ++a) {
       if (!std::isfinite(r_new[a]) || !std::isfinite(lam[L + a]))
         throw Error(CHASE_ERR_NUMERIC, "non-finite Ritz value or residual");
@@ -1350,6 +1356,15 @@ chase_status chase_create(chase_handle_t* out, chase_dtype dtype, int64_t n, int
       h->adj = dev_alloc(h, 2 * (size_t)n * ne * h->esz);
       ensure_tape(h, (int)ne, o.adjoint_reserve);
     }
+    {
+      const size_t doubles = std::max<size_t>(kJacobiPinned, 2 * (size_t)ne + 8);
+      void* p = nullptr;
+      if (hipHostMalloc(&p, doubles * 8, hipHostMallocCoherent) != hipSuccess) {
+        (void)hipGetLastError();
+        throw Error(CHASE_ERR_NOMEM, "pinned host allocation failed");
+      }
+      h->pin = static_cast<double*>(p);
+    }
     rb_check(rocblas_create_handle(&h->rb), "rocblas_create_handle");
     CHASE_HIP(hipEventCreate(&h->eig_ev[0]));
     CHASE_HIP(hipEventCreate(&h->eig_ev[1]));
@@ -1371,6 +1386,7 @@ void chase_destroy(chase_handle_t h) {
   for (hipEvent_t e : h->eig_ev)
     if (e) (void)hipEventDestroy(e);
   if (h->rb) rocblas_destroy_handle(h->rb);
+  if (h->pin) (void)hipHostFree(h->pin);
   delete h;
 }
 
@@ -1563,10 +1579,9 @@ chase_status chase_rayleigh_ritz(chase_handle_t h, const void* H, int64_t ldh, v
     set_stream(h, st);
     prepare_h_products(h, H, ldh, st);
     rr_step(h, H, ldh, Q, ldq, k, norm_scale, h->W, h->Z, nullptr, nullptr, st);
-    check_info(h, st, "Hermitian eigensolver");
-    CHASE_HIP(hipMemcpyAsync(ritz, h->d_evals, k * 8, hipMemcpyDeviceToHost, st));
-    if (resid) CHASE_HIP(hipMemcpyAsync(resid, h->d_res, k * 8, hipMemcpyDeviceToHost, st));
-    CHASE_HIP(hipStreamSynchronize(st));
+    check_info(h, k, "Hermitian eigensolver");
+    std::copy(h->pin, h->pin + k, ritz);
+    if (resid) std::copy(h->pin + k, h->pin + 2 * (size_t)k, resid);
   });
 }
 
@@ -1584,10 +1599,12 @@ chase_status chase_heev(chase_handle_t h, void* G, int64_t ldg, int k, int metho
     set_stream(h, st);
     copy_cols(h->cplx, G, ldg, h->G, k, k, k, st);
     const int sw = small_eig(h, k, method, st);
-    if (sw < 0) check_info(h, st, "Hermitian eigensolver");
-    copy_cols(h->cplx, h->G, k, G, ldg, k, k, st);
-    CHASE_HIP(hipMemcpyAsync(evals, h->d_evals, k * 8, hipMemcpyDeviceToHost, st));
+    report(h->d_evals, 1, nullptr, k, h->d_info, nullptr, h->pin, st);
     CHASE_HIP(hipStreamSynchronize(st));
+    check_info(h, k, "Hermitian eigensolver");
+    copy_cols(h->cplx, h->G, k, G, ldg, k, k, st);
+    CHASE_HIP(hipStreamSynchronize(st));
+    std::copy(h->pin, h->pin + k, evals);
     if (sweeps) *sweeps = sw < 0 ? 0 : sw;
   });
 }
