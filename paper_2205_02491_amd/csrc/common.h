@@ -253,6 +253,11 @@ void crt_cheb(bool cplx, const GemmArgs& g, const CrtBasis& B, const void* hbuf,
 // first pivot that is not positive (then A holds partial results).
 void cholesky_upper(bool cplx, void* A, int64_t lda, int k, int* d_info, hipStream_t st);
 
+// M = diag(d) R^{-1} (k x k, zeros below the diagonal) for the upper
+// triangular R, if k <= 512: returns false, with nothing done, above.
+bool chol_inverse(bool cplx, const void* R, int64_t ldr, int k, const double* d, void* M,
+                  int64_t ldm, hipStream_t st);
+
 // ------------------------------------------------------------------ Jacobi eigensolver
 // Device workspace of the block Jacobi eigensolver for orders up to kmax.
 size_t jacobi_ws_bytes(bool cplx, int kmax);

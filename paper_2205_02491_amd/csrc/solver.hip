@@ -660,18 +660,24 @@ void qr_step(chase_handle_s* h, void* X, int64_t ldx, int k, int L, void* Wb, ch
     } else {
       ++clean;
     }
-    if (cplx)
-      rb_check(rocsolver_ztrtri(h->rb, rocblas_fill_upper, rocblas_diagonal_non_unit, k,
-                                static_cast<rocblas_double_complex*>(R), ldr, h->d_info),
-               "ztrtri");
-    else
-      rb_check(rocsolver_dtrtri(h->rb, rocblas_fill_upper, rocblas_diagonal_non_unit, k,
-                                static_cast<double*>(R), ldr, h->d_info),
-               "dtrtri");
-    triu_rowscale(cplx, R, ldr, k, h->d_scale, st);
+    // factor of the block: D R^{-1}, in the Gram matrix's place for the orders
+    // the one-launch inverse takes, else in R's
+    const void* F = h->G;
+    if (!chol_inverse(cplx, R, ldr, k, h->d_scale, h->G, ldr, st)) {
+      F = R;
+      if (cplx)
+        rb_check(rocsolver_ztrtri(h->rb, rocblas_fill_upper, rocblas_diagonal_non_unit, k,
+                                  static_cast<rocblas_double_complex*>(R), ldr, h->d_info),
+                 "ztrtri");
+      else
+        rb_check(rocsolver_dtrtri(h->rb, rocblas_fill_upper, rocblas_diagonal_non_unit, k,
+                                  static_cast<double*>(R), ldr, h->d_info),
+                 "dtrtri");
+      triu_rowscale(cplx, R, ldr, k, h->d_scale, st);
+    }
     // next = block * (D R^{-1}); the locked columns keep their values.  Column
     // j of the factor's block [L, k) is zero below row L + j.
-    gemm_nn(h, n, k - L, k, cur, ldc, off(R, (int64_t)L * ldr, h->esz), ldr,
+    gemm_nn(h, n, k - L, k, cur, ldc, off(const_cast<void*>(F), (int64_t)L * ldr, h->esz), ldr,
             off(nxt, (int64_t)L * ldn, h->esz), ldn, st, L);
     std::swap(cur, nxt);
     std::swap(ldc, ldn);
