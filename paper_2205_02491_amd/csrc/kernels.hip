@@ -446,15 +446,16 @@ __global__ __launch_bounds__(TPB) void lz_gemv_k(const double* __restrict__ H, i
 
 // Block-wide sum of one value per thread (fixed order: deterministic), the
 // same in every thread.
+template <int NT = TPB>
 __device__ inline double block_sum1(double x) {
-  __shared__ double red1[TPB / 64];
+  __shared__ double red1[NT / 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
   __syncthreads();
   if (lane == 0) red1[wave] = x;
   __syncthreads();
   double s = 0;
-  for (int w = 0; w < TPB / 64; ++w) s += red1[w];
+  for (int w = 0; w < NT / 64; ++w) s += red1[w];
   return s;
 }
 
@@ -597,56 +598,44 @@ __global__ __launch_bounds__(TPB) void col_dots_k(const double* __restrict__ X, 
 // A column is live while rr > tol2 rr0 and pq > 0.  Iterating a converged
 // column on rounding-level residuals makes p^H A p noise and alpha blow up,
 // so converged (or broken-down) columns are frozen.
-__device__ inline bool cg_live(const double* rr, const double* rr0, const double* pq, double tol2,
-                               int64_t j) {
-  return rr[j] > tol2 * rr0[j] && pq[j] > 0.0;
+__device__ inline bool cg_live(double rr, double rr0, double pq, double tol2) {
+  return rr > tol2 * rr0 && pq > 0.0;
 }
 
-// live columns: alpha = rr / pq; x += alpha p; r -= alpha q; rr_new = |r|^2
-// (frozen columns: rr_new = rr, nothing else changes)
+// One conjugate-gradient step of a column, one workgroup each: pq = Re(p^H q),
+// and for live columns alpha = rr / pq; x += alpha p; r -= alpha q; beta = |r|^2
+// / rr; p = r + beta p; rr = |r|^2.  Frozen columns are left alone.  The
+// columns are independent, so the three phases need no launches between
+// them (three kernels left 8 us of launch gaps in a step of 60).
+constexpr int CGT = 512;
 template <int W>
-__global__ __launch_bounds__(TPB) void cg_step_k(double* __restrict__ X, double* __restrict__ R,
-                                                 const double* __restrict__ P,
+__global__ __launch_bounds__(CGT) void cg_step_k(double* __restrict__ X, double* __restrict__ R,
+                                                 double* __restrict__ P,
                                                  const double* __restrict__ Q, int64_t ld,
-                                                 int64_t n, const double* rr, const double* rr0,
-                                                 const double* pq, double tol2, double* rr_new) {
+                                                 int64_t n, double* rr, const double* rr0,
+                                                 double tol2) {
   const int64_t j = blockIdx.x;
-  if (!cg_live(rr, rr0, pq, tol2, j)) {
-    if (threadIdx.x == 0) rr_new[j] = rr[j];
-    return;
-  }
-  const double a = rr[j] / pq[j];
   double* x = X + j * ld * W;
   double* r = R + j * ld * W;
-  const double* p = P + j * ld * W;
+  double* p = P + j * ld * W;
   const double* q = Q + j * ld * W;
+  const double rrj = rr[j];
   double s = 0;
-  for (int64_t i = threadIdx.x; i < n * W; i += TPB) {
+  for (int64_t i = threadIdx.x; i < n * W; i += CGT) s += p[i] * q[i];
+  const double pq = block_sum1<CGT>(s);
+  if (!cg_live(rrj, rr0[j], pq, tol2)) return;  // the same in every thread
+  const double a = rrj / pq;
+  s = 0;
+  for (int64_t i = threadIdx.x; i < n * W; i += CGT) {
     x[i] += a * p[i];
     const double ri = r[i] - a * q[i];
     r[i] = ri;
     s += ri * ri;
   }
-  s = block_sum1(s);
-  if (threadIdx.x == 0) rr_new[j] = s;
-}
-
-// live columns (same test as cg_step_k, on the values before the step):
-// beta = rr_new / rr; p = r + beta p; rr = rr_new
-template <int W>
-__global__ __launch_bounds__(TPB) void cg_dir_k(double* __restrict__ P,
-                                                const double* __restrict__ R, int64_t ld,
-                                                int64_t n, double* rr, const double* rr0,
-                                                const double* pq, double tol2,
-                                                const double* rr_new) {
-  const int64_t j = blockIdx.x;
-  if (!cg_live(rr, rr0, pq, tol2, j)) return;
-  const double b = rr_new[j] / rr[j];
-  double* p = P + j * ld * W;
-  const double* r = R + j * ld * W;
-  for (int64_t i = threadIdx.x; i < n * W; i += TPB) p[i] = r[i] + b * p[i];
-  __syncthreads();
-  if (threadIdx.x == 0) rr[j] = rr_new[j];
+  const double rr_new = block_sum1<CGT>(s);
+  const double b = rr_new / rrj;
+  for (int64_t i = threadIdx.x; i < n * W; i += CGT) p[i] = r[i] + b * p[i];
+  if (threadIdx.x == 0) rr[j] = rr_new;
 }
 
 // E(i, j) = (M(i, j) - conj(M(j, i))) / (2 (lam_j - lam_i)) for i != j with
@@ -923,31 +912,17 @@ void col_dots(bool cplx, const void* X, int64_t ldx, const void* Y, int64_t ldy,
   CHASE_HIP(hipGetLastError());
 }
 
-void cg_step(bool cplx, void* X, void* R, const void* P, const void* Q, int64_t ld, int64_t n,
-             int64_t k, const double* rr, const double* rr0, const double* pq, double tol2,
-             double* rr_new, hipStream_t st) {
+void cg_step(bool cplx, void* X, void* R, void* P, const void* Q, int64_t ld, int64_t n, int64_t k,
+             double* rr, const double* rr0, double tol2, hipStream_t st) {
   if (k <= 0) return;
   if (cplx)
-    hipLaunchKernelGGL(cg_step_k<2>, dim3((unsigned)k), dim3(TPB), 0, st, static_cast<double*>(X),
-                       static_cast<double*>(R), static_cast<const double*>(P),
-                       static_cast<const double*>(Q), ld, n, rr, rr0, pq, tol2, rr_new);
+    hipLaunchKernelGGL(cg_step_k<2>, dim3((unsigned)k), dim3(CGT), 0, st, static_cast<double*>(X),
+                       static_cast<double*>(R), static_cast<double*>(P),
+                       static_cast<const double*>(Q), ld, n, rr, rr0, tol2);
   else
-    hipLaunchKernelGGL(cg_step_k<1>, dim3((unsigned)k), dim3(TPB), 0, st, static_cast<double*>(X),
-                       static_cast<double*>(R), static_cast<const double*>(P),
-                       static_cast<const double*>(Q), ld, n, rr, rr0, pq, tol2, rr_new);
-  CHASE_HIP(hipGetLastError());
-}
-
-void cg_dir(bool cplx, void* P, const void* R, int64_t ld, int64_t n, int64_t k, double* rr,
-            const double* rr0, const double* pq, double tol2, const double* rr_new,
-            hipStream_t st) {
-  if (k <= 0) return;
-  if (cplx)
-    hipLaunchKernelGGL(cg_dir_k<2>, dim3((unsigned)k), dim3(TPB), 0, st, static_cast<double*>(P),
-                       static_cast<const double*>(R), ld, n, rr, rr0, pq, tol2, rr_new);
-  else
-    hipLaunchKernelGGL(cg_dir_k<1>, dim3((unsigned)k), dim3(TPB), 0, st, static_cast<double*>(P),
-                       static_cast<const double*>(R), ld, n, rr, rr0, pq, tol2, rr_new);
+    hipLaunchKernelGGL(cg_step_k<1>, dim3((unsigned)k), dim3(CGT), 0, st, static_cast<double*>(X),
+                       static_cast<double*>(R), static_cast<double*>(P),
+                       static_cast<const double*>(Q), ld, n, rr, rr0, tol2);
   CHASE_HIP(hipGetLastError());
 }
 

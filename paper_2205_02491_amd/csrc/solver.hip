@@ -1677,9 +1677,7 @@ chase_status chase_eigvec_adjoint(chase_handle_t h, const void* H, int64_t ldh, 
     void* Q = h->Z;
     double* lam = h->d_evals;
     double* rr = h->d_coef;
-    double* rr_new = rr + ne;
-    double* pq = rr + 2 * ne;
-    double* rr0 = rr + 3 * ne;
+    double* rr0 = rr + ne;
     h2d_sync(lam, lambda_host, m * 8, st);
     // M = V^H G (m x m, in G, ld ne)
     gram(h, V, ldv, G, ldg, n, m, m, h->G, ne, false, st);
@@ -1698,9 +1696,9 @@ chase_status chase_eigvec_adjoint(chase_handle_t h, const void* H, int64_t ldh, 
     copy_cols(cplx, R, n, P, n, n, m, st);
     col_dots(cplx, R, n, R, n, n, m, rr, st);
     CHASE_HIP(hipMemcpyAsync(rr0, rr, m * 8, hipMemcpyDeviceToDevice, st));
-    std::vector<double> hr(m), hr0(m);
-    CHASE_HIP(hipMemcpyAsync(hr0.data(), rr0, m * 8, hipMemcpyDeviceToHost, st));
+    report(rr0, 1, nullptr, m, nullptr, nullptr, h->pin, st);
     CHASE_HIP(hipStreamSynchronize(st));
+    const std::vector<double> hr0(h->pin, h->pin + m);
     bool done = true;
     for (int j = 0; j < m; ++j) done = done && hr0[j] == 0.0;
     int it = 0;
@@ -1724,12 +1722,11 @@ chase_status chase_eigvec_adjoint(chase_handle_t h, const void* H, int64_t ldh, 
         g.beta = 1.0;
         gemm(cplx, PREC_F64, OP_N, OP_N, EPI_STORE, g, st);
       }
-      col_dots(cplx, P, n, Q, n, n, m, pq, st);
-      cg_step(cplx, X, R, P, Q, n, n, m, rr, rr0, pq, tol * tol, rr_new, st);
-      cg_dir(cplx, P, R, n, n, m, rr, rr0, pq, tol * tol, rr_new, st);
+      cg_step(cplx, X, R, P, Q, n, n, m, rr, rr0, tol * tol, st);
       if (it % 10 == 0 || it == max_iter) {
-        CHASE_HIP(hipMemcpyAsync(hr.data(), rr, m * 8, hipMemcpyDeviceToHost, st));
+        report(rr, 1, nullptr, m, nullptr, nullptr, h->pin, st);
         CHASE_HIP(hipStreamSynchronize(st));
+        const double* hr = h->pin;
         double worst = 0.0;
         for (int j = 0; j < m; ++j) {
           if (!std::isfinite(hr[j])) throw Error(CHASE_ERR_NUMERIC, "non-finite CG residual");
