@@ -26,7 +26,8 @@
 // lie along one row of C: 32 lanes then write 32 consecutive rows of a
 // column-major output.
 //
-// Workgroup tile 256 rows (of C) x 128 columns, K chunk 16 (one MFMA
+// Largest workgroup tile (smaller ones below) 256 rows (of C) x 128 columns,
+// K chunk 16 (one MFMA
 // k-step), 512 threads = 8 wave64 in a 4 x 2 grid, each owning 64 x 64 as
 // 2 x 2 fragments of 32 x 32 (230 VGPRs: two waves per SIMD).  Chunks are
 // copied global -> LDS by the gfx950 direct LDS loads (global_load_lds_dwordx4:
@@ -51,6 +52,19 @@
 // a workspace, and a second kernel sums the slices in FP64 and applies the
 // Chebyshev-step update.
 //
+// The two-term form rounds every intermediate block to bf16, and which way a
+// value falls depends on the last bits of the FP32 sum before it: two orders
+// of summation end 4e-7 apart on a block whose residual is 1e-4.  The result
+// is therefore held to one order: MFMA shape, k ascending, and the K slices
+// of a plan made for 256 x 128 tiles.  The tile itself does not enter, so it
+// is chosen freely: 64 to 256 rows by 64 to 128 columns, the same bytes.
+// What bounds a workgroup is filling its LDS (76 KB per 32-deep chunk at 256
+// x 96, about 14 B per clock and CU of the 12-20 the L2 gives): fewer bytes
+// per workgroup on more CUs.  Measured, two-term pass of 24 steps, complex:
+// 8000 x 260 7.4 -> 6.3 ms (192 x 96: 252 workgroups where 256 x 128 made
+// 192), 2111 x 90 1.19 -> 0.64 ms (128 x 96), 900 x 60 1.07 -> 0.39 ms and
+// 513 x 8 0.99 -> 0.35 ms (64 x 64; a chunk is 24 KB instead of 80).
+//
 // Measured on one MI355X (n=30000, 2000 columns, 1888 tiles): 32.9 ms per
 // step with the tail (34.3 ms without), 438 TFLOP/s algorithmic (1.3
 // PFLOP/s of BF16 MFMA work); two-term form 23.5 ms.  n=20000 with 1300 columns: 10.4 ms (11.2 ms
@@ -61,6 +75,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cstdlib>
+#include <type_traits>
 
 #include "common.h"
 
@@ -72,9 +87,10 @@ typedef float f16v __attribute__((ext_vector_type(16)));
 typedef double d2v __attribute__((ext_vector_type(2)));
 typedef unsigned int u4v __attribute__((ext_vector_type(4)));
 
-constexpr int TBM = S8_COLS_A;  // rows of C per workgroup (columns of the T split)
-constexpr int TBN = S8_COLS_B;  // columns of C per workgroup (columns of the X split)
-constexpr int NTHR = 512;
+// Largest tile of C per workgroup: rows (columns of the T split) and columns
+// (columns of the X split); the operands are padded to it.
+constexpr int TBM_MAX = S8_COLS_A;
+constexpr int TBN_MAX = S8_COLS_B;
 constexpr int KC = 16;          // K per chunk = one MFMA k-step
 constexpr int NSTAGE = 2;       // LDS stages (stage of chunk c: c & 1)
 
@@ -155,7 +171,7 @@ __device__ inline void cheb_elem(const GemmArgs& g, int64_t i, int64_t j, double
 // (l32, h) is C(i0 + wi*32*FI + fi*32 + l32, j0 + wj*32*FJ + fj*32 +
 // 8*(r/4) + 4*h + r%4) (the 32x32x16 MFMA result layout, measured on the
 // hardware).
-template <bool CPLX, int FI = 2, int FJ = 2>
+template <bool CPLX, int FI, int FJ>
 __device__ inline void epilogue(const GemmArgs& g, const f16v (&acc_re)[FI][FJ],
                                 const f16v (&acc_im)[FI][FJ], int64_t i0, int64_t j0, int wi,
                                 int wj, int l32, int h) {
@@ -177,7 +193,7 @@ __device__ inline void epilogue(const GemmArgs& g, const f16v (&acc_re)[FI][FJ],
 
 // Split-K tail: the FP32 partial tile of one K slice, column-major within
 // the tile (TBM rows), re then im.
-template <bool CPLX, int FI = 2, int FJ = 2>
+template <bool CPLX, int FI, int FJ, int TBM, int TBN>
 __device__ inline void store_partial(float* __restrict__ ws, const f16v (&acc_re)[FI][FJ],
                                      const f16v (&acc_im)[FI][FJ], int wi, int wj, int l32,
                                      int h) {
@@ -203,22 +219,37 @@ struct TailPlan {
   float* ws;
 };
 
-template <bool CPLX, bool SPLIT, int TERMS>
-__global__ __launch_bounds__(NTHR) void gemm_bf16x3_kernel(GemmArgs g, int tiles_n, int ntiles,
-                                                           TailPlan tp) {
+// Waves of a TBM x TBN tile: FI x FJ fragments of 32 x 32 each, at most
+// eight waves; few enough fragments per wave that the four SIMDs hold equal
+// shares where the tile divides that way.
+template <int TBM, int TBN>
+struct Layout {
+  static constexpr int FI = TBM == 256 && TBN == 128 ? 2 : TBM == 192 && TBN == 128 ? 3 : 1;
+  static constexpr int FJ = TBM == 64    ? 1
+                            : TBM == 192 && TBN == 128 ? 1
+                            : TBN == 96  ? 3
+                            : TBM == 128 && TBN == 64 ? 1
+                                         : 2;
+  static constexpr int WGI = TBM / (32 * FI);  // waves along the rows of C
+  static constexpr int WGJ = TBN / (32 * FJ);  // and along its columns
+  static constexpr int NTHR = 64 * WGI * WGJ;
+  static_assert(WGI * 32 * FI == TBM && WGJ * 32 * FJ == TBN && NTHR <= 512, "waves, tile");
+};
+
+template <bool CPLX, bool SPLIT, int TERMS, int TBM, int TBN>
+__global__ __launch_bounds__((Layout<TBM, TBN>::NTHR)) void gemm_bf16x3_kernel(
+    GemmArgs g, int tiles_n, int ntiles, TailPlan tp) {
   static_assert(TERMS == 2 || TERMS == 3, "two or three split terms");
   constexpr int P = CPLX ? 4 : 2;
   constexpr int CB = (KC / 8) * P * 16;  // bytes of one column in one chunk
   constexpr int PIECES = CB / 16;
-  constexpr int NW = NTHR / 64;
+  using L = Layout<TBM, TBN>;
+  constexpr int FI = L::FI, FJ = L::FJ, WGI = L::WGI, NW = L::NTHR / 64;
   constexpr int NCOL = TBM + TBN;
   constexpr int STAGE = NCOL * CB;
   constexpr int BLK_COLS = 1024 / CB;    // columns per 1 KB wave load
   constexpr int NBLK = NCOL / BLK_COLS;
-  constexpr int LOADS = NBLK / NW;       // wave loads per chunk
-  constexpr int WGI = TBM / 64;          // waves along the rows of C
-  static_assert(WGI * (TBN / 64) == NW, "64 x 64 per wave");
-  static_assert(LOADS * NW == NBLK && LOADS <= 15, "chunk / waves, vmcnt immediate");
+  constexpr int LOADS = (NBLK + NW - 1) / NW;  // wave loads per chunk
   __shared__ __attribute__((aligned(1024))) char lds[NSTAGE * STAGE];
 
   // Workgroup ids are remapped so that each XCD takes a contiguous range of
@@ -252,6 +283,7 @@ __global__ __launch_bounds__(NTHR) void gemm_bf16x3_kernel(GemmArgs g, int tiles
 #pragma unroll
     for (int e = 0; e < LOADS; ++e) {
       const int blk = wave * LOADS + e;
+      if (NBLK % NW != 0 && blk >= NBLK) continue;
       const int col0 = blk * BLK_COLS;
       const int pc = slot(col0 + bc, lane % PIECES);  // slot() is an involution in p
       // two terms: the block's lo planes (odd pieces) are never read, so they
@@ -266,11 +298,11 @@ __global__ __launch_bounds__(NTHR) void gemm_bf16x3_kernel(GemmArgs g, int tiles
     }
   };
 
-  f16v acc_re[2][2], acc_im[2][2];
+  f16v acc_re[FI][FJ], acc_im[FI][FJ];
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < FI; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
+    for (int b = 0; b < FJ; ++b) {
       acc_re[a][b] = f16v{};
       acc_im[a][b] = f16v{};
     }
@@ -290,24 +322,27 @@ __global__ __launch_bounds__(NTHR) void gemm_bf16x3_kernel(GemmArgs g, int tiles
     asm volatile("" ::: "memory");
     if (c + 1 < ce) issue(c + 1);
     const char* st = lds + (int)(c & 1) * STAGE;
-    u4v tf[2][P], xf[2][P];
+    u4v tf[FI][P], xf[FJ][P];
 #pragma unroll
-    for (int f = 0; f < 2; ++f) {
-      const int ct = wi * 64 + f * 32 + l32;
-      const int cx = TBM + wj * 64 + f * 32 + l32;
+    for (int f = 0; f < FI; ++f) {
+      const int ct = wi * (32 * FI) + f * 32 + l32;
 #pragma unroll
-      for (int p = 0; p < P; ++p) {
-        const int pc = h * P + p;
-        tf[f][p] = *reinterpret_cast<const u4v*>(st + ct * CB + slot(ct, pc) * 16);
-        xf[f][p] = *reinterpret_cast<const u4v*>(st + cx * CB + slot(cx, pc) * 16);
-      }
+      for (int p = 0; p < P; ++p)
+        tf[f][p] = *reinterpret_cast<const u4v*>(st + ct * CB + slot(ct, h * P + p) * 16);
+    }
+#pragma unroll
+    for (int f = 0; f < FJ; ++f) {
+      const int cx = TBM + wj * (32 * FJ) + f * 32 + l32;
+#pragma unroll
+      for (int p = 0; p < P; ++p)
+        xf[f][p] = *reinterpret_cast<const u4v*>(st + cx * CB + slot(cx, h * P + p) * 16);
     }
     if constexpr (CPLX) {
 #pragma unroll
-      for (int fj = 0; fj < 2; ++fj) {
+      for (int fj = 0; fj < FJ; ++fj) {
         const u4v nxi_h = neg_u4(xf[fj][2]), nxi_l = neg_u4(xf[fj][3]);
 #pragma unroll
-        for (int fi = 0; fi < 2; ++fi) {
+        for (int fi = 0; fi < FI; ++fi) {
           f16v re = acc_re[fi][fj], im = acc_im[fi][fj];
           if constexpr (TERMS == 3) {  // block lo planes
             re = mfma(xf[fj][1], tf[fi][0], re);
@@ -331,9 +366,9 @@ __global__ __launch_bounds__(NTHR) void gemm_bf16x3_kernel(GemmArgs g, int tiles
       }
     } else {
 #pragma unroll
-      for (int fj = 0; fj < 2; ++fj)
+      for (int fj = 0; fj < FJ; ++fj)
 #pragma unroll
-        for (int fi = 0; fi < 2; ++fi) {
+        for (int fi = 0; fi < FI; ++fi) {
           f16v re = acc_re[fi][fj];
           if constexpr (TERMS == 3) re = mfma(xf[fj][1], tf[fi][0], re);
           re = mfma(xf[fj][0], tf[fi][1], re);
@@ -343,10 +378,10 @@ __global__ __launch_bounds__(NTHR) void gemm_bf16x3_kernel(GemmArgs g, int tiles
     }
   }
   if constexpr (SPLIT)
-    store_partial<CPLX>(tp.ws + (int64_t)u * (CPLX ? 2 : 1) * (TBM * TBN), acc_re, acc_im, wi, wj,
-                        l32, h);
+    store_partial<CPLX, FI, FJ, TBM, TBN>(tp.ws + (int64_t)u * (CPLX ? 2 : 1) * (TBM * TBN),
+                                          acc_re, acc_im, wi, wj, l32, h);
   else
-    epilogue<CPLX>(g, acc_re, acc_im, i0, j0, wi, wj, l32, h);
+    epilogue<CPLX, FI, FJ>(g, acc_re, acc_im, i0, j0, wi, wj, l32, h);
 }
 
 // Two-term products with a 32-deep K chunk per barrier.  The block operand
@@ -366,23 +401,22 @@ __device__ inline int lds_slot(int c, int p) {
   return p ^ ((c / R) & (PIECES - 1));
 }
 
-template <bool CPLX, bool SPLIT>
-__global__ __launch_bounds__(NTHR) void gemm_bf16x2_k32_kernel(GemmArgs g, int tiles_n,
-                                                               int ntiles, TailPlan tp) {
+template <bool CPLX, bool SPLIT, int TBM, int TBN>
+__global__ __launch_bounds__((Layout<TBM, TBN>::NTHR)) void gemm_bf16x2_k32_kernel(
+    GemmArgs g, int tiles_n, int ntiles, TailPlan tp) {
   constexpr int P = CPLX ? 4 : 2;   // planes of a group in the s8 layout
   constexpr int PX = P / 2;         // the block's hi planes (re_hi, im_hi)
   constexpr int GPC = KC2 / 8;      // 8-row groups per chunk
   constexpr int CBT = GPC * P * 16;   // bytes of a T column per chunk
   constexpr int CBX = GPC * PX * 16;  // bytes of a block column per chunk (hi planes)
   constexpr int PT = CBT / 16, PXN = CBX / 16;
-  constexpr int NW = NTHR / 64;
+  using L = Layout<TBM, TBN>;
+  constexpr int FI = L::FI, FJ = L::FJ, WGI = L::WGI, NW = L::NTHR / 64;
   constexpr int TBYTES = TBM * CBT;
   constexpr int STAGE = TBYTES + TBN * CBX;
   constexpr int TBLK = TBYTES / 1024, XBLK = TBN * CBX / 1024;
-  constexpr int LOADS = (TBLK + XBLK) / NW;
-  constexpr int WGI = TBM / 64;
-  static_assert(WGI * (TBN / 64) == NW, "64 x 64 per wave");
-  static_assert(LOADS * NW == TBLK + XBLK && LOADS <= 15, "chunk / waves, vmcnt immediate");
+  constexpr int NBLK = TBLK + XBLK;
+  constexpr int LOADS = (NBLK + NW - 1) / NW;
   static_assert(2 * STAGE <= 160 * 1024, "two stages in the CU's LDS");
   __shared__ __attribute__((aligned(1024))) char lds[2 * STAGE];
 
@@ -412,6 +446,7 @@ __global__ __launch_bounds__(NTHR) void gemm_bf16x2_k32_kernel(GemmArgs g, int t
 #pragma unroll
     for (int e = 0; e < LOADS; ++e) {
       const int blk = wave * LOADS + e;
+      if (NBLK % NW != 0 && blk >= NBLK) continue;
       const char* src;
       if (blk < TBLK) {
         const int col = blk * (1024 / CBT) + lane / PT;
@@ -429,11 +464,11 @@ __global__ __launch_bounds__(NTHR) void gemm_bf16x2_k32_kernel(GemmArgs g, int t
     }
   };
 
-  f16v acc_re[2][2], acc_im[2][2];
+  f16v acc_re[FI][FJ], acc_im[FI][FJ];
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < FI; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
+    for (int b = 0; b < FJ; ++b) {
       acc_re[a][b] = f16v{};
       acc_im[a][b] = f16v{};
     }
@@ -455,15 +490,18 @@ __global__ __launch_bounds__(NTHR) void gemm_bf16x2_k32_kernel(GemmArgs g, int t
 #pragma unroll
     for (int s = 0; s < KC2 / 16; ++s) {
       const int gq = 2 * s + h;  // the lane's 8-row group within the chunk
-      u4v tf[2][P], xf[2][PX];
+      u4v tf[FI][P], xf[FJ][PX];
 #pragma unroll
-      for (int f = 0; f < 2; ++f) {
-        const int ct = wi * 64 + f * 32 + l32;
-        const int cx = wj * 64 + f * 32 + l32;
+      for (int f = 0; f < FI; ++f) {
+        const int ct = wi * (32 * FI) + f * 32 + l32;
 #pragma unroll
         for (int p = 0; p < P; ++p)
           tf[f][p] = *reinterpret_cast<const u4v*>(st + ct * CBT +
                                                    lds_slot<CBT, PT>(ct, gq * P + p) * 16);
+      }
+#pragma unroll
+      for (int f = 0; f < FJ; ++f) {
+        const int cx = wj * (32 * FJ) + f * 32 + l32;
 #pragma unroll
         for (int q = 0; q < PX; ++q)
           xf[f][q] = *reinterpret_cast<const u4v*>(stx + cx * CBX +
@@ -471,10 +509,10 @@ __global__ __launch_bounds__(NTHR) void gemm_bf16x2_k32_kernel(GemmArgs g, int t
       }
       if constexpr (CPLX) {
 #pragma unroll
-        for (int fj = 0; fj < 2; ++fj) {
+        for (int fj = 0; fj < FJ; ++fj) {
           const u4v nxi = neg_u4(xf[fj][1]);
 #pragma unroll
-          for (int fi = 0; fi < 2; ++fi) {
+          for (int fi = 0; fi < FI; ++fi) {
             f16v re = acc_re[fi][fj], im = acc_im[fi][fj];
             re = mfma(xf[fj][0], tf[fi][1], re);
             im = mfma(xf[fj][1], tf[fi][1], im);
@@ -490,9 +528,9 @@ __global__ __launch_bounds__(NTHR) void gemm_bf16x2_k32_kernel(GemmArgs g, int t
         }
       } else {
 #pragma unroll
-        for (int fj = 0; fj < 2; ++fj)
+        for (int fj = 0; fj < FJ; ++fj)
 #pragma unroll
-          for (int fi = 0; fi < 2; ++fi) {
+          for (int fi = 0; fi < FI; ++fi) {
             f16v re = acc_re[fi][fj];
             re = mfma(xf[fj][0], tf[fi][1], re);
             re = mfma(xf[fj][0], tf[fi][0], re);
@@ -502,15 +540,15 @@ __global__ __launch_bounds__(NTHR) void gemm_bf16x2_k32_kernel(GemmArgs g, int t
     }
   }
   if constexpr (SPLIT)
-    store_partial<CPLX>(tp.ws + (int64_t)u * (CPLX ? 2 : 1) * (TBM * TBN), acc_re, acc_im, wi, wj,
-                        l32, h);
+    store_partial<CPLX, FI, FJ, TBM, TBN>(tp.ws + (int64_t)u * (CPLX ? 2 : 1) * (TBM * TBN),
+                                          acc_re, acc_im, wi, wj, l32, h);
   else
-    epilogue<CPLX>(g, acc_re, acc_im, i0, j0, wi, wj, l32, h);
+    epilogue<CPLX, FI, FJ>(g, acc_re, acc_im, i0, j0, wi, wj, l32, h);
 }
 
 // Split-K tail: sum the slices' partial tiles (FP64) and apply the
 // Chebyshev-step update, one element per thread, rows fastest.
-template <bool CPLX>
+template <bool CPLX, int TBM, int TBN>
 __global__ void tail_finish_k(GemmArgs g, int tiles_n, TailPlan tp) {
   constexpr int TE = TBM * TBN;
   const int64_t total = (int64_t)tp.rem * TE;
@@ -606,6 +644,50 @@ bool two_term_k32() {
   return on;
 }
 
+// The launches of one product: whole tiles, then the tail's slices and sum.
+template <int TBM, int TBN, bool CPLX, bool SPLIT>
+static void launch_tiles(bool k32, int terms, const GemmArgs& g, int tiles_n, int items,
+                         int ntiles, const TailPlan& tp, hipStream_t st) {
+  const dim3 grid((items + 7) / 8 * 8), block(Layout<TBM, TBN>::NTHR);
+  if (k32)
+    hipLaunchKernelGGL((gemm_bf16x2_k32_kernel<CPLX, SPLIT, TBM, TBN>), grid, block, 0, st, g,
+                       tiles_n, ntiles, tp);
+  else if (terms == 3)
+    hipLaunchKernelGGL((gemm_bf16x3_kernel<CPLX, SPLIT, 3, TBM, TBN>), grid, block, 0, st, g,
+                       tiles_n, ntiles, tp);
+  else if constexpr (TBM == TBM_MAX && TBN == TBN_MAX)
+    hipLaunchKernelGGL((gemm_bf16x3_kernel<CPLX, SPLIT, 2, TBM, TBN>), grid, block, 0, st, g,
+                       tiles_n, ntiles, tp);
+  CHASE_HIP(hipGetLastError());
+}
+
+template <int TBM, int TBN, bool CPLX>
+static void run_tiles_of(bool k32, int terms, const GemmArgs& g, int tiles_n, int ntiles,
+                         const TailPlan& tp, hipStream_t st) {
+  const int whole = ntiles - tp.rem;
+  if (whole > 0)
+    launch_tiles<TBM, TBN, CPLX, false>(k32, terms, g, tiles_n, whole, whole, tp, st);
+  if (tp.rem > 0) {
+    launch_tiles<TBM, TBN, CPLX, true>(k32, terms, g, tiles_n, tp.rem * tp.slices, ntiles, tp,
+                                       st);
+    const int64_t elems = (int64_t)tp.rem * TBM * TBN;
+    const unsigned fin = (unsigned)std::min<int64_t>((elems + 255) / 256, 8192);
+    hipLaunchKernelGGL((tail_finish_k<CPLX, TBM, TBN>), dim3(fin), dim3(256), 0, st, g, tiles_n,
+                       tp);
+    CHASE_HIP(hipGetLastError());
+  }
+}
+
+template <int TBM, int TBN>
+static void run_tiles(bool cplx, bool k32, int terms, const GemmArgs& g, int tiles_n, int ntiles,
+                      const TailPlan& tp, hipStream_t st) {
+  static_assert(TBM <= TBM_MAX && TBN <= TBN_MAX, "operands and workspace sized for the largest");
+  if (cplx)
+    run_tiles_of<TBM, TBN, true>(k32, terms, g, tiles_n, ntiles, tp, st);
+  else
+    run_tiles_of<TBM, TBN, false>(k32, terms, g, tiles_n, ntiles, tp, st);
+}
+
 void gemm_bf16x3(bool cplx, const GemmArgs& g, hipStream_t st, int terms) {
   if (g.M <= 0 || g.N <= 0) return;
   CHASE_REQUIRE(g.a_s8 && g.b_s8 && g.s8_groups > 0 && g.s8_groups % (KC / 8) == 0,
@@ -613,8 +695,8 @@ void gemm_bf16x3(bool cplx, const GemmArgs& g, hipStream_t st, int terms) {
   CHASE_REQUIRE(g.s8_groups * 8 >= g.K, "split-BF16 operands shorter than K");
   CHASE_REQUIRE(terms == 2 || terms == 3, "split-BF16 products take two or three terms");
   const bool k32 = terms == 2 && g.s8_groups % (KC2 / 8) == 0 && two_term_k32();
-  const int tiles_m = (int)((g.M + TBM - 1) / TBM);
-  const int tiles_n = (int)((g.N + TBN - 1) / TBN);
+  const int tiles_m = (int)((g.M + TBM_MAX - 1) / TBM_MAX);
+  const int tiles_n = (int)((g.N + TBN_MAX - 1) / TBN_MAX);
   const int ntiles = tiles_m * tiles_n;
   const int64_t nchunks = g.s8_groups / ((k32 ? KC2 : KC) / 8);
   // One workgroup per CU (LDS-bound), so a launch runs in rounds of `cus`
@@ -637,59 +719,50 @@ void gemm_bf16x3(bool cplx, const GemmArgs& g, hipStream_t st, int terms) {
       }
     }
   }
-  const int whole = ntiles - tp.rem;
-  if (whole > 0) {
-    const int grid_x = (whole + 7) / 8 * 8;
-    if (cplx && k32)
-      hipLaunchKernelGGL((gemm_bf16x2_k32_kernel<true, false>), dim3(grid_x), dim3(NTHR), 0, st,
-                         g, tiles_n, whole, tp);
-    else if (k32)
-      hipLaunchKernelGGL((gemm_bf16x2_k32_kernel<false, false>), dim3(grid_x), dim3(NTHR), 0, st,
-                         g, tiles_n, whole, tp);
-    else if (cplx && terms == 3)
-      hipLaunchKernelGGL((gemm_bf16x3_kernel<true, false, 3>), dim3(grid_x), dim3(NTHR), 0, st, g,
-                         tiles_n, whole, tp);
-    else if (cplx)
-      hipLaunchKernelGGL((gemm_bf16x3_kernel<true, false, 2>), dim3(grid_x), dim3(NTHR), 0, st, g,
-                         tiles_n, whole, tp);
-    else if (terms == 3)
-      hipLaunchKernelGGL((gemm_bf16x3_kernel<false, false, 3>), dim3(grid_x), dim3(NTHR), 0, st,
-                         g, tiles_n, whole, tp);
-    else
-      hipLaunchKernelGGL((gemm_bf16x3_kernel<false, false, 2>), dim3(grid_x), dim3(NTHR), 0, st,
-                         g, tiles_n, whole, tp);
-    CHASE_HIP(hipGetLastError());
+  // The plan above fixes every element's K slices and with them its bytes;
+  // the tile may still shrink.  Columns: the narrowest width that covers the
+  // block with as many column tiles (260 columns: 3 x 96 instead of 3 x 128,
+  // 346 -> 282 us per step at n = 8000).  Rows, where all tiles have the same
+  // slices (all in the tail, or none): the fewest with which every workgroup
+  // still has a CU of its own (a second round would cost what the smaller
+  // tile saves) and the last tile stays inside the operand's padding, which
+  // is to 256 rows.  The 16-deep two-term kernel is for comparison only and
+  // keeps the largest tile.
+  const int tbn = !k32 && terms == 2 ? TBN_MAX
+                  : tiles_n * 64 >= g.N ? 64
+                  : tiles_n * 96 >= g.N ? 96
+                                        : TBN_MAX;
+  int tbm = TBM_MAX;
+  if ((tp.rem == 0 || tp.rem == ntiles) && (k32 || terms == 3)) {
+    for (int rows : {64, 128, 192}) {
+      if (rows == 192 && tbn == 64) continue;
+      const int64_t tm = (g.M + rows - 1) / rows;
+      if (tm * tiles_n * tp.slices > std::min(cus, S8_TAIL_SLOTS) || tm * rows > (int64_t)tiles_m * TBM_MAX) continue;
+      tbm = rows;
+      break;
+    }
   }
-  if (tp.rem > 0) {
-    const int items = tp.rem * tp.slices;
-    const int grid_x = (items + 7) / 8 * 8;
-    const int64_t elems = (int64_t)tp.rem * TBM * TBN;
-    const unsigned fin = (unsigned)std::min<int64_t>((elems + 255) / 256, 8192);
-    if (cplx && k32)
-      hipLaunchKernelGGL((gemm_bf16x2_k32_kernel<true, true>), dim3(grid_x), dim3(NTHR), 0, st,
-                         g, tiles_n, ntiles, tp);
-    else if (k32)
-      hipLaunchKernelGGL((gemm_bf16x2_k32_kernel<false, true>), dim3(grid_x), dim3(NTHR), 0, st,
-                         g, tiles_n, ntiles, tp);
-    else if (cplx && terms == 3)
-      hipLaunchKernelGGL((gemm_bf16x3_kernel<true, true, 3>), dim3(grid_x), dim3(NTHR), 0, st, g,
-                         tiles_n, ntiles, tp);
-    else if (cplx)
-      hipLaunchKernelGGL((gemm_bf16x3_kernel<true, true, 2>), dim3(grid_x), dim3(NTHR), 0, st, g,
-                         tiles_n, ntiles, tp);
-    else if (terms == 3)
-      hipLaunchKernelGGL((gemm_bf16x3_kernel<false, true, 3>), dim3(grid_x), dim3(NTHR), 0, st,
-                         g, tiles_n, ntiles, tp);
-    else
-      hipLaunchKernelGGL((gemm_bf16x3_kernel<false, true, 2>), dim3(grid_x), dim3(NTHR), 0, st,
-                         g, tiles_n, ntiles, tp);
-    CHASE_HIP(hipGetLastError());
-    if (cplx)
-      hipLaunchKernelGGL(tail_finish_k<true>, dim3(fin), dim3(256), 0, st, g, tiles_n, tp);
-    else
-      hipLaunchKernelGGL(tail_finish_k<false>, dim3(fin), dim3(256), 0, st, g, tiles_n, tp);
-    CHASE_HIP(hipGetLastError());
-  }
+  const int tiles = (int)((g.M + tbm - 1) / tbm) * tiles_n;
+  if (tp.rem && tbm != TBM_MAX) tp.rem = tiles;
+  auto run = [&](auto m, auto n) {
+    run_tiles<decltype(m)::value, decltype(n)::value>(cplx, k32, terms, g, tiles_n, tiles, tp, st);
+  };
+  auto rows = [&](auto n) {
+    if (tbm == 64)
+      run(std::integral_constant<int, 64>{}, n);
+    else if (tbm == 128)
+      run(std::integral_constant<int, 128>{}, n);
+    else if (tbm == TBM_MAX)
+      run(std::integral_constant<int, TBM_MAX>{}, n);
+    else if constexpr (decltype(n)::value != 64)
+      run(std::integral_constant<int, 192>{}, n);
+  };
+  if (tbn == 64)
+    rows(std::integral_constant<int, 64>{});
+  else if (tbn == 96)
+    rows(std::integral_constant<int, 96>{});
+  else
+    rows(std::integral_constant<int, TBN_MAX>{});
 }
 
 }  // namespace chase

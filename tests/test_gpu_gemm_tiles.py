@@ -121,3 +121,38 @@ def test_int8_products_tile_edges(pk, cplx, n, k):
     y = to_np(y)
     err = np.max(np.abs(y - y_ref), axis=0) / np.max(np.abs(y_ref), axis=0)
     assert err.max() < 1e-12, (int(err.argmax()), float(err.max()))
+
+
+@pytest.mark.parametrize("prec", ["bf16x3", "bf16x2"])
+@pytest.mark.parametrize("cplx", [True, False])
+@pytest.mark.parametrize("n,k_wide,ks", [(300, 128, (1, 33, 64, 65, 96, 97)),
+                                         (1100, 230, (129, 190, 192, 193)),
+                                         (2300, 128, (31, 96)), (3500, 128, (40, 64, 65, 96))])
+def test_split_bf16_tiles(pk, cplx, prec, n, k_wide, ks):
+    """Split-BF16 products at the tiles their rule picks (64, 128, 192 and 256
+    rows by 64, 96 and 128 columns).  Same number of column tiles: the same K
+    slices and the same order of every element's sum, so the columns a
+    narrower block shares with a wider one are the same bytes.  Against the
+    FP64 defect pass: products relative to the residual (1e-4 of the block)
+    are off by 2^-16 (three terms) or 2^-8 (two terms), six steps amplify by
+    less than 24."""
+    announce(f"split-BF16 tiles: {prec} n={n} k={k_wide} {ks} cplx={cplx}")
+    code = pk.PREC_BF16X3 if prec == "bf16x3" else pk.PREC_BF16X2
+    g = np.random.Generator(np.random.PCG64(47 * n + k_wide))
+    z = gen.gaussian(g, (n, n), cplx)
+    h = z + z.conj().T
+    h = to_gpu(h * (np.sqrt(n) / (2.1 * np.linalg.norm(h))))
+    v = np.linalg.qr(gen.gaussian(g, (n, k_wide), cplx))[0]
+    r = gen.gaussian(g, (n, k_wide), cplx) * 1e-4 / np.sqrt(n)
+    theta = np.linspace(-1.0, -0.6, k_wide)
+
+    def run(k, prec):
+        return to_np(pk.chase_filter_ritz(h, to_gpu(v[:, :k].copy()), to_gpu(r[:, :k].copy()),
+                                          theta[:k], np.full(k, 6, np.int32), 1.05, -1.02, -0.5,
+                                          prec=prec)[0])
+
+    wide, ref = run(k_wide, code), run(k_wide, pk.PREC_FP64)
+    tol = 1e-4 * 24 * 2.0 ** (-16 if prec == "bf16x3" else -8)
+    assert np.max(np.abs(wide - ref)) <= tol * np.max(np.abs(ref))
+    for k in ks:
+        assert np.array_equal(run(k, code), wide[:, :k]), k
