@@ -6,15 +6,17 @@
 // into blocks of JB indices.  A sweep is the round-robin tournament over the
 // blocks: in each round every pair of blocks (p, q) gets one cyclic Jacobi
 // sweep over its 2 JB indices, run by one workgroup in LDS and accumulated
-// into a 2JB x 2JB unitary U_pq; one launch then applies all pairs' U to the
-// whole matrix (G <- J^H G J, J the block-diagonal product of the U_pq) and
-// to the eigenvector block (V <- V J).  The convergence is quadratic; in the
+// into a 2JB x 2JB unitary U_pq; the next round's launch applies all pairs' U
+// to the whole matrix (G <- J^H G J, J the block-diagonal product of the U_pq)
+// and to the eigenvector block (V <- V J) beside its own pairs, which form
+// their subproblems themselves.  The convergence is quadratic; in the
 // subspace iteration the projected matrix is close to diagonal once the
 // Ritz vectors settle, and then a few sweeps suffice.
 #include "common.h"
 
 #include <algorithm>
 #include <cmath>
+#include <utility>
 
 namespace chase {
 namespace {
@@ -24,7 +26,6 @@ constexpr int JM = 2 * JB;   // order of a pair's subproblem
 constexpr int JLD = JM + 1;  // LDS leading dimension (padded against bank conflicts)
 constexpr int JT = 256;      // threads per workgroup
 constexpr int JPT = 2 * JT;  // threads per workgroup of the pair solves
-constexpr int JCG = JT / JM; // column groups of the tile stores (8)
 constexpr int NPART = 256;   // workgroups of the norm reduction
 
 struct cd {
@@ -65,6 +66,14 @@ __host__ __device__ inline int rr_player(int m, int r, int j) {
   return j == 0 ? 0 : (j - 1 + r) % (m - 1) + 1;
 }
 
+// Pair of round r that player x (of m) is in, and whether as its first (0) or
+// second (1) player: the inverse of rr_player.
+__device__ inline void rr_place(int m, int r, int x, int& pair, int& half) {
+  const int j = x == 0 ? 0 : (x - 1 + (m - 1) - r) % (m - 1) + 1;
+  half = j >= m / 2;
+  pair = half ? m - 1 - j : j;
+}
+
 // Player of an inner round (m = JM, 0 <= r < JM - 1) without a division.
 __device__ __forceinline__ int inner_player(int r, int j) {
   const int p = j - 1 + r;
@@ -101,6 +110,150 @@ __device__ __forceinline__ int jac_rotation(double app, double aqq, T apq, doubl
   return 1;
 }
 
+typedef double d4v __attribute__((ext_vector_type(4)));
+
+// Y = A B for JM x JM tiles in LDS on the FP64 matrix cores (16x16x4 MFMA),
+// A(i, l) at As[l * JLD + i] and B(l, c) at Bs[l * JLD + c].  Wave w of the
+// four computes the quadrant of rows 16 (w & 1) and columns 16 (w >> 1).
+// The operands go in swapped (B first), so the instruction produces the
+// quadrant transposed: lane L holds Y(16 (w & 1) + L % 16, 16 (w >> 1) +
+// L / 16 + 4 r) in out[r] (rows run along the lanes, as stores want them).
+__device__ __forceinline__ void tile_mma(const double* As, const double* Bs, double (&out)[4]) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int i0 = 16 * (w & 1), c0 = 16 * (w >> 1), l16 = lane & 15, lk = lane >> 4;
+  d4v acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int k0 = 0; k0 < JM; k0 += 4) {
+    const double a = As[(k0 + lk) * JLD + i0 + l16];
+    const double b = Bs[(k0 + lk) * JLD + c0 + l16];
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(b, a, acc, 0, 0, 0);
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) out[r] = acc[r];
+}
+__device__ __forceinline__ void tile_mma(const cd* As, const cd* Bs, cd (&out)[4]) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int i0 = 16 * (w & 1), c0 = 16 * (w >> 1), l16 = lane & 15, lk = lane >> 4;
+  d4v re = {0.0, 0.0, 0.0, 0.0}, im = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int k0 = 0; k0 < JM; k0 += 4) {
+    const cd a = As[(k0 + lk) * JLD + i0 + l16];
+    const cd b = Bs[(k0 + lk) * JLD + c0 + l16];
+    re = __builtin_amdgcn_mfma_f64_16x16x4f64(b.x, a.x, re, 0, 0, 0);
+    re = __builtin_amdgcn_mfma_f64_16x16x4f64(-b.y, a.y, re, 0, 0, 0);
+    im = __builtin_amdgcn_mfma_f64_16x16x4f64(b.y, a.x, im, 0, 0, 0);
+    im = __builtin_amdgcn_mfma_f64_16x16x4f64(b.x, a.y, im, 0, 0, 0);
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) out[r] = cd{re[r], im[r]};
+}
+
+// Position of out[r] of tile_mma in this thread: row, column.
+__device__ __forceinline__ int mma_row() { return 16 * ((threadIdx.x >> 6) & 1) + (threadIdx.x & 15); }
+__device__ __forceinline__ int mma_col(int r) {
+  return 16 * (threadIdx.x >> 7) + ((threadIdx.x & 63) >> 4) + 4 * r;
+}
+
+// One 16 x 16 product over JM = 32 terms on the FP64 matrix cores: C(r, c) =
+// sum_l a(l, r) b(l, c), from the lane's a(4 s + L / 16, L % 16) and b(4 s + L
+// / 16, L % 16), s = 0 .. 7; lane L gets C(L % 16, L / 16 + 4 q) in out[q]
+// (operands swapped as in tile_mma).
+__device__ __forceinline__ void quad_mma(const double (&a)[JM / 4], const double (&b)[JM / 4],
+                                         double (&out)[4]) {
+  d4v acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int s = 0; s < JM / 4; ++s)
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(b[s], a[s], acc, 0, 0, 0);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) out[q] = acc[q];
+}
+__device__ __forceinline__ void quad_mma(const cd (&a)[JM / 4], const cd (&b)[JM / 4],
+                                         cd (&out)[4]) {
+  d4v re = {0.0, 0.0, 0.0, 0.0}, im = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int s = 0; s < JM / 4; ++s) {
+    re = __builtin_amdgcn_mfma_f64_16x16x4f64(b[s].x, a[s].x, re, 0, 0, 0);
+    im = __builtin_amdgcn_mfma_f64_16x16x4f64(b[s].y, a[s].x, im, 0, 0, 0);
+    re = __builtin_amdgcn_mfma_f64_16x16x4f64(-b[s].y, a[s].y, re, 0, 0, 0);
+    im = __builtin_amdgcn_mfma_f64_16x16x4f64(b[s].x, a[s].y, im, 0, 0, 0);
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) out[q] = cd{re[q], im[q]};
+}
+
+constexpr int THLD = JB + 1;  // row length of the half tiles in pair_load
+
+// The subproblem of blocks (bp, bq) after the rotations of round `prev`, from
+// the matrix before them: bp was in pair x of that round (indices X), bq in
+// pair y (indices Y), x != y as two blocks meet once a sweep, so
+//   S = [ Ux' G(X,X) Ux, Ux' G(X,Y) Uy; ., Uy' G(Y,Y) Uy ]
+// with the JB columns of Ux and Uy that belong to bp and bq.  Six waves form
+// the three right products (32 x 16, one 16-row half each) straight from
+// global memory, three the left ones.  Ts: 3 * JM * THLD elements.
+template <class T>
+__device__ void pair_load(const T* __restrict__ G, int64_t ldg, int k, int nb, int prev, int bp,
+                          int bq, const T* __restrict__ uprev, T* S, T* Ts) {
+  int x, hx, y, hy;
+  rr_place(nb, prev, bp, x, hx);
+  rr_place(nb, prev, bq, y, hy);
+  const int x0 = rr_player(nb, prev, x), x1 = rr_player(nb, prev, nb - 1 - x);
+  const int y0 = rr_player(nb, prev, y), y1 = rr_player(nb, prev, nb - 1 - y);
+  const T* Ux = uprev + (int64_t)x * JM * JM + hx * JB * JM;  // its JB columns
+  const T* Uy = uprev + (int64_t)y * JM * JM + hy * JB * JM;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int l16 = lane & 15, lk = lane >> 4;
+  if (w < 6) {
+    const int s = w >> 1;  // product: (X,X), (X,Y), (Y,Y)
+    const int rh = w & 1;  // 16-row half
+    const int gr = (s < 2 ? (rh ? x1 : x0) : (rh ? y1 : y0)) * JB + l16;
+    const int c0 = s == 0 ? x0 : y0, c1 = s == 0 ? x1 : y1;
+    const T* Ub = s == 0 ? Ux : Uy;
+    T a[JM / 4], b[JM / 4], out[4];
+#pragma unroll
+    for (int st = 0; st < JM / 4; ++st) {
+      const int l = 4 * st + lk;
+      const int gc = (st < JM / 8 ? c0 : c1) * JB + (l & (JB - 1));
+      a[st] = gr < k && gc < k ? G[gr + (int64_t)gc * ldg] : from_real<T>(0.0);
+      b[st] = Ub[l + l16 * JM];
+    }
+    quad_mma(a, b, out);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      Ts[(s * JM + rh * JB + l16) * THLD + lk + 4 * q] = out[q];
+  }
+  __syncthreads();
+  if (w < 3) {
+    const T* Ua = w < 2 ? Ux : Uy;
+    T a[JM / 4], b[JM / 4], out[4];
+#pragma unroll
+    for (int st = 0; st < JM / 4; ++st) {
+      const int l = 4 * st + lk;
+      a[st] = conj_(Ua[l + l16 * JM]);
+      b[st] = Ts[(w * JM + l) * THLD + l16];
+    }
+    quad_mma(a, b, out);
+    const int r0 = w < 2 ? 0 : JB, c0 = w < 1 ? 0 : JB;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int r = r0 + l16, c = c0 + lk + 4 * q;
+      S[c * JLD + r] = out[q];
+      if (w == 1) S[r * JLD + c] = conj_(out[q]);
+    }
+  }
+  __syncthreads();
+  // the diagonal blocks Hermitian to the last bit, as the stored tiles are
+  for (int e = threadIdx.x; e < 2 * JB * JB; e += JPT) {
+    const int d = e / (JB * JB) * JB, r = d + e % JB, c = d + e % (JB * JB) / JB;
+    if (r < c) {
+      const T v = (S[c * JLD + r] + conj_(S[r * JLD + c])) * 0.5;
+      S[c * JLD + r] = v;
+      S[r * JLD + c] = conj_(v);
+    } else if (r == c) {
+      S[c * JLD + r] = from_real<T>(real_(S[c * JLD + r]));
+    }
+  }
+}
+
 // Pair of blocks `pair` of round `round`: load its 2JB x 2JB subproblem,
 // run one cyclic Jacobi sweep over its indices (round-robin over 2JB
 // players: JB disjoint rotations per inner round, applied together), and
@@ -111,17 +264,18 @@ __device__ __forceinline__ int jac_rotation(double app, double aqq, T apq, doubl
 // Bound by the chain of the 2JB - 1 dependent inner rounds: one workgroup per
 // pair, a few dozen on the chip.  In an inner round 16 threads compute the
 // rotations and publish them; then waves 0 - 3 update S, one 2 x 2 block a
-// thread, beside waves 4 - 7, which update U.  A launch takes 25 us at k = 140
-// and 33 us at k = 260 (complex; 35 and 42 with S and U updated in turn by the
-// same four waves and a tangent-form rotation).  Slower: every thread
-// computing its own rotations (28; 33 with both overlapped), which saves the
-// exchange but repeats the square roots in all waves.  Rotating only across
-// the two blocks after a sweep's first round halves the inner rounds (21 us)
-// but takes 38% more sweeps.
+// thread, beside waves 4 - 7, which update U: the inner rounds are 20 of a
+// launch's 27 us at k = 140 (complex; 10 us more with S and U updated in turn
+// by the same four waves and a tangent-form rotation).  Slower: every thread
+// computing its own rotations (3 us), which saves the exchange but repeats
+// the square roots in all waves; reading what a round updates before its
+// rotations are known (4 us), which holds up the rotations' own reads.
+// Rotating only across the two blocks after a sweep's first round halves the
+// inner rounds but takes 38% more sweeps.
 template <class T>
 __device__ void pair_body(const T* __restrict__ G, int64_t ldg, int k, int nb, int round,
                           int pair, double thr, T* __restrict__ ubuf, int* __restrict__ flags,
-                          T* S, T* U) {
+                          const T* __restrict__ uprev, T* S, T* U, T* Ts) {
   __shared__ double rcs[JB], rsn[JB];
   __shared__ T rph[JB];
   __shared__ int rrot[JB];
@@ -133,11 +287,14 @@ __device__ void pair_body(const T* __restrict__ G, int64_t ldg, int k, int nb, i
   for (int e = tid; e < JM * JM; e += JPT) {
     const int r = e % JM, c = e / JM;
     const int gr = gidx(r), gc = gidx(c);
-    T v = from_real<T>(0.0);
-    if (gr < k && gc < k) v = G[gr + (int64_t)gc * ldg];
-    S[c * JLD + r] = v;
+    if (round == 0) {
+      T v = from_real<T>(0.0);
+      if (gr < k && gc < k) v = G[gr + (int64_t)gc * ldg];
+      S[c * JLD + r] = v;
+    }
     U[c * JLD + r] = from_real<T>(r == c ? 1.0 : 0.0);
   }
+  if (round > 0) pair_load<T>(G, ldg, k, nb, round - 1, bp, bq, uprev, S, Ts);
   __syncthreads();
   const int half = tid / JT, t = tid % JT;
   const int j = t / JB, i = t % JB;
@@ -208,80 +365,44 @@ __device__ void pair_body(const T* __restrict__ G, int64_t ldg, int k, int nb, i
   // the rounding of the rotations leaves U unitary only to a few ulps per
   // inner round, and applying a non-unitary J^H G J shifts the eigenvalues by
   // that much in every round; the step brings it back to rounding level.
-  // M = U^H U goes into S (no longer needed).
-  const int row = tid % JM, cg = tid / JM;
-  constexpr int PCG = JPT / JM, PM = JM / PCG;  // columns per thread
+  // M = U^H U goes into S (no longer needed).  Both products on the matrix
+  // cores, a quadrant in each of four waves: with every thread summing its
+  // entries from LDS they took 5 us of a launch.
   if (any) {
+    const int lane = tid & 63, w = tid >> 6, l16 = lane & 15, lk = lane >> 4;
+    const int i0 = JB * (w & 1), c0 = JB * (w >> 1);
+    T a[JM / 4], b[JM / 4], out[4];
+    if (w < 4) {
 #pragma unroll
-    for (int m = 0; m < PM; ++m) {
-      const int c = cg + PCG * m;
-      T acc = from_real<T>(0.0);
-#pragma unroll 4
-      for (int l = 0; l < JM; ++l) mac(acc, conj_(U[row * JLD + l]), U[c * JLD + l]);
-      S[c * JLD + row] = acc;
+      for (int st = 0; st < JM / 4; ++st) {
+        a[st] = conj_(U[(i0 + l16) * JLD + 4 * st + lk]);
+        b[st] = U[(c0 + l16) * JLD + 4 * st + lk];
+      }
+      quad_mma(a, b, out);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) S[(c0 + lk + 4 * q) * JLD + i0 + l16] = out[q];
     }
     __syncthreads();
-    T nu[PM];
+    if (w < 4) {
 #pragma unroll
-    for (int m = 0; m < PM; ++m) {
-      const int c = cg + PCG * m;
-      T acc = from_real<T>(0.0);
-#pragma unroll 4
-      for (int l = 0; l < JM; ++l) mac(acc, U[l * JLD + row], S[c * JLD + l]);
-      nu[m] = U[c * JLD + row] * 1.5 - acc * 0.5;
+      for (int st = 0; st < JM / 4; ++st) {
+        a[st] = U[(4 * st + lk) * JLD + i0 + l16];
+        b[st] = S[(c0 + l16) * JLD + 4 * st + lk];
+      }
+      quad_mma(a, b, out);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        out[q] = U[(c0 + lk + 4 * q) * JLD + i0 + l16] * 1.5 - out[q] * 0.5;
     }
     __syncthreads();
+    if (w < 4)
 #pragma unroll
-    for (int m = 0; m < PM; ++m) U[(cg + PCG * m) * JLD + row] = nu[m];
+      for (int q = 0; q < 4; ++q) U[(c0 + lk + 4 * q) * JLD + i0 + l16] = out[q];
     __syncthreads();
   }
   T* Uo = ubuf + (int64_t)pair * JM * JM;
   for (int e = tid; e < JM * JM; e += JPT) Uo[e] = U[(e / JM) * JLD + (e % JM)];
   if (tid == 0) flags[pair] = any;
-}
-
-typedef double d4v __attribute__((ext_vector_type(4)));
-
-// Y = A B for JM x JM tiles in LDS on the FP64 matrix cores (16x16x4 MFMA),
-// A(i, l) at As[l * JLD + i] and B(l, c) at Bs[l * JLD + c].  Wave w of the
-// four computes the quadrant of rows 16 (w & 1) and columns 16 (w >> 1).
-// The operands go in swapped (B first), so the instruction produces the
-// quadrant transposed: lane L holds Y(16 (w & 1) + L % 16, 16 (w >> 1) +
-// L / 16 + 4 r) in out[r] (rows run along the lanes, as stores want them).
-__device__ __forceinline__ void tile_mma(const double* As, const double* Bs, double (&out)[4]) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int i0 = 16 * (w & 1), c0 = 16 * (w >> 1), l16 = lane & 15, lk = lane >> 4;
-  d4v acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int k0 = 0; k0 < JM; k0 += 4) {
-    const double a = As[(k0 + lk) * JLD + i0 + l16];
-    const double b = Bs[(k0 + lk) * JLD + c0 + l16];
-    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(b, a, acc, 0, 0, 0);
-  }
-#pragma unroll
-  for (int r = 0; r < 4; ++r) out[r] = acc[r];
-}
-__device__ __forceinline__ void tile_mma(const cd* As, const cd* Bs, cd (&out)[4]) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int i0 = 16 * (w & 1), c0 = 16 * (w >> 1), l16 = lane & 15, lk = lane >> 4;
-  d4v re = {0.0, 0.0, 0.0, 0.0}, im = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int k0 = 0; k0 < JM; k0 += 4) {
-    const cd a = As[(k0 + lk) * JLD + i0 + l16];
-    const cd b = Bs[(k0 + lk) * JLD + c0 + l16];
-    re = __builtin_amdgcn_mfma_f64_16x16x4f64(b.x, a.x, re, 0, 0, 0);
-    re = __builtin_amdgcn_mfma_f64_16x16x4f64(-b.y, a.y, re, 0, 0, 0);
-    im = __builtin_amdgcn_mfma_f64_16x16x4f64(b.y, a.x, im, 0, 0, 0);
-    im = __builtin_amdgcn_mfma_f64_16x16x4f64(b.x, a.y, im, 0, 0, 0);
-  }
-#pragma unroll
-  for (int r = 0; r < 4; ++r) out[r] = cd{re[r], im[r]};
-}
-
-// Position of out[r] of tile_mma in this thread: row, column.
-__device__ __forceinline__ int mma_row() { return 16 * ((threadIdx.x >> 6) & 1) + (threadIdx.x & 15); }
-__device__ __forceinline__ int mma_col(int r) {
-  return 16 * (threadIdx.x >> 7) + ((threadIdx.x & 63) >> 4) + 4 * r;
 }
 
 // JM rows of V (row chunk `chunk`) times the columns of pair b of round
@@ -316,106 +437,107 @@ __device__ void vtile_body(T* __restrict__ V, int64_t ldv, int k, int nb, int ro
   }
 }
 
-// First launch of a round: workgroups [0, npairs) solve the pairs of round
-// `round` into the buffers (ubuf, flags); the next ones apply the previous
-// round's unitaries (ubuf_v, flags_v, round_v) to the eigenvector block.
-// The two halves touch disjoint memory (G is only read, V only by the
-// second), so they run side by side.
+// Tile of the updated matrix at (pair a rows, pair b columns), a <= b, of
+// round `round`: U_a^H X U_b, and its mirror (b, a) the conjugate transpose
+// (a == b: the Hermitian part); copied where neither pair rotated.  All
+// threads of the workgroup move data, four waves multiply.
 template <class T>
-__global__ __launch_bounds__(JPT) void jac_stage1_k(const T* __restrict__ G, int64_t ldg,
-                                                   T* __restrict__ V, int64_t ldv, int k, int nb,
-                                                   int round, int npairs, double thr,
-                                                   T* __restrict__ ubuf, int* __restrict__ flags,
-                                                   int round_v, const T* __restrict__ ubuf_v,
-                                                   const int* __restrict__ flags_v) {
-  __shared__ T sm0[JM * JLD];
-  __shared__ T sm1[JM * JLD];
-  const int w = blockIdx.x;
-  if (w < npairs) {
-    pair_body<T>(G, ldg, k, nb, round, w, thr, ubuf, flags, sm0, sm1);
-  } else {
-    const int P = nb / 2, t = w - npairs;
-    vtile_body<T>(V, ldv, k, nb, round_v, t % P, t / P, ubuf_v, flags_v, sm0, sm1);
-  }
-}
-
-// Second launch of a round: the tile of G at (pair a rows, pair b columns),
-// a <= b, becomes U_a^H X U_b and its mirror (b, a) the conjugate transpose
-// (a == b: the Hermitian part); tiles whose two pairs did not rotate are
-// left as they are.
-template <class T>
-__global__ __launch_bounds__(JT) void jac_stage2_k(T* __restrict__ G, int64_t ldg, int k, int nb,
-                                                   int round, const T* __restrict__ ubuf,
-                                                   const int* __restrict__ flags) {
-  __shared__ T Xs[JM * JLD];  // X(i, l) at Xs[l * JLD + i]; later the result Y
-  __shared__ T Bs[JM * JLD];  // U_b (B(l, c) at Bs[l * JLD + c]), then A = U_a^H
-  __shared__ T Ts[JM * JLD];  // X U_b, T(l, c) at Ts[l * JLD + c]
+__device__ void gtile_body(const T* __restrict__ G, int64_t ldg, T* __restrict__ D, int64_t ldd,
+                           int k, int nb, int round, int t, const T* __restrict__ ubuf,
+                           const int* __restrict__ flags, T* Xs, T* Bs, T* Ts) {
+  // Xs: X(i, l) at Xs[l * JLD + i], later the result Y; Bs: U_b (B(l, c) at
+  // Bs[l * JLD + c]), then A = U_a^H; Ts: X U_b, T(l, c) at Ts[l * JLD + c]
   const int tid = threadIdx.x;
-  const int i = tid % JM, cg = tid / JM;
-  const int t = blockIdx.x;
   int b = (int)((sqrt(8.0 * (double)t + 1.0) - 1.0) * 0.5);
   if ((b + 1) * (b + 2) / 2 <= t) ++b;
   if (b * (b + 1) / 2 > t) --b;
   const int a = t - b * (b + 1) / 2;
   const int fa = flags[a], fb = flags[b];
-  if (!fa && !fb) return;
   const int a0 = rr_player(nb, round, a), a1 = rr_player(nb, round, nb - 1 - a);
   const int b0 = rr_player(nb, round, b), b1 = rr_player(nb, round, nb - 1 - b);
   auto ga = [&](int l) { return l < JB ? a0 * JB + l : a1 * JB + (l - JB); };
   auto gb = [&](int l) { return l < JB ? b0 * JB + l : b1 * JB + (l - JB); };
   const T* Ua = ubuf + (int64_t)a * JM * JM;
   const T* Ub = ubuf + (int64_t)b * JM * JM;
-  for (int e = tid; e < JM * JM; e += JT) {
+  const bool rot = fa || fb;
+  for (int e = tid; e < JM * JM; e += JPT) {
     const int r = e % JM, c = e / JM;
     const int gr = ga(r), gc = gb(c);
     T v = from_real<T>(0.0);
     if (gr < k && gc < k) v = G[gr + (int64_t)gc * ldg];
     Xs[c * JLD + r] = v;
-    Bs[r * JLD + c] = fb ? Ub[e] : from_real<T>(r == c ? 1.0 : 0.0);
+    if (rot) Bs[r * JLD + c] = fb ? Ub[e] : from_real<T>(r == c ? 1.0 : 0.0);
   }
   __syncthreads();
-  T out[4];
-  tile_mma(Xs, Bs, out);  // T = X U_b, stored as T(l, c) at Ts[l * JLD + c]
+  if (rot) {
+    T out[4];
+    if (tid < JT) {
+      tile_mma(Xs, Bs, out);  // T = X U_b
 #pragma unroll
-  for (int r = 0; r < 4; ++r) Ts[mma_row() * JLD + mma_col(r)] = out[r];
-  __syncthreads();
-  // A(c, r) = conj(U_a(r, c)) at Bs[r * JLD + c]
-  for (int e = tid; e < JM * JM; e += JT) {
-    const int r = e % JM, c = e / JM;
-    Bs[r * JLD + c] = fa ? conj_(Ua[e]) : from_real<T>(r == c ? 1.0 : 0.0);
+      for (int r = 0; r < 4; ++r) Ts[mma_row() * JLD + mma_col(r)] = out[r];
+    }
+    __syncthreads();
+    // A(c, r) = conj(U_a(r, c)) at Bs[r * JLD + c]
+    for (int e = tid; e < JM * JM; e += JPT) {
+      const int r = e % JM, c = e / JM;
+      Bs[r * JLD + c] = fa ? conj_(Ua[e]) : from_real<T>(r == c ? 1.0 : 0.0);
+    }
+    __syncthreads();
+    if (tid < JT) {
+      tile_mma(Bs, Ts, out);  // Y = U_a^H T, stored as Y(i, c) at Xs[c * JLD + i]
+#pragma unroll
+      for (int r = 0; r < 4; ++r) Xs[mma_col(r) * JLD + mma_row()] = out[r];
+    }
+    __syncthreads();
   }
-  __syncthreads();
-  tile_mma(Bs, Ts, out);  // Y = U_a^H T, stored as Y(i, c) at Xs[c * JLD + i]
+  const int i = tid % JM, gi = ga(i), gm = gb(i);
 #pragma unroll
-  for (int r = 0; r < 4; ++r) Xs[mma_col(r) * JLD + mma_row()] = out[r];
-  __syncthreads();
-  if (a == b) {
-    const int gi = ga(i);
-#pragma unroll
-    for (int m = 0; m < JM / JCG; ++m) {
-      const int c = cg + JCG * m;
-      const int gc = ga(c);
+  for (int c = tid / JM; c < JM; c += JPT / JM) {
+    const int gc = gb(c), gt = ga(c);
+    if (a == b) {
       T v = (Xs[c * JLD + i] + conj_(Xs[i * JLD + c])) * 0.5;
       if (i == c) v = from_real<T>(real_(v));
-      if (gi < k && gc < k) G[gi + (int64_t)gc * ldg] = v;
+      if (gi < k && gc < k) D[gi + (int64_t)gc * ldd] = v;
+    } else {
+      if (gi < k && gc < k) D[gi + (int64_t)gc * ldd] = Xs[c * JLD + i];
+      // mirror: lanes run over the rows of the (b, a) tile
+      if (gm < k && gt < k) D[gm + (int64_t)gt * ldd] = conj_(Xs[i * JLD + c]);
     }
+  }
+}
+
+// One round of a sweep, one launch.  Workgroups [0, npairs) solve the pairs
+// of round `round` into (ubuf, flags), each forming its own subproblem from
+// the matrix G before round - 1 and that round's unitaries (uprev, fprev);
+// beside them the next `gtiles` apply those unitaries to the whole matrix, G
+// -> D, and the rest to the eigenvector block.  Nothing a workgroup writes
+// is read in the same launch.
+//
+// A launch of pairs and eigenvectors followed by one of the matrix in place
+// leaves the second's time and a launch gap on the chain of the rounds: 32.4
+// + gap against 27.5 us a round at k = 140, 42 against 36 at k = 260 (complex;
+// 33 and 41 before the Newton-Schulz step moved to the matrix cores).  A
+// dense matrix, complex: k = 140 3.17 -> 2.76 ms, 256 5.9 -> 5.15, 700 21.9 ->
+// 19.3; the copied tiles and the 60 KB of LDS cost less than the launch at
+// every order measured, to 1300.
+template <class T>
+__global__ __launch_bounds__(JPT) void jac_round_k(
+    const T* __restrict__ G, int64_t ldg, T* __restrict__ D, int64_t ldd, T* __restrict__ V,
+    int64_t ldv, int k, int nb, int round, int npairs, int gtiles, double thr,
+    T* __restrict__ ubuf, int* __restrict__ flags, const T* __restrict__ uprev,
+    const int* __restrict__ fprev) {
+  __shared__ T sm0[JM * JLD];
+  __shared__ T sm1[JM * JLD];
+  __shared__ T sm2[3 * JM * THLD];
+  static_assert(3 * JM * THLD >= JM * JLD, "tile of gtile_body");
+  const int w = blockIdx.x;
+  if (w < npairs) {
+    pair_body<T>(G, ldg, k, nb, round, w, thr, ubuf, flags, uprev, sm0, sm1, sm2);
+  } else if (w < npairs + gtiles) {
+    gtile_body<T>(G, ldg, D, ldd, k, nb, round - 1, w - npairs, uprev, fprev, sm0, sm1, sm2);
   } else {
-    const int gi = ga(i);
-#pragma unroll
-    for (int m = 0; m < JM / JCG; ++m) {
-      const int c = cg + JCG * m;
-      const int gc = gb(c);
-      if (gi < k && gc < k) G[gi + (int64_t)gc * ldg] = Xs[c * JLD + i];
-    }
-    // mirror: lanes run over the rows of the (b, a) tile
-    const int cr = tid % JM, ig = tid / JM;
-    const int gcr = gb(cr);
-#pragma unroll
-    for (int m = 0; m < JM / JCG; ++m) {
-      const int ii = ig + JCG * m;
-      const int gii = ga(ii);
-      if (gcr < k && gii < k) G[gcr + (int64_t)gii * ldg] = conj_(Xs[cr * JLD + ii]);
-    }
+    const int P = nb / 2, t = w - npairs - gtiles;
+    vtile_body<T>(V, ldv, k, nb, round - 1, t % P, t / P, uprev, fprev, sm0, sm1);
   }
 }
 
@@ -494,7 +616,7 @@ inline int jac_blocks(int k) {
 // Workspace layout for orders up to kmax (byte offsets): the pairs'
 // unitaries, their rotation flags, the norm partials, the diagonal.
 struct JacLayout {
-  size_t ubuf[2], flags[2], part, diag, total;
+  size_t ubuf[2], flags[2], part, diag, gbuf, total;
   JacLayout(bool cplx, int kmax) {
     const int P = jac_blocks(std::max(kmax, 1)) / 2;
     const size_t esz = cplx ? 16 : 8;
@@ -506,7 +628,8 @@ struct JacLayout {
     flags[1] = 2 * ub + fl;
     part = 2 * ub + 2 * fl;
     diag = part + 2 * NPART * 8;
-    total = diag + (size_t)std::max(kmax, 1) * 8;
+    gbuf = (diag + (size_t)std::max(kmax, 1) * 8 + 255) / 256 * 256;
+    total = gbuf + (size_t)std::max(kmax, 1) * std::max(kmax, 1) * esz;
   }
 };
 
@@ -538,7 +661,9 @@ struct JacobiRunner {
                      reinterpret_cast<int*>(base + lay.flags[1])};
     const int tiles_g = P * (P + 1) / 2;
     const int tiles_v = ((k + JM - 1) / JM) * P;
-    T* Gt = static_cast<T*>(G);
+    // the matrix and its other buffer, exchanged by every round's update
+    T *Gt = static_cast<T*>(G), *Do = reinterpret_cast<T*>(base + lay.gbuf);
+    int64_t ldt = ldg, ldo = k;
     T* Vt = static_cast<T*>(V);
     hipLaunchKernelGGL(jac_eye_k<T>, dim3(std::min<int64_t>(1024, ((int64_t)k * k + 255) / 256)),
                        dim3(256), 0, st, Vt, ldv, k);
@@ -550,27 +675,27 @@ struct JacobiRunner {
       if (sweeps >= max_sweeps)
         throw Error(CHASE_ERR_NUMERIC, "Jacobi eigensolver did not converge in " +
                                            std::to_string(max_sweeps) + " sweeps");
-      // round r: pairs of r with the eigenvector update of r - 1, then G;
-      // the last round's eigenvector update closes the sweep
+      // round r: its pairs, with the matrix and eigenvector updates of r - 1;
+      // the last round's updates close the sweep
       for (int r = 0; r <= nb - 1; ++r) {
-        const bool pairs = r < nb - 1, vupd = r > 0;
-        const int cur = r & 1, prev = (r + 1) & 1;
-        hipLaunchKernelGGL(jac_stage1_k<T>, dim3((pairs ? P : 0) + (vupd ? tiles_v : 0)),
-                           dim3(JPT), 0, st, static_cast<const T*>(Gt), ldg, Vt, ldv, k, nb, r,
-                           pairs ? P : 0, thr, ubuf[cur], flags[cur], r - 1,
-                           static_cast<const T*>(ubuf[prev]),
+        const int np = r < nb - 1 ? P : 0, cur = r & 1, prev = (r + 1) & 1;
+        const int ng = r > 0 ? tiles_g : 0, nv = r > 0 ? tiles_v : 0;
+        hipLaunchKernelGGL(jac_round_k<T>, dim3(np + ng + nv), dim3(JPT), 0, st,
+                           static_cast<const T*>(Gt), ldt, Do, ldo, Vt, ldv, k, nb, r, np, ng,
+                           thr, ubuf[cur], flags[cur], static_cast<const T*>(ubuf[prev]),
                            static_cast<const int*>(flags[prev]));
-        if (pairs)
-          hipLaunchKernelGGL(jac_stage2_k<T>, dim3(tiles_g), dim3(JT), 0, st, Gt, ldg, k, nb, r,
-                             static_cast<const T*>(ubuf[cur]),
-                             static_cast<const int*>(flags[cur]));
+        if (r > 0) {
+          std::swap(Gt, Do);
+          std::swap(ldt, ldo);
+        }
       }
       CHASE_HIP(hipGetLastError());
       ++sweeps;
       double d2;
-      norms(G, ldg, k, pinned, &off2, &d2, st);
+      norms(Gt, ldt, k, pinned, &off2, &d2, st);
       if (!std::isfinite(off2)) throw Error(CHASE_ERR_NUMERIC, "non-finite entries in Jacobi");
     }
+    diag_real(sizeof(T) == 16, Gt, ldt, k, reinterpret_cast<double*>(base + lay.diag), st);
     return sweeps;
   }
 };
@@ -607,7 +732,6 @@ int jacobi_heev(bool cplx, void* G, int64_t ldg, int k, void* V, int64_t ldv, vo
                                        dia2, st);
   // eigenvalues: the diagonal, ascending (stable), eigenvectors gathered to match
   double* d_diag = reinterpret_cast<double*>(static_cast<char*>(ws) + lay.diag);
-  diag_real(cplx, G, ldg, k, d_diag, st);
   hipLaunchKernelGGL(jac_sort_k, dim3((unsigned)((k + JT - 1) / JT)), dim3(JT), 0, st, d_diag, k,
                      d_evals, d_perm);
   CHASE_HIP(hipGetLastError());

@@ -1,0 +1,60 @@
+"""Edges of the k x k kernels: the Jacobi rounds at block counts where pairs,
+padding and the eigenvector tiles change, its sort on repeated eigenvalues,
+and the Cholesky QR on both sides of the order (512) up to which one launch
+inverts the factor.
+
+Tolerances.  Jacobi stops at an off-diagonal norm of 1e-14 |G|_F (|G|_F <= 10
+here: 1e-13) and rounds by a few u |G|_F in each of at most 200 rounds (2e-13):
+1e-12 on residual and orthonormality, per column.  QR: k u times a small
+constant per entry of Q^H Q: 1e-13 sqrt(k) in the Frobenius norm, and 1e-11
+on the projector onto the block's span (condition 10 k)."""
+import numpy as np
+import pytest
+
+import gen
+from gpu_util import announce, to_gpu, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def pk():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2205_02491_amd as pk
+    pk.lib()
+    return pk
+
+
+@pytest.mark.parametrize("cplx", [True, False])
+@pytest.mark.parametrize("k", [1, 2, 16, 31, 33, 48, 49, 64, 65, 97])
+def test_jacobi_rounds_and_repeated_eigenvalues(pk, cplx, k):
+    announce(f"Jacobi rounds k={k} cplx={cplx}")
+    g = np.random.Generator(np.random.PCG64(53 * k + cplx))
+    q = np.linalg.qr(gen.gaussian(g, (k, k), cplx))[0]
+    lam = np.repeat(np.linspace(-1.0, 1.0, (k + 2) // 3), 3)[:k]  # triples
+    a = (q * lam) @ q.conj().T
+    for m in ((a + a.conj().T) / 2, np.diag(lam[::-1]).astype(q.dtype), np.zeros_like(q)):
+        w, v, _ = pk.chase_heev(to_gpu(m), pk.EIG_JACOBI)
+        v = to_np(v)
+        assert np.all(np.diff(w) >= 0)
+        assert np.max(np.abs(w - np.linalg.eigvalsh(m))) < 1e-12
+        assert np.max(np.linalg.norm(m @ v - v * w, axis=0)) < 1e-12
+        assert np.max(np.linalg.norm(v.conj().T @ v - np.eye(k), axis=0)) < 1e-12
+
+
+@pytest.mark.parametrize("cplx", [True, False])
+@pytest.mark.parametrize("n,k,locked", [(40, 1, 0), (70, 31, 0), (70, 32, 5), (90, 33, 0),
+                                        (300, 256, 0), (300, 257, 40), (700, 511, 0),
+                                        (700, 512, 0), (700, 513, 0), (700, 600, 90)])
+def test_qr_inverse_orders(pk, cplx, n, k, locked):
+    announce(f"QR n={n} k={k} locked={locked} cplx={cplx}")
+    g = np.random.Generator(np.random.PCG64(59 * n + k))
+    x = gen.gaussian(g, (n, k), cplx) * np.logspace(0, 1, k)
+    if locked:
+        x[:, :locked] = np.linalg.qr(x[:, :locked])[0]
+    ref = np.linalg.qr(x)[0]
+    q = to_np(pk.chase_qr(to_gpu(x), locked))
+    assert np.array_equal(q[:, :locked], x[:, :locked])
+    assert np.linalg.norm(q.conj().T @ q - np.eye(k)) < 1e-13 * max(1.0, np.sqrt(k))
+    assert np.linalg.norm(q - ref @ (ref.conj().T @ q)) < 1e-11
