@@ -74,6 +74,29 @@ __device__ inline void rr_place(int m, int r, int x, int& pair, int& half) {
   pair = half ? m - 1 - j : j;
 }
 
+// Value of the next and of the previous lane of the 16-lane DPP row (the row's
+// last and first lane: 0).
+__device__ __forceinline__ double from_lane_above(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x101, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x101, 0xf, 0xf, false);
+  return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double from_lane_below(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x111, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x111, 0xf, 0xf, false);
+  return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ cd from_lane_above(cd v) {
+  return {from_lane_above(v.x), from_lane_above(v.y)};
+}
+__device__ __forceinline__ cd from_lane_below(cd v) {
+  return {from_lane_below(v.x), from_lane_below(v.y)};
+}
+__device__ __forceinline__ double pick(bool c, double a, double b) { return c ? a : b; }
+__device__ __forceinline__ cd pick(bool c, cd a, cd b) {
+  return {c ? a.x : b.x, c ? a.y : b.y};
+}
+
 // Player of an inner round (m = JM, 0 <= r < JM - 1) without a division.
 __device__ __forceinline__ int inner_player(int r, int j) {
   const int p = j - 1 + r;
@@ -263,15 +286,19 @@ __device__ void pair_load(const T* __restrict__ G, int64_t ldg, int k, int nb, i
 //
 // Bound by the chain of the 2JB - 1 dependent inner rounds: one workgroup per
 // pair, a few dozen on the chip.  In an inner round 16 threads compute the
-// rotations and publish them; then waves 0 - 3 update S, one 2 x 2 block a
-// thread, beside waves 4 - 7, which update U: the inner rounds are 20 of a
-// launch's 27 us at k = 140 (complex; 10 us more with S and U updated in turn
-// by the same four waves and a tangent-form rotation).  Slower: every thread
-// computing its own rotations (3 us), which saves the exchange but repeats
-// the square roots in all waves; reading what a round updates before its
-// rotations are known (4 us), which holds up the rotations' own reads.
-// Rotating only across the two blocks after a sweep's first round halves the
-// inner rounds but takes 38% more sweeps.
+// rotations and publish them; then waves 0 - 3 update S in LDS, one 2 x 2
+// block a thread, beside waves 4 - 7, which keep U in registers: a lane holds
+// the two columns of its position in the tournament, and the columns move on
+// by one lane after a round (U in LDS: 5% more at k = 260, its reads and
+// writes hold up those of S).  The inner rounds are 20 of a launch's 27 us at
+// k = 140 (complex; 10 us more with S and U updated in turn by the same four
+// waves and a tangent-form rotation).  Slower: every thread computing its own
+// rotations (3 us), which saves the exchange but repeats the square roots in
+// all waves; reading the blocks of S before the rotations are known, by the
+// same wave (4 us) or with the rotations in another (2 us): either way those
+// reads come before the rotations' own.  Rotating only across the two blocks
+// after a sweep's first round halves the inner rounds but takes 38% more
+// sweeps.
 template <class T>
 __device__ void pair_body(const T* __restrict__ G, int64_t ldg, int k, int nb, int round,
                           int pair, double thr, T* __restrict__ ubuf, int* __restrict__ flags,
@@ -292,12 +319,19 @@ __device__ void pair_body(const T* __restrict__ G, int64_t ldg, int k, int nb, i
       if (gr < k && gc < k) v = G[gr + (int64_t)gc * ldg];
       S[c * JLD + r] = v;
     }
-    U[c * JLD + r] = from_real<T>(r == c ? 1.0 : 0.0);
   }
   if (round > 0) pair_load<T>(G, ldg, k, nb, round - 1, bp, bq, uprev, S, Ts);
   __syncthreads();
   const int half = tid / JT, t = tid % JT;
-  const int j = t / JB, i = t % JB;
+  // S: pairs i (rows) and j (columns), consecutive lanes along the rows; U:
+  // pair j's columns, in the lanes of a DPP row, at rows i and i + JB
+  const int j = half ? t % JB : t / JB, i = half ? t / JB : t % JB;
+  T ut[2], ub[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    ut[h] = from_real<T>(j == i + h * JB ? 1.0 : 0.0);
+    ub[h] = from_real<T>(JM - 1 - j == i + h * JB ? 1.0 : 0.0);
+  }
   for (int rr = 0; rr < JM - 1; ++rr) {
     if (tid < JB) {
       const int a = inner_player(rr, tid), b = inner_player(rr, JM - 1 - tid);
@@ -349,18 +383,34 @@ __device__ void pair_body(const T* __restrict__ G, int64_t ldg, int k, int nb, i
         S[aj * JLD + bi] = n10;
         S[bj * JLD + bi] = n11;
       } else {
-        // U <- U u on the columns of pair j, rows i and i + JB
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-          const int rho = i + h * JB;
-          const T u0 = U[aj * JLD + rho], u1 = U[bj * JLD + rho] * pjc;
-          U[aj * JLD + rho] = u0 * cj - u1 * sj;
-          U[bj * JLD + rho] = u0 * sj + u1 * cj;
+          const T u0 = ut[h], u1 = ub[h] * pjc;
+          ut[h] = u0 * cj - u1 * sj;
+          ub[h] = u0 * sj + u1 * cj;
         }
+      }
+    }
+    if (half == 1) {
+      // the players move on by one position: the first halves down, the
+      // second up, position 0 stays
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const T nt = from_lane_above(ut[h]), nb_ = from_lane_below(ub[h]);
+        const T t0 = ut[h], b0 = ub[h];
+        ut[h] = pick(j == 0, t0, pick(j == JB - 1, b0, nt));
+        ub[h] = pick(j == 0, nt, nb_);
       }
     }
     __syncthreads();
   }
+  if (half == 1)  // 2 JB - 1 moves: every player is back
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      U[j * JLD + i + h * JB] = ut[h];
+      U[(JM - 1 - j) * JLD + i + h * JB] = ub[h];
+    }
+  __syncthreads();
   // One Newton-Schulz step towards the nearest unitary, U <- U (3 I - U^H U) / 2:
   // the rounding of the rotations leaves U unitary only to a few ulps per
   // inner round, and applying a non-unitary J^H G J shifts the eigenvalues by
@@ -515,10 +565,10 @@ __device__ void gtile_body(const T* __restrict__ G, int64_t ldg, T* __restrict__
 //
 // A launch of pairs and eigenvectors followed by one of the matrix in place
 // leaves the second's time and a launch gap on the chain of the rounds: 32.4
-// + gap against 27.5 us a round at k = 140, 42 against 36 at k = 260 (complex;
+// + gap against 27.3 us a round at k = 140, 42 against 34 at k = 260 (complex;
 // 33 and 41 before the Newton-Schulz step moved to the matrix cores).  A
-// dense matrix, complex: k = 140 3.17 -> 2.76 ms, 256 5.9 -> 5.15, 700 21.9 ->
-// 19.3; the copied tiles and the 60 KB of LDS cost less than the launch at
+// dense matrix, complex: k = 140 3.17 -> 2.66 ms, 256 5.9 -> 4.93, 700 21.9 ->
+// 18.6; the copied tiles and the 60 KB of LDS cost less than the launch at
 // every order measured, to 1300.
 template <class T>
 __global__ __launch_bounds__(JPT) void jac_round_k(
