@@ -181,9 +181,6 @@ void scale_cols(bool cplx, void* V, int64_t ldv, int64_t n, int64_t k, const dou
 // Y[:, j] = (a ? a[j] : 1) X[:, j] + (b ? b[j] : 0) Y[:, j]   (a, b on the device)
 void axpby_cols(bool cplx, const double* a, const void* X, int64_t ldx, const double* b, void* Y,
                 int64_t ldy, int64_t n, int64_t k, hipStream_t st);
-// Y += a * X for n x k blocks
-void axpy_cols(bool cplx, double a, const void* X, int64_t ldx, void* Y, int64_t ldy, int64_t n,
-               int64_t k, hipStream_t st);
 // Hermitian part in place: A = (A + A^H)/2 (n x n)
 void herm_part(bool cplx, void* A, int64_t lda, int64_t n, hipStream_t st);
 // c128 -> c64 (or double -> float) conversion of an n x n matrix into ld n

@@ -186,18 +186,6 @@ __global__ void axpby_cols_k(const double* __restrict__ a, const double* __restr
   }
 }
 
-template <int W>
-__global__ void axpy_cols_k(double a, const double* __restrict__ X, int64_t ldx,
-                            double* __restrict__ Y, int64_t ldy, int64_t n, int64_t k) {
-  for (int64_t j = blockIdx.y; j < k; j += gridDim.y) {
-    const double* x = X + j * ldx * W;
-    double* y = Y + j * ldy * W;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n * W;
-         i += (int64_t)gridDim.x * blockDim.x)
-      y[i] += a * x[i];
-  }
-}
-
 // A = (A + A^H)/2, each unordered pair handled once (i <= j)
 template <bool CPLX>
 __global__ void herm_part_k(double* __restrict__ A, int64_t lda, int64_t n) {
@@ -818,19 +806,6 @@ void axpby_cols(bool cplx, const double* a, const void* X, int64_t ldx, const do
   else
     hipLaunchKernelGGL(axpby_cols_k<1>, grid, dim3(TPB), 0, st, a, static_cast<const double*>(X),
                        ldx, b, static_cast<double*>(Y), ldy, n, k);
-  CHASE_HIP(hipGetLastError());
-}
-
-void axpy_cols(bool cplx, double a, const void* X, int64_t ldx, void* Y, int64_t ldy, int64_t n,
-               int64_t k, hipStream_t st) {
-  if (n <= 0 || k <= 0) return;
-  dim3 grid(blocks_for(n * (cplx ? 2 : 1), TPB * 4, 64), (unsigned)(k < 65535 ? k : 65535));
-  if (cplx)
-    hipLaunchKernelGGL(axpy_cols_k<2>, grid, dim3(TPB), 0, st, a, static_cast<const double*>(X),
-                       ldx, static_cast<double*>(Y), ldy, n, k);
-  else
-    hipLaunchKernelGGL(axpy_cols_k<1>, grid, dim3(TPB), 0, st, a, static_cast<const double*>(X),
-                       ldx, static_cast<double*>(Y), ldy, n, k);
   CHASE_HIP(hipGetLastError());
 }
 
