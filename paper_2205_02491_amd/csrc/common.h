@@ -99,6 +99,14 @@ struct GemmArgs {
   // below row tri_row0 + j, so a column tile's K loop stops there.
   int tri;
   int64_t tri_row0;
+  // STORE with B's conjugate transpose, optional (K2 > 0): a second product
+  // of K2 terms in the same pass, C = alpha (A B^H + ratio2 A2 B2^H) + beta C
+  const void* A2;
+  int64_t lda2;
+  const void* B2;
+  int64_t ldb2;
+  int64_t K2;
+  double ratio2;
 };
 
 // ------------------------------------------------------------------ split BF16

@@ -248,9 +248,16 @@ __global__ __launch_bounds__(64 * WM * WN * WK, OCC) void gemm_kernel(GemmArgs g
   const int wm = wmn / WN, wn = wmn - wm * WN;
   const int l16 = lane & 15, lk = lane >> 4;
 
+  // two products in one pass: each of the two waves of a tile takes one of
+  // them whole instead of half of the only one
+  constexpr bool PAIR = EPI == EPI_STORE && OPB == OP_C && WK == 2;
+  const bool pair = PAIR && g.K2 > 0, second = pair && wk == 1;
+  if (second) kend = g.K2;
+
   using TAe = typename El<TA, CPLX>::type;
-  const TAe* __restrict__ A = static_cast<const TAe*>(g.A);
-  const T* __restrict__ B = static_cast<const T*>(g.B);
+  const TAe* __restrict__ A = static_cast<const TAe*>(second ? g.A2 : g.A);
+  const T* __restrict__ B = static_cast<const T*>(second ? g.B2 : g.B);
+  const int64_t lda = second ? g.lda2 : g.lda, ldb = second ? g.ldb2 : g.ldb;
 
   using FA = Frag<TA, CPLX, OPA == OP_C, FM>;
   using FB = Frag<double, CPLX, OPB == OP_N, FN>;
@@ -266,27 +273,30 @@ __global__ __launch_bounds__(64 * WM * WN * WK, OCC) void gemm_kernel(GemmArgs g
     const int64_t un = stages >> 1;  // whole units
     nfull = 2 * (un / WK + (wk < (int)(un % WK) ? 1 : 0));
     if ((stages & 1) && (int)(un % WK) == wk) nfull += 1;
+    if (pair) nfull = stages;
   }
   const int krem = (int)(klen % KS);
   // the partial stage belongs to the wave whose turn it is
-  const bool has_rem = krem != 0 && (int)((stages >> 1) % WK) == wk;
+  const bool has_rem = krem != 0 && (pair || (int)((stages >> 1) % WK) == wk);
 
   const int64_t mw = m0 + wm * FM * 16, nw = n0 + wn * FN * 16;  // this wave's part of C
   typename FA::Ptr pa;
   typename FB::Ptr pb;
-  FA::init(pa, A, g.lda, mw, M, kbeg + 2 * KS * (int64_t)wk, l16, lk);
-  FB::init(pb, B, g.ldb, nw, N, kbeg + 2 * KS * (int64_t)wk, l16, lk);
+  const int64_t kfirst = pair ? 0 : kbeg + 2 * KS * (int64_t)wk;
+  FA::init(pa, A, lda, mw, M, kfirst, l16, lk);
+  FB::init(pb, B, ldb, nw, N, kfirst, l16, lk);
   // pointer advance after the first / second stage of a unit
-  constexpr int64_t adv0 = KS, adv1 = (2 * WK - 1) * KS;
-  const int64_t a0 = OPA == OP_N ? adv0 * g.lda : adv0, a1 = OPA == OP_N ? adv1 * g.lda : adv1;
-  const int64_t b0 = OPB == OP_N ? adv0 : adv0 * g.ldb, b1 = OPB == OP_N ? adv1 : adv1 * g.ldb;
+  constexpr int64_t adv0 = KS;
+  const int64_t adv1 = pair ? KS : (2 * WK - 1) * KS;
+  const int64_t a0 = OPA == OP_N ? adv0 * lda : adv0, a1 = OPA == OP_N ? adv1 * lda : adv1;
+  const int64_t b0 = OPB == OP_N ? adv0 : adv0 * ldb, b1 = OPB == OP_N ? adv1 : adv1 * ldb;
 
   typename FA::V fa[S][FA::NV];
   typename FB::V fb[S][FB::NV];
   static_assert(S % 2 == 0, "the pipeline covers whole units");
   auto load = [&](int s) {
-    FA::load(fa[s], pa, g.lda, (s & 1) ? a1 : a0);
-    FB::load(fb[s], pb, g.ldb, (s & 1) ? b1 : b0);
+    FA::load(fa[s], pa, lda, (s & 1) ? a1 : a0);
+    FB::load(fb[s], pb, ldb, (s & 1) ? b1 : b0);
   };
 
   acc_t acc_re[FM][FN], acc_im[CPLX ? FM : 1][CPLX ? FN : 1], acc_s[GAUSS ? FM : 1][GAUSS ? FN : 1];
@@ -389,8 +399,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK, OCC) void gemm_kernel(GemmArgs g
     if (has_rem) {
       typename FA::V a[FA::NV];
       typename FB::V b[FB::NV];
-      FA::load_part(a, pa, g.lda, lk, krem);
-      FB::load_part(b, pb, g.ldb, lk, krem);
+      FA::load_part(a, pa, lda, lk, krem);
+      FB::load_part(b, pb, ldb, lk, krem);
       compute(a, b);
     }
   }
@@ -403,6 +413,17 @@ __global__ __launch_bounds__(64 * WM * WN * WK, OCC) void gemm_kernel(GemmArgs g
         const acc_t p1 = acc_re[fm][fn], p2 = acc_im[fm][fn];
         acc_re[fm][fn] = p1 - p2;
         acc_im[fm][fn] = acc_s[fm][fn] - p1 - p2;
+      }
+  }
+
+  if constexpr (PAIR) {
+    const double f = second ? g.ratio2 : 1.0;
+#pragma unroll
+    for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+      for (int fn = 0; fn < FN; ++fn) {
+        acc_re[fm][fn] *= f;
+        if constexpr (CPLX) acc_im[fm][fn] *= f;
       }
   }
 
@@ -642,6 +663,15 @@ inline int waves_of(const GemmArgs& g) {
   return g.K <= 192 ? 2 : 4;
 }
 
+// Two rank-k updates of one matrix in one pass (K2 > 0): on the two-wave
+// tile, a wave each, where that tile fills the chip; the matrix is read and
+// written once instead of twice.  The real update takes it only where its
+// single ones run on the same tile.
+inline bool rank_pair(bool cplx, const GemmArgs& g) {
+  if (g.M < 2 || g.N < 2 || tiles_of(g.M, g.N, 32, 32) < 4 * NCU) return false;
+  return cplx || std::max(g.K, g.K2) <= 192;
+}
+
 // Complex, four-product form.  Rates: 20000 x 1300 x 1300.
 template <int OPA, int OPB, int EPI>
 void four_f64(const GemmArgs& g, hipStream_t st) {
@@ -808,6 +838,28 @@ void gemm(bool cplx, Prec prec, Op opa, Op opb, Epi epi, const GemmArgs& g, hipS
     CHASE_REQUIRE(opa == OP_N && opb == OP_N && epi == EPI_CHEB,
                   "split-BF16 products exist only for the filter step");
     return gemm_bf16x3(cplx, g, st, prec == PREC_BF16X2 ? 2 : 3);
+  }
+  if (g.K2 > 0) {
+    CHASE_REQUIRE(prec == PREC_F64 && opa == OP_N && opb == OP_C && epi == EPI_STORE,
+                  "two products in one pass: rank-k updates only");
+    if (rank_pair(cplx, g)) {
+      if (cplx)
+        launch<double, double, true, OP_N, OP_C, EPI_STORE, false, 2, 2, 2, 3>(g, st);
+      else
+        launch<double, double, false, OP_N, OP_C, EPI_STORE, false, 2, 2, 2, 4>(g, st);
+      return;
+    }
+    GemmArgs g1 = g, g2 = g;
+    g1.K2 = g2.K2 = 0;
+    g2.A = g.A2;
+    g2.lda = g.lda2;
+    g2.B = g.B2;
+    g2.ldb = g.ldb2;
+    g2.K = g.K2;
+    g2.alpha = g.alpha * g.ratio2;
+    g2.beta = 1.0;
+    gemm(cplx, prec, opa, opb, epi, g1, st);
+    return gemm(cplx, prec, opa, opb, epi, g2, st);
   }
   if (cplx)
     dispatch<true>(prec, opa, opb, epi, g, st);

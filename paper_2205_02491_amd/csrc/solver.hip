@@ -1745,25 +1745,26 @@ chase_status chase_eigvec_adjoint(chase_handle_t h, const void* H, int64_t ldh, 
       g.beta = 1.0;
       gemm(cplx, PREC_F64, OP_N, OP_N, EPI_STORE, g, st);
     }
-    // dH += (X V^H + V X^H) / 2
+    // Within the block: V E V^H, E = Hermitian part of M_ij / (lambda_j - lambda_i).
+    // E is Hermitian, so with X + V E for X the outer part's products give it too:
+    // dH += ((X + V E) V^H + V (X + V E)^H) / 2
+    sym_divdiff(cplx, h->G, ne, lam, m, h->R, ne, st);
+    {
+      GemmArgs g = gargs(n, m, m, V, ldv, h->R, ne, X, n);
+      g.beta = 1.0;
+      gemm(cplx, PREC_F64, OP_N, OP_N, EPI_STORE, g, st);
+    }
     {
       GemmArgs g = gargs(n, n, m, X, n, V, ldv, dH, ldd);
       g.alpha = 0.5;
       g.beta = 1.0;
+      g.A2 = V;
+      g.lda2 = ldv;
+      g.B2 = X;
+      g.ldb2 = n;
+      g.K2 = m;
+      g.ratio2 = 1.0;
       gemm(cplx, PREC_F64, OP_N, OP_C, EPI_STORE, g, st);
-      GemmArgs g2 = gargs(n, n, m, V, ldv, X, n, dH, ldd);
-      g2.alpha = 0.5;
-      g2.beta = 1.0;
-      gemm(cplx, PREC_F64, OP_N, OP_C, EPI_STORE, g2, st);
-    }
-    // Within the block: dH += V E V^H, E = Hermitian part of M_ij / (lambda_j - lambda_i)
-    sym_divdiff(cplx, h->G, ne, lam, m, h->R, ne, st);
-    {
-      GemmArgs g = gargs(n, m, m, V, ldv, h->R, ne, Q, n);  // Q = V E
-      gemm(cplx, PREC_F64, OP_N, OP_N, EPI_STORE, g, st);
-      GemmArgs g2 = gargs(n, n, m, Q, n, V, ldv, dH, ldd);  // dH += Q V^H
-      g2.beta = 1.0;
-      gemm(cplx, PREC_F64, OP_N, OP_C, EPI_STORE, g2, st);
     }
     CHASE_HIP(hipStreamSynchronize(st));
   });
@@ -1808,12 +1809,19 @@ chase_status chase_filter_adjoint(chase_handle_t h, const void* H, int64_t ldh, 
       if (cols <= 0) continue;
       const Coef c = cf[s - 1];
       void* g1 = off(G1, (int64_t)a0 * n, h->esz);
-      // dH += a_s Gb_s X_{s-1}^H  (X_{s-1} from tape slot s-1)
-      {
-        GemmArgs g = gargs(n, n, cols, g1, n, off(h->tape, ((int64_t)(s - 1) * k + a0) * n, h->esz),
-                           n, dH, ldd);
+      // dH += a_s Gb_s X_{s-1}^H  (X_{s-1} from tape slot s-1), two steps at a
+      // time (degrees are even): Gb_{s+1} is there until this step writes over it
+      const void* xs = off(h->tape, ((int64_t)(s - 1) * k + a0) * n, h->esz);
+      if ((mmax - s) % 2 == 1) {
+        const int b0 = first_col(s + 1);
+        GemmArgs g = gargs(n, n, cols, g1, n, xs, n, dH, ldd);
         g.alpha = c.alpha;
         g.beta = 1.0;
+        g.A2 = off(G0, (int64_t)b0 * n, h->esz);
+        g.B2 = off(h->tape, ((int64_t)s * k + b0) * n, h->esz);
+        g.lda2 = g.ldb2 = n;
+        g.K2 = k - b0;
+        g.ratio2 = cf[s].alpha / c.alpha;
         gemm(h->cplx, PREC_F64, OP_N, OP_C, EPI_STORE, g, st);
       }
       {

@@ -12,6 +12,7 @@ import numpy as np
 import pytest
 
 import gen
+import oracle
 from gpu_util import announce, to_gpu, to_np
 
 pytestmark = pytest.mark.gpu
@@ -63,10 +64,12 @@ def test_qr_inverse_orders(pk, cplx, n, k, locked):
 @pytest.mark.parametrize("cplx", [True, False])
 @pytest.mark.parametrize("n,deg", [(2, (2,)), (31, (2, 2, 4, 8)), (32, (6,) * 5),
                                    (33, (2, 4, 4, 10, 12)), (65, (4,) * 3 + (6,) * 30),
-                                   (130, (2, 14))])
+                                   (130, (2, 14)), (993, (2,) * 3 + (4,) * 30),
+                                   (1025, (2, 4, 6, 6, 8)), (1060, (2,) * 180 + (4,) * 20)])
 def test_filter_adjoint_edges(pk, cplx, n, deg):
-    """Reverse sweep with columns that join it at different steps, and the
-    Hermitian part at tile edges (32), against automatic differentiation of
+    """Reverse sweep with columns that join it at different steps, the rank-k
+    updates of two steps in one pass (from order 993; the real one up to 192
+    columns) and the Hermitian part at tile edges (32), against automatic differentiation of
     the recurrence on the CPU.  Both sides round n u per product and amplify
     by less than 4 s per step (s <= 14): 1e-11 of the largest entry."""
     import torch
@@ -105,3 +108,26 @@ def test_filter_adjoint_edges(pk, cplx, n, deg):
         assert np.max(np.abs(to_np(got) - ref)) <= 1e-11 * np.max(np.abs(ref))
     dh = to_np(h.grad)
     assert np.array_equal(dh, dh.conj().T)
+
+
+@pytest.mark.parametrize("cplx", [True, False])
+@pytest.mark.parametrize("n,m", [(40, 3), (1000, 1), (1000, 33), (1031, 195)])
+def test_eigvec_adjoint_rank_updates(pk, cplx, n, m):
+    """Eigenvector adjoint, whose two rank-m updates run in one pass from
+    order 993 (the real one up to 192 columns), against the oracle's
+    first-order perturbation.  Conjugate gradients to 1e-12 across a gap of
+    0.3, divided differences of rounding (1e-13) over gaps of 1 / (5 m) >=
+    1e-3: 1e-8 of the norm."""
+    import torch
+    announce(f"eigvec adjoint rank updates n={n} m={m} cplx={cplx}")
+    g = np.random.Generator(np.random.PCG64(67 * n + m))
+    q = np.linalg.qr(gen.gaussian(g, (n, n), cplx))[0]
+    lam = np.concatenate([-1.0 + 0.25 * (np.arange(m) + g.uniform(0.0, 0.2, m)) / m,
+                          np.linspace(-0.45, 1.0, n - m)])
+    h = (q * lam) @ q.conj().T
+    h = (h + h.conj().T) / 2
+    v, gv = q[:, :m].copy(), gen.gaussian(g, (n, m), cplx)
+    ref = oracle.eigvec_adjoint(h, v, lam[:m], gv)
+    dh = torch.zeros((n, n), dtype=to_gpu(h).dtype, device="cuda")
+    pk.chase_eigvec_adjoint(to_gpu(h), to_gpu(v), lam[:m], to_gpu(gv), dh, tol=1e-12)
+    assert np.linalg.norm(to_np(dh) - ref) <= 1e-8 * np.linalg.norm(ref)
