@@ -153,14 +153,14 @@ void rb_check(rocblas_status s, const char* what) {
     throw Error(CHASE_ERR_HIP, std::string(what) + " failed: " + rocblas_status_to_string(s));
 }
 
-size_t splitk_ws_elems(bool cplx, int ne) {
+size_t splitk_ws_elems(bool cplx, int64_t n, int ne) {
   size_t mx = 0;
   for (int k = 1; k <= ne; ++k) {
     int s;
     int64_t ks;
-    // K is at least ne (the library's projections have K = n >= ne); the
-    // Hermitian products computed as triangles have the most slices
-    splitk_plan(cplx, k, k, INT64_MAX / 4, &s, &ks, true);
+    // the library's projections have K = n; the Hermitian products computed
+    // as triangles have the most slices
+    splitk_plan(cplx, k, k, n, &s, &ks, true);
     mx = std::max(mx, (size_t)s * k * k);
   }
   return mx;
@@ -179,7 +179,7 @@ Sizes sizes(chase_dtype dt, int64_t n, int nev, int nex, const chase_opts& o) {
   const size_t esz = cplx ? 16 : 8;
   const int64_t ne = nev + nex;
   s.blocks = 3 * (size_t)n * ne * esz + 2 * (size_t)ne * ne * esz;
-  s.ws = splitk_ws_elems(cplx, (int)ne) * esz;
+  s.ws = splitk_ws_elems(cplx, n, (int)ne) * esz;
   s.small = (size_t)ne * 8 * 5 + (size_t)gemm_row_tiles(n) * ne * 8 + 64 + (size_t)ne * 4 +
             (size_t)ne * esz;
   s.lz = lanczos_bytes(cplx, n, o.lanczos_vecs, o.lanczos_steps, &s.lz_splits);
@@ -1311,7 +1311,7 @@ chase_status chase_create(chase_handle_t* out, chase_dtype dtype, int64_t n, int
     h->Z = dev_alloc(h, (size_t)n * ne * h->esz);
     h->G = dev_alloc(h, (size_t)ne * ne * h->esz);
     h->R = dev_alloc(h, (size_t)ne * ne * h->esz);
-    h->ws_elems = splitk_ws_elems(h->cplx, (int)ne);
+    h->ws_elems = splitk_ws_elems(h->cplx, n, (int)ne);
     h->ws = dev_alloc(h, h->ws_elems * h->esz);
     h->d_scale = static_cast<double*>(dev_alloc(h, ne * 8));
     h->d_evals = static_cast<double*>(dev_alloc(h, ne * 8));
