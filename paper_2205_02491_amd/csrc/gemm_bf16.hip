@@ -220,16 +220,17 @@ struct TailPlan {
 };
 
 // Waves of a TBM x TBN tile: FI x FJ fragments of 32 x 32 each, at most
-// eight waves; few enough fragments per wave that the four SIMDs hold equal
-// shares where the tile divides that way.
+// eight waves, so that two can share a SIMD; shares as equal as the tile's
+// division allows (128 x 96: six waves of two fragments, not four of three).
 template <int TBM, int TBN>
 struct Layout {
-  static constexpr int FI = TBM == 256 && TBN == 128 ? 2 : TBM == 192 && TBN == 128 ? 3 : 1;
-  static constexpr int FJ = TBM == 64    ? 1
-                            : TBM == 192 && TBN == 128 ? 1
-                            : TBN == 96  ? 3
-                            : TBM == 128 && TBN == 64 ? 1
-                                         : 2;
+  static constexpr int FI = TBM == 192 && TBN == 128 ? 3
+                            : (TBM == 256 && TBN == 128) || (TBM == 128 && TBN == 96) ? 2
+                                                                                      : 1;
+  static constexpr int FJ = TBM == 64 || (TBM == 192 && TBN == 128) || (TBM == 128 && TBN < 128)
+                                ? 1
+                            : TBN == 96 ? 3
+                                        : 2;
   static constexpr int WGI = TBM / (32 * FI);  // waves along the rows of C
   static constexpr int WGJ = TBN / (32 * FJ);  // and along its columns
   static constexpr int NTHR = 64 * WGI * WGJ;
