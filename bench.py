@@ -54,12 +54,12 @@ PREC_CODE = {"fp64": 0, "fp32": 1, "bf16x3": 2, "bf16x2": 3, "fp64i8": 0, "bf16x
 EIG_CODE = {"auto": 0, "library": 1, "jacobi": 2}
 EIG_CHOICE = "auto"
 KERNEL_NAME = {
-    "fp64": "gemm_kernel<double,double,complex,N,N,CHEB,8,Gauss,128x64> (FP64 MFMA 16x16x4)",
-    "fp32": "gemm_kernel<float,float,complex,N,N,CHEB,16,Gauss,128x64> (FP32 MFMA 16x16x4)",
+    "fp64": "gemm_kernel<double,double,complex,N,N,CHEB,Gauss,96x32> (FP64 MFMA 16x16x4)",
+    "fp32": "gemm_kernel<float,float,complex,N,N,CHEB,Gauss> (FP32 MFMA 16x16x4)",
     "bf16x3": "gemm_bf16x3_kernel<complex, 3 terms> (BF16 MFMA 32x32x16, 256x128 tiles)",
     "bf16x2": "gemm_bf16x3_kernel<complex, 2 terms; start pass 3 terms> (BF16 MFMA 32x32x16, "
               "256x128 tiles)",
-    "fp64i8": "FP64 step on INT8: 42 rocBLAS INT8 GEMMs (14 moduli x 3 Gauss products) + "
+    "fp64i8": "FP64 step on INT8: 42 INT8 GEMMs (14 moduli x 3 Gauss products) + "
               "crt_cheb_k (Garner reconstruction, Chebyshev epilogue); executed = INT8 ops",
     "bf16x2i8": "gemm_bf16x3_kernel<complex, 2 terms; start pass 3 terms> (BF16 MFMA 32x32x16); "
                 "FP64 steps and Rayleigh-Ritz H Q on INT8 (14 moduli)",
