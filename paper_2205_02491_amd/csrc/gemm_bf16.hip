@@ -58,9 +58,10 @@
 // is therefore held to one order: MFMA shape, k ascending, and the K slices
 // of a plan made for 256 x 128 tiles.  The tile itself does not enter, so it
 // is chosen freely: 64 to 256 rows by 64 to 128 columns, the same bytes.
-// What bounds a workgroup is filling its LDS (76 KB per 32-deep chunk at 256
-// x 96, about 14 B per clock and CU of the 12-20 the L2 gives): fewer bytes
-// per workgroup on more CUs.  Measured, two-term pass of 24 steps, complex:
+// A large tile on part of the chip leaves the rest of its matrix cores idle: 8000
+// x 260 on 192 x 96 tiles (252 workgroups, 321 us a step) runs 0.93 PFLOP/s of
+// MFMA work with its padding, where the vendor's GEMM of a large product runs
+// 1.12 on this power-limited card.  Measured, two-term pass of 24 steps, complex:
 // 8000 x 260 7.4 -> 6.3 ms (192 x 96: 252 workgroups where 256 x 128 made
 // 192), 2111 x 90 1.19 -> 0.64 ms (128 x 96), 900 x 60 1.07 -> 0.39 ms and
 // 513 x 8 0.99 -> 0.35 ms (64 x 64; a chunk is 24 KB instead of 80).
