@@ -724,13 +724,15 @@ void gemm_bf16x3(bool cplx, const GemmArgs& g, hipStream_t st, int terms) {
   // The plan above fixes every element's K slices and with them its bytes;
   // the tile may still shrink.  Columns: the narrowest width that covers the
   // block with as many column tiles (260 columns: 3 x 96 instead of 3 x 128,
-  // 346 -> 282 us per step at n = 8000).  Rows, where all tiles have the same
-  // slices (all in the tail, or none): the fewest with which every workgroup
-  // still has a CU of its own (a second round would cost what the smaller
-  // tile saves) and the last tile stays inside the operand's padding, which
-  // is to 256 rows.  The 16-deep two-term kernel is for comparison only and
-  // keeps the largest tile.
-  const int tbn = !k32 && terms == 2 ? TBN_MAX
+  // 346 -> 282 us per step at n = 8000), unless the tail begins inside a row
+  // of tiles: a narrower tile would move columns across its beginning (three
+  // column tiles and more than 256 in all: n above 21760).  Rows, where all
+  // tiles have the same slices (all in the tail, or none): the fewest with
+  // which every workgroup still has a CU of its own (a second round would cost
+  // what the smaller tile saves) and the last tile stays inside the operand's
+  // padding, which is to 256 rows.  The 16-deep two-term kernel is for
+  // comparison only and keeps the largest tile.
+  const int tbn = (!k32 && terms == 2) || tp.tile0 % tiles_n != 0 ? TBN_MAX
                   : tiles_n * 64 >= g.N ? 64
                   : tiles_n * 96 >= g.N ? 96
                                         : TBN_MAX;
