@@ -291,6 +291,29 @@ __global__ __launch_bounds__(64 * WM * WN * WK, OCC) void gemm_kernel(GemmArgs g
   const int64_t a0 = OPA == OP_N ? adv0 * lda : adv0, a1 = OPA == OP_N ? adv1 * lda : adv1;
   const int64_t b0 = OPB == OP_N ? adv0 : adv0 * ldb, b1 = OPB == OP_N ? adv1 : adv1 * ldb;
 
+  // The partial tiles are finished a column fragment at a time: ENT entries,
+  // dealt to the threads.  The real rank-k updates, short in K and bound by C,
+  // read their entries of C before the K loop: read where they are used, behind
+  // the bounds of each entry, they came one memory latency after another (order
+  // 20000, rank 1: 1.94 -> 1.36 ms, 4.7 TB/s).
+  constexpr int ROWS = TBM, COLS = WN * 16, ENT = ROWS * COLS;
+  constexpr bool AHEAD = EPI == EPI_STORE && OPB == OP_C && !CPLX && WK == 2 && FM * FN == 4;
+  double* __restrict__ Cd = static_cast<double*>(g.C);
+  T yc[AHEAD ? FN : 1][AHEAD ? ENT / NTHR : 1];
+  if constexpr (AHEAD) {
+    static_assert(ENT % NTHR == 0, "whole rounds of the threads");
+    if (g.beta != 0.0)
+#pragma unroll
+      for (int fn = 0; fn < FN; ++fn)
+#pragma unroll
+        for (int u = 0; u < ENT / NTHR; ++u) {
+          const int e = threadIdx.x + u * NTHR, c = e / ROWS;
+          const int64_t i = m0 + e % ROWS < M ? m0 + e % ROWS : M - 1;
+          const int64_t j = FB::index(n0 + (c / 16) * FN * 16, fn, c & 15, N);
+          yc[fn][u] = reinterpret_cast<const T*>(Cd)[i + j * g.ldc];
+        }
+  }
+
   typename FA::V fa[S][FA::NV];
   typename FB::V fb[S][FB::NV];
   static_assert(S % 2 == 0, "the pipeline covers whole units");
@@ -430,8 +453,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, OCC) void gemm_kernel(GemmArgs g
   // ---------------------------------------------------------------- epilogue
   // register r of fragment (fm, fn) holds C's row FA::index(mw, fm, l16) and
   // column FB::index(nw, fn, lk + 4 r)
-  double* __restrict__ Cd = static_cast<double*>(g.C);
-  auto finish = [&](int64_t i, int64_t j, double vr, double vi, double& colsum) {
+  auto finish = [&](int64_t i, int64_t j, double vr, double vi, double& colsum, const T* yc) {
     if constexpr (EPI == EPI_RESID) {
       const double lam = g.lambda[j];
       const T v = static_cast<const T*>(g.V)[i + j * g.ldv];
@@ -462,7 +484,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, OCC) void gemm_kernel(GemmArgs g
         vi *= g.alpha;
       }
       if (g.beta != 0.0) {
-        const T y = reinterpret_cast<const T*>(Cd)[o];
+        const T y = yc ? *yc : reinterpret_cast<const T*>(Cd)[o];
         vr += g.beta * re_(y);
         vi += g.beta * im_(y);
       }
@@ -484,7 +506,6 @@ __global__ __launch_bounds__(64 * WM * WN * WK, OCC) void gemm_kernel(GemmArgs g
   if constexpr (WK > 1) {
     // The WK partial tiles meet in LDS, one column fragment at a time; then
     // every thread of the workgroup finishes its share of the entries.
-    constexpr int ROWS = TBM, COLS = WN * 16, ENT = ROWS * COLS;
     static_assert(EPI != EPI_RESID || (ROWS <= 64 && (ROWS & (ROWS - 1)) == 0),
                   "a column's rows are a lane group of one wave");
     __shared__ T part[WK][COLS][ROWS];
@@ -505,7 +526,10 @@ __global__ __launch_bounds__(64 * WM * WN * WK, OCC) void gemm_kernel(GemmArgs g
         }
       }
       __syncthreads();
-      for (int e = threadIdx.x; e < ENT; e += NTHR) {
+#pragma unroll
+      for (int u = 0; u < (ENT + NTHR - 1) / NTHR; ++u) {
+        const int e = threadIdx.x + u * NTHR;
+        if (ENT % NTHR != 0 && e >= ENT) break;
         const int i = e % ROWS, c = e / ROWS;
         const int64_t nc = n0 + (c / 16) * FN * 16;
         const int64_t j = FB::index(nc, fn, c & 15, N);
@@ -518,7 +542,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, OCC) void gemm_kernel(GemmArgs g
             vr += re_(v);
             vi += im_(v);
           }
-          finish(m0 + i, j, vr, vi, cs);
+          finish(m0 + i, j, vr, vi, cs, AHEAD ? &yc[fn][u] : nullptr);
         }
         if constexpr (EPI == EPI_RESID) {
 #pragma unroll
@@ -549,7 +573,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, OCC) void gemm_kernel(GemmArgs g
           double vi = 0.0;
           if constexpr (CPLX) vi = (double)acc_im[fm][fn][r];
           finish(FA::index(mw, fm, l16, M), FB::index(nw, fn, frag_col<TC>(lk, r), N),
-                 (double)acc_re[fm][fn][r], vi, colsum[fn][r]);
+                 (double)acc_re[fm][fn][r], vi, colsum[fn][r], nullptr);
         }
     }
     if constexpr (EPI == EPI_RESID) {
@@ -652,6 +676,15 @@ void gauss_f64(const GemmArgs& g, hipStream_t st) {
   }
 }
 
+// Real rank-k updates on 64 x 32 tiles of two waves a K half (rank_tile): where
+// the 32 x 32 tiles would fill the chip and up to this rank.  Against the tiles
+// of the table below, us: order 2000 rank 400 60 / 70, 700 98 / 102; 3500: 173 /
+// 187, 291 / 283; 20000: 5355 / 5895, 8769 / 8883, but 7685 / 7199 at 512.
+constexpr int64_t kRankK = 448;
+inline bool rank_tile(const GemmArgs& g) {
+  return std::max(g.K, g.K2) <= kRankK && tiles_of(g.M, g.N, 32, 32) >= 4 * NCU;
+}
+
 // Waves per workgroup of the four-product and residual forms' 32 x 32 tiles:
 // 8 while the tiles do not fill the chip; with 1024 tiles or more (four 4-wave
 // workgroups a compute unit), fewer waves split K, so that more workgroups
@@ -670,7 +703,7 @@ inline int waves_of(const GemmArgs& g) {
 // its single ones run on the same tile.
 inline bool rank_pair(bool cplx, const GemmArgs& g) {
   if (g.M < 2 || g.N < 2 || tiles_of(g.M, g.N, 32, 32) < 4 * NCU) return false;
-  return cplx || std::max(g.K, g.K2) <= 192;
+  return cplx || rank_tile(g);
 }
 
 // Complex, four-product form.  Rates: 20000 x 1300 x 1300.
@@ -699,10 +732,16 @@ void real_f64(const GemmArgs& g, hipStream_t st) {
   // pairs of rows (or columns) are loaded together: at least two of them
   if (g.M < 2 || g.N < 2)
     return launch<double, double, false, OPA, OPB, EPI, false, 1, 1>(g, st);
-  // rank-k updates: short K, see waves_of (order 2000, rank 100: 33 us with
-  // 64 x 32 tiles and 4 waves, 28 with 32 x 32 and 2)
-  if (g.K <= 192 && waves_of(g) == 2)
-    return launch<double, double, false, OPA, OPB, EPI, false, 2, 2, 2, 4>(g, st);
+  // rank-k updates (order 2000, rank 100: 25 us; 28 on 32 x 32 tiles, 33 with
+  // 64 x 32 tiles and four waves that split K)
+  if constexpr (OPB == OP_C) {
+    if (rank_tile(g))
+      return launch<double, double, false, OPA, OPB, EPI, false, 2, 2, 2, 4, 2>(g, st);
+  } else {
+    // a long block times a small factor: short K, see waves_of
+    if (g.K <= 192 && waves_of(g) == 2)
+      return launch<double, double, false, OPA, OPB, EPI, false, 2, 2, 2, 4>(g, st);
+  }
   static constexpr Tile t[] = {{128, 64, 70}, {64, 64, 67}, {64, 32, 62}, {64, 16, 55},
                                {32, 32, 48},  {32, 16, 41}, {16, 16, 24}, {96, 32, 64}};
   switch (pick(t, g.M, g.N)) {
@@ -847,7 +886,7 @@ void gemm(bool cplx, Prec prec, Op opa, Op opb, Epi epi, const GemmArgs& g, hipS
       if (cplx)
         launch<double, double, true, OP_N, OP_C, EPI_STORE, false, 2, 2, 2, 3>(g, st);
       else
-        launch<double, double, false, OP_N, OP_C, EPI_STORE, false, 2, 2, 2, 4>(g, st);
+        launch<double, double, false, OP_N, OP_C, EPI_STORE, false, 2, 2, 2, 4, 2>(g, st);
       return;
     }
     GemmArgs g1 = g, g2 = g;
