@@ -47,7 +47,8 @@ enum Op { OP_N = 0, OP_C = 1 };
 //           Xs is the B operand itself, out may hold X_{s-2})
 //   SPLITK: partial sums of a K-slice to a workspace (reduced separately)
 //   RESID : partial column sums of |AB - lambda_j * V|^2 per row tile
-enum Epi { EPI_STORE = 0, EPI_CHEB = 1, EPI_SPLITK = 2, EPI_RESID = 3 };
+//   SHIFT : F = AB - lambda_j * V (RESID's block alone, on any tile)
+enum Epi { EPI_STORE = 0, EPI_CHEB = 1, EPI_SPLITK = 2, EPI_RESID = 3, EPI_SHIFT = 4 };
 
 // Arithmetic of the products: FP64 (double MFMA), FP32 (float MFMA,
 // operands rounded to float when staged in LDS, FP32 accumulation) or split
@@ -65,15 +66,16 @@ struct GemmArgs {
   void* C;  // output (STORE/CHEB: same element type as B; SPLITK: ws)
   int64_t ldc;
   double alpha, beta, gamma;
-  const double* lambda;  // RESID: per-column shift (device)
-  const void* V;         // RESID: matrix subtracted (ld ldv)
+  const double* lambda;  // RESID, SHIFT: per-column shift (device)
+  const void* V;         // RESID, SHIFT: matrix subtracted (ld ldv)
   int64_t ldv;
   double* partial;       // RESID: [row_tiles][N] partial sums
   int splits;            // SPLITK: number of K slices (grid z)
   int64_t kslice;        // SPLITK: K length per slice (multiple of the K tile)
   int a_f32;             // A stored as c64/float (mixed-precision copy of H)
   // CHEB: optional forcing term + colcoef[j] * F(i, j) (defect-correction
-  // form of the filter); RESID: optional store of the residual block to F
+  // form of the filter); RESID: optional store of the residual block to F;
+  // SHIFT: the output
   const double* colcoef;
   void* F;
   int64_t ldf;

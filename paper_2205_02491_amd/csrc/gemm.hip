@@ -5,7 +5,8 @@
 //     optionally + c_j F_j (the forcing term of the filter's defect form),
 //   - split-K partial sums for the tall-skinny Gram / projection products of
 //     the QR and Rayleigh-Ritz steps,
-//   - per-column residual norms ||H v - lambda v||^2 of the residual step.
+//   - per-column residual norms ||H v - lambda v||^2 of the residual step,
+//   - the shifted product H P - P diag(lambda) of the eigenvector adjoint.
 //
 // Operands go from memory straight into MFMA fragments: every wave owns FM x
 // FN fragments of 16 x 16 of C and loads its own operand fragments S stages
@@ -454,13 +455,13 @@ __global__ __launch_bounds__(64 * WM * WN * WK, OCC) void gemm_kernel(GemmArgs g
   // register r of fragment (fm, fn) holds C's row FA::index(mw, fm, l16) and
   // column FB::index(nw, fn, lk + 4 r)
   auto finish = [&](int64_t i, int64_t j, double vr, double vi, double& colsum, const T* yc) {
-    if constexpr (EPI == EPI_RESID) {
+    if constexpr (EPI == EPI_RESID || EPI == EPI_SHIFT) {
       const double lam = g.lambda[j];
       const T v = static_cast<const T*>(g.V)[i + j * g.ldv];
       vr -= lam * re_(v);
       if constexpr (CPLX) vi -= lam * im_(v);
-      colsum += vr * vr + vi * vi;
-      if (g.F) {
+      if constexpr (EPI == EPI_RESID) colsum += vr * vr + vi * vi;
+      if (EPI == EPI_SHIFT || g.F) {
         if constexpr (CPLX)
           static_cast<T*>(g.F)[i + j * g.ldf] = T{vr, vi};
         else
@@ -714,8 +715,10 @@ void four_f64(const GemmArgs& g, hipStream_t st) {
   const int p = pick(t, g.M, g.N);
   if (p == 1) return launch<double, double, true, OPA, OPB, EPI, false, 1, 1>(g, st);
   // the larger tile for long blocks times a factor only: the rank-k updates
-  // (OPB = C) are short and bound by C
-  if constexpr (OPB == OP_N) {
+  // (OPB = C) are short and bound by C, and the shifted products with H (SHIFT),
+  // long in K, gain nothing (eigenvector adjoint 12000 x 300: 178 ms with 32 x
+  // 32, 185 with 64 x 32; 8000 x 1500: 478 and 472)
+  if constexpr (OPB == OP_N && EPI != EPI_SHIFT) {
     if (p == 2) return launch<double, double, true, OPA, OPB, EPI, false, 4, 2, 4, 2>(g, st);
   }
   switch (waves_of(g)) {
@@ -817,6 +820,11 @@ void dispatch(Prec prec, Op opa, Op opb, Epi epi, const GemmArgs& g, hipStream_t
         if (waves_of(g) == 8)
           return launch<double, double, CPLX, OP_N, OP_N, EPI_RESID, false, 2, 2>(g, st);
         return launch<double, double, CPLX, OP_N, OP_N, EPI_RESID, false, 2, 2, 4, 4>(g, st);
+      case EPI_SHIFT:
+        if constexpr (CPLX)
+          return four_f64<OP_N, OP_N, EPI_SHIFT>(g, st);
+        else
+          return real_f64<OP_N, OP_N, EPI_SHIFT>(g, st);
       default: break;
     }
   } else if (opa == OP_C && opb == OP_N) {

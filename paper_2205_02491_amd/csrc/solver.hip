@@ -1709,10 +1709,9 @@ chase_status chase_eigvec_adjoint(chase_handle_t h, const void* H, int64_t ldh, 
         g.lambda = lam;
         g.V = P;
         g.ldv = n;
-        g.partial = h->d_partial;
         g.F = Q;
         g.ldf = n;
-        gemm(cplx, PREC_F64, OP_N, OP_N, EPI_RESID, g, st);
+        gemm(cplx, PREC_F64, OP_N, OP_N, EPI_SHIFT, g, st);
       }
       // Q -= V (V^H Q)
       gram(h, V, ldv, Q, n, n, m, m, h->R, ne, false, st);
