@@ -767,23 +767,37 @@ void real_f64(const GemmArgs& g, hipStream_t st) {
 // FP32 products of the filter step (A stored as TA, B in FP64).  Rates:
 // TFLOP/s (algorithmic) on the complex 20000 x 1300 step; 8000 x 260 takes 1.03
 // ms with 96 x 48 tiles, 1.08 with 64 x 32, 1.70 with 128 x 64.
-template <typename TA, bool CPLX>
-void cheb_f32(const GemmArgs& g, hipStream_t st) {
-  // pairs of rows are loaded together (real data): at least two of them
-  if (g.M < 2) return launch<TA, float, CPLX, OP_N, OP_N, EPI_CHEB, true, 1, 1>(g, st);
+template <typename TA>
+void cheb_f32_cplx(const GemmArgs& g, hipStream_t st) {
   static constexpr Tile t[] = {{128, 64, 150}, {64, 32, 146}, {32, 32, 96}, {32, 16, 81},
                                {16, 16, 47}, {96, 48, 146}};
   switch (pick(t, g.M, g.N)) {
-    case 0: return launch<TA, float, CPLX, OP_N, OP_N, EPI_CHEB, true, 4, 2, 2, 1, 2, 2>(g, st);
-    case 5:
-      // an odd number of row fragments: complex data only (no row pairs)
-      if constexpr (CPLX)
-        return launch<TA, float, CPLX, OP_N, OP_N, EPI_CHEB, true, 3, 3, 4, 1, 2>(g, st);
-      [[fallthrough]];
-    case 1: return launch<TA, float, CPLX, OP_N, OP_N, EPI_CHEB, true, 4, 2, 4, 2>(g, st);
-    case 2: return launch<TA, float, CPLX, OP_N, OP_N, EPI_CHEB, true, 2, 2>(g, st);
-    case 3: return launch<TA, float, CPLX, OP_N, OP_N, EPI_CHEB, true, 2, 1>(g, st);
-    default: return launch<TA, float, CPLX, OP_N, OP_N, EPI_CHEB, true, 1, 1>(g, st);
+    case 0: return launch<TA, float, true, OP_N, OP_N, EPI_CHEB, true, 4, 2, 2, 1, 2, 2>(g, st);
+    case 1: return launch<TA, float, true, OP_N, OP_N, EPI_CHEB, true, 4, 2, 4, 2>(g, st);
+    case 2: return launch<TA, float, true, OP_N, OP_N, EPI_CHEB, true, 2, 2>(g, st);
+    case 3: return launch<TA, float, true, OP_N, OP_N, EPI_CHEB, true, 2, 1>(g, st);
+    case 5: return launch<TA, float, true, OP_N, OP_N, EPI_CHEB, true, 3, 3, 4, 1, 2>(g, st);
+    default: return launch<TA, float, true, OP_N, OP_N, EPI_CHEB, true, 1, 1>(g, st);
+  }
+}
+
+// Real: a table of its own (96 x 48 has an odd number of row fragments, and the
+// rates are not in proportion).  Rates: TFLOP/s on steps of 4000 x 1000 to 20000
+// x 1300.  15000 x 2000 takes 9.1 ms with 128 x 128, 10.6 with 128 x 64, 10.8
+// with 64 x 32; 9000 x 1500 2.74, 2.88, 3.11.
+template <typename TA>
+void cheb_f32_real(const GemmArgs& g, hipStream_t st) {
+  // pairs of rows are loaded together: at least two of them
+  if (g.M < 2) return launch<TA, float, false, OP_N, OP_N, EPI_CHEB, false, 1, 1>(g, st);
+  static constexpr Tile t[] = {{128, 128, 97}, {128, 64, 88}, {64, 32, 80},
+                               {32, 32, 46},   {32, 16, 44},  {16, 16, 23}};
+  switch (pick(t, g.M, g.N)) {
+    case 0: return launch<TA, float, false, OP_N, OP_N, EPI_CHEB, false, 4, 4, 2, 1, 2, 2>(g, st);
+    case 1: return launch<TA, float, false, OP_N, OP_N, EPI_CHEB, false, 4, 2, 2, 1, 2, 2>(g, st);
+    case 2: return launch<TA, float, false, OP_N, OP_N, EPI_CHEB, false, 4, 2, 4, 2>(g, st);
+    case 3: return launch<TA, float, false, OP_N, OP_N, EPI_CHEB, false, 2, 2>(g, st);
+    case 4: return launch<TA, float, false, OP_N, OP_N, EPI_CHEB, false, 2, 1>(g, st);
+    default: return launch<TA, float, false, OP_N, OP_N, EPI_CHEB, false, 1, 1>(g, st);
   }
 }
 
@@ -794,7 +808,10 @@ void dispatch(Prec prec, Op opa, Op opb, Epi epi, const GemmArgs& g, hipStream_t
   if (prec == PREC_F32) {
     CHASE_REQUIRE(opa == OP_N && opb == OP_N && epi == EPI_CHEB,
                   "FP32 products exist only for the filter step");
-    return g.a_f32 ? cheb_f32<float, CPLX>(g, st) : cheb_f32<double, CPLX>(g, st);
+    if constexpr (CPLX)
+      return g.a_f32 ? cheb_f32_cplx<float>(g, st) : cheb_f32_cplx<double>(g, st);
+    else
+      return g.a_f32 ? cheb_f32_real<float>(g, st) : cheb_f32_real<double>(g, st);
   }
   if (opa == OP_N && opb == OP_N) {
     switch (epi) {
