@@ -633,18 +633,21 @@ struct Tile {
 inline int64_t tiles_of(int64_t M, int64_t N, int tm, int tn) {
   return ((M + tm - 1) / tm) * ((N + tn - 1) / tn);
 }
+inline double tile_cost(const Tile& t, int64_t M, int64_t N) {
+  return (double)((tiles_of(M, N, t.tm, t.tn) + NCU - 1) / NCU) * t.tm * t.tn / t.rate;
+}
 template <int N>
-int pick(const Tile (&t)[N], int64_t M, int64_t N_) {
+int pick(const Tile (&t)[N], int64_t M, int64_t N_, double* least = nullptr) {
   int best = 0;
   double cost = 0.0;
   for (int i = 0; i < N; ++i) {
-    const int64_t tiles = tiles_of(M, N_, t[i].tm, t[i].tn);
-    const double c = (double)((tiles + NCU - 1) / NCU) * t[i].tm * t[i].tn / t[i].rate;
+    const double c = tile_cost(t[i], M, N_);
     if (i == 0 || c < cost) {
       best = i;
       cost = c;
     }
   }
+  if (least) *least = cost;
   return best;
 }
 
@@ -764,14 +767,209 @@ void real_f64(const GemmArgs& g, hipStream_t st) {
   }
 }
 
-// FP32 products of the filter step (A stored as TA, B in FP64).  Rates:
-// TFLOP/s (algorithmic) on the complex 20000 x 1300 step; 8000 x 260 takes 1.03
-// ms with 96 x 48 tiles, 1.08 with 64 x 32, 1.70 with 128 x 64.
+// ------------------------------------------------------------------ staged FP32
+// FP32 filter step through LDS: 128 x 64 tiles, K chunks of 16 in two stages, 512
+// threads = 8 waves of 32 x 32 (4 x 2); the next chunk's loads are in flight
+// during a chunk's MFMAs, operands are rounded to FP32 on the way into LDS
+// (k-major, one element of padding a row against bank conflicts).  A thread's
+// loads run along the columns of A and B whatever their alignment, and each
+// element is read once per tile: where the direct kernel's fragment loads are
+// the bound (wide blocks, columns that do not begin on a cache line, H in
+// FP64), this one is faster (see cheb_f32).
+constexpr int STM = 128, STN = 64, SBK = 16, SNT = 512, SPAD = 1;
+
+template <typename TA, bool CPLX>
+__global__ __launch_bounds__(SNT) void staged_f32_kernel(GemmArgs g, int tiles_n, int ntiles) {
+  using TE = typename El<double, CPLX>::type;  // element of B and C
+  using TAe = typename El<TA, CPLX>::type;
+  using V = typename El<float, CPLX>::type;
+  constexpr int LA = STM * SBK / SNT, LB = STN * SBK / SNT;  // elements a thread loads
+  __shared__ V As[2][SBK][STM + SPAD];
+  __shared__ V Bs[2][SBK][STN + SPAD];
+  const int per_xcd = gridDim.x >> 3;
+  const int t = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (t >= ntiles) return;
+  const int tm = t / tiles_n, tn = t - tm * tiles_n;
+  const int64_t m0 = (int64_t)tm * STM, n0 = (int64_t)tn * STN, M = g.M, N = g.N, K = g.K;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave >> 1, wn = wave & 1, l16 = lane & 15, lk = lane >> 4;
+  const TAe* __restrict__ A = static_cast<const TAe*>(g.A);
+  const TE* __restrict__ B = static_cast<const TE*>(g.B);
+
+  TAe ra[LA];
+  TE rb[LB];
+  auto load = [&](int64_t k0) {
+#pragma unroll
+    for (int e = 0; e < LA; ++e) {
+      const int idx = tid + e * SNT;
+      const int64_t i = m0 + idx % STM, k = k0 + idx / STM;
+      ra[e] = i < M && k < K ? A[i + k * g.lda] : TAe(0);
+    }
+#pragma unroll
+    for (int e = 0; e < LB; ++e) {
+      const int idx = tid + e * SNT;
+      const int64_t k = k0 + idx % SBK, j = n0 + idx / SBK;
+      rb[e] = j < N && k < K ? B[k + j * g.ldb] : TE(0);
+    }
+  };
+  auto rounded = [](auto x) {
+    if constexpr (CPLX)
+      return V{(float)x.x, (float)x.y};
+    else
+      return (float)x;
+  };
+  auto store = [&](int buf) {
+#pragma unroll
+    for (int e = 0; e < LA; ++e) {
+      const int idx = tid + e * SNT;
+      As[buf][idx / STM][idx % STM] = rounded(ra[e]);
+    }
+#pragma unroll
+    for (int e = 0; e < LB; ++e) {
+      const int idx = tid + e * SNT;
+      Bs[buf][idx % SBK][idx / SBK] = rounded(rb[e]);
+    }
+  };
+
+  // complex: re*re, im*im and (re + im)(re + im)
+  f4 p1[2][2], p2[CPLX ? 2 : 1][2], p3[CPLX ? 2 : 1][2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      p1[a][b] = f4{0, 0, 0, 0};
+      if constexpr (CPLX) p2[a][b] = p3[a][b] = f4{0, 0, 0, 0};
+    }
+  const int64_t nchunks = (K + SBK - 1) / SBK;
+  load(0);
+  store(0);
+  __syncthreads();
+  for (int64_t c = 0; c < nchunks; ++c) {
+    const int buf = (int)(c & 1);
+    const bool more = c + 1 < nchunks;
+    if (more) load((c + 1) * SBK);
+#pragma unroll
+    for (int ks = 0; ks < SBK / 4; ++ks) {
+      const int kk = ks * 4 + lk;
+      V a[2], b[2];
+#pragma unroll
+      for (int f = 0; f < 2; ++f) {
+        a[f] = As[buf][kk][wm * 32 + f * 16 + l16];
+        b[f] = Bs[buf][kk][wn * 32 + f * 16 + l16];
+      }
+#pragma unroll
+      for (int fn = 0; fn < 2; ++fn)
+#pragma unroll
+        for (int fm = 0; fm < 2; ++fm) {
+          if constexpr (CPLX) {
+            p1[fm][fn] = MF<float>::fma(b[fn].x, a[fm].x, p1[fm][fn]);
+            p2[fm][fn] = MF<float>::fma(b[fn].y, a[fm].y, p2[fm][fn]);
+            p3[fm][fn] = MF<float>::fma(b[fn].x + b[fn].y, a[fm].x + a[fm].y, p3[fm][fn]);
+          } else {
+            p1[fm][fn] = MF<float>::fma(b[fn], a[fm], p1[fm][fn]);
+          }
+        }
+    }
+    if (more) store(buf ^ 1);
+    __syncthreads();
+  }
+
+  TE* __restrict__ C = static_cast<TE*>(g.C);
+#pragma unroll
+  for (int fm = 0; fm < 2; ++fm) {
+    const int64_t i = m0 + wm * 32 + fm * 16 + l16;
+    if (i >= M) continue;
+#pragma unroll
+    for (int fn = 0; fn < 2; ++fn)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int64_t j = n0 + wn * 32 + fn * 16 + frag_col<float>(lk, r);
+        if (j >= N) continue;
+        double vr = (double)p1[fm][fn][r], vi = 0.0;
+        if constexpr (CPLX) {
+          const float q1 = p1[fm][fn][r], q2 = p2[fm][fn][r];
+          vr = (double)(q1 - q2);
+          vi = (double)(p3[fm][fn][r] - q1 - q2);
+        }
+        const TE x = B[i + j * g.ldb];
+        vr = g.alpha * (vr - g.gamma * re_(x));
+        vi = g.alpha * (vi - g.gamma * im_(x));
+        if (g.beta != 0.0) {
+          const TE y = C[i + j * g.ldc];
+          vr += g.beta * re_(y);
+          vi += g.beta * im_(y);
+        }
+        if (g.colcoef) {
+          const double cj = g.colcoef[j];
+          const TE f = static_cast<const TE*>(g.F)[i + j * g.ldf];
+          vr += cj * re_(f);
+          vi += cj * im_(f);
+        }
+        if constexpr (CPLX)
+          C[i + j * g.ldc] = TE{vr, vi};
+        else
+          C[i + j * g.ldc] = vr;
+      }
+  }
+}
+
+template <typename TA, bool CPLX>
+void launch_staged_f32(const GemmArgs& g, hipStream_t st) {
+  const int64_t tiles_n = (g.N + STN - 1) / STN, ntiles = (g.M + STM - 1) / STM * tiles_n;
+  CHASE_REQUIRE(ntiles <= INT32_MAX - 8, "too many output tiles");
+  hipLaunchKernelGGL((staged_f32_kernel<TA, CPLX>), dim3((unsigned)((ntiles + 7) / 8 * 8)),
+                     dim3(SNT), 0, st, g, (int)tiles_n, (int)ntiles);
+  CHASE_HIP(hipGetLastError());
+}
+
+// Whether the direct kernel's speed suffers from columns that do not begin at
+// multiples of 32 bytes, 64 for H in FP64 (odd orders): 20001 rows against 20000,
+// 1300 columns, 35.0 ms instead of 27.9 complex and 16.1 instead of 10.9 real, the
+// staged kernel 28.1 (28.0) and 11.8 (11.5).  Smaller matrices and blocks lose less
+// than the direct tiles' finer division gains; direct / staged, passes of degrees
+// 2 to 10, ms: complex 9001 x 900 33.5 / 35.5, 11001 x 400 22.3 / 25.2, 10007 x 1001
+// 43.9 / 41.2, 20001 x 400 92.2 / 85.2; real 11001 x 400 10.5 / 11.0, 20001 x 300
+// 30.4 / 29.5; H in FP64, complex 20001 x 300 89.0 / 73.5, real 9001 x 900 18.9 / 17.2.
+template <typename TA, bool CPLX>
+bool f32_unaligned(const GemmArgs& g) {
+  constexpr int64_t W = CPLX ? 2 : 1;
+  constexpr int64_t line = sizeof(TA) == 8 ? 64 : 32;
+  if (g.lda * W * (int64_t)sizeof(TA) % line == 0 && g.ldb * W * 8 % line == 0) return false;
+  if (sizeof(TA) == 8) return g.M >= (CPLX ? 9600 : 8000);
+  return CPLX ? g.M >= 9600 && g.M * g.N >= 7000000 : g.M * g.N >= 5500000;
+}
+// The staged kernel with `rate`, where it has two tiles for every compute unit
+// (with H in FP64 for half of them) and undercuts the direct tiles' cost.  20001 x
+// 150, 471 tiles, pass of degrees 2 to 10, direct / staged: real 17.2 / 18.7 ms,
+// with H in FP64 21.2 / 19.8.
+template <typename TA>
+bool staged_f32(const GemmArgs& g, double rate, double direct) {
+  const Tile t{STM, STN, rate};
+  return 2 * tiles_of(g.M, g.N, STM, STN) >= (sizeof(TA) == 8 ? 3 : 4) * NCU &&
+         tile_cost(t, g.M, g.N) < direct;
+}
+
+// FP32 products of the filter step (A stored as TA, B in FP64), complex.
+// Rates: TFLOP/s (algorithmic) on the 20000 x 1300 step; 8000 x 260 takes 1.03
+// ms with 96 x 48 tiles, 1.08 with 64 x 32, 1.70 with 128 x 64.  H in FP64 (no
+// room for its FP32 copy) doubles the bytes of its fragments: the staged kernel
+// is the faster one there for wide blocks (20000 x 1300 29.2 ms, 31.1 with 96 x
+// 48; 9000 x 700 4.20 and 3.63).
 template <typename TA>
 void cheb_f32_cplx(const GemmArgs& g, hipStream_t st) {
   static constexpr Tile t[] = {{128, 64, 150}, {64, 32, 146}, {32, 32, 96}, {32, 16, 81},
                                {16, 16, 47}, {96, 48, 146}};
-  switch (pick(t, g.M, g.N)) {
+  static constexpr Tile t64[] = {{128, 64, 136}, {64, 32, 134}, {32, 32, 96}, {32, 16, 81},
+                                 {16, 16, 47}, {96, 48, 139}};
+  static constexpr Tile tu[] = {{128, 64, 120}, {64, 32, 108}, {32, 32, 65}, {32, 16, 55},
+                                {16, 16, 35}, {96, 48, 116}};
+  const bool unaligned = f32_unaligned<TA, true>(g);
+  double c;
+  const int p = unaligned ? pick(tu, g.M, g.N, &c)
+                : sizeof(TA) == 8 ? pick(t64, g.M, g.N, &c) : pick(t, g.M, g.N, &c);
+  if ((unaligned || sizeof(TA) == 8) && staged_f32<TA>(g, 149, c))
+    return launch_staged_f32<TA, true>(g, st);
+  switch (p) {
     case 0: return launch<TA, float, true, OP_N, OP_N, EPI_CHEB, true, 4, 2, 2, 1, 2, 2>(g, st);
     case 1: return launch<TA, float, true, OP_N, OP_N, EPI_CHEB, true, 4, 2, 4, 2>(g, st);
     case 2: return launch<TA, float, true, OP_N, OP_N, EPI_CHEB, true, 2, 2>(g, st);
@@ -781,17 +979,28 @@ void cheb_f32_cplx(const GemmArgs& g, hipStream_t st) {
   }
 }
 
-// Real: a table of its own (96 x 48 has an odd number of row fragments, and the
+// Real: tables of their own (96 x 48 has an odd number of row fragments, and the
 // rates are not in proportion).  Rates: TFLOP/s on steps of 4000 x 1000 to 20000
 // x 1300.  15000 x 2000 takes 9.1 ms with 128 x 128, 10.6 with 128 x 64, 10.8
-// with 64 x 32; 9000 x 1500 2.74, 2.88, 3.11.
+// with 64 x 32; 9000 x 1500 2.74, 2.88, 3.11.  H in FP64: 6001 x 1500 1.51 ms staged,
+// 1.67 with 128 x 128; 9000 x 700 1.83 and 1.35.
 template <typename TA>
 void cheb_f32_real(const GemmArgs& g, hipStream_t st) {
   // pairs of rows are loaded together: at least two of them
   if (g.M < 2) return launch<TA, float, false, OP_N, OP_N, EPI_CHEB, false, 1, 1>(g, st);
   static constexpr Tile t[] = {{128, 128, 97}, {128, 64, 88}, {64, 32, 80},
                                {32, 32, 46},   {32, 16, 44},  {16, 16, 23}};
-  switch (pick(t, g.M, g.N)) {
+  static constexpr Tile t64[] = {{128, 128, 92}, {128, 64, 80}, {64, 32, 68},
+                                 {32, 32, 44},   {32, 16, 42},  {16, 16, 22}};
+  static constexpr Tile tu[] = {{128, 128, 68}, {128, 64, 65}, {64, 32, 65},
+                                {32, 32, 38},   {32, 16, 36},  {16, 16, 20}};
+  const bool unaligned = f32_unaligned<TA, false>(g);
+  double c;
+  const int p = unaligned ? pick(tu, g.M, g.N, &c)
+                : sizeof(TA) == 8 ? pick(t64, g.M, g.N, &c) : pick(t, g.M, g.N, &c);
+  if ((unaligned || sizeof(TA) == 8) && staged_f32<TA>(g, sizeof(TA) == 8 ? 83 : 90, c))
+    return launch_staged_f32<TA, false>(g, st);
+  switch (p) {
     case 0: return launch<TA, float, false, OP_N, OP_N, EPI_CHEB, false, 4, 4, 2, 1, 2, 2>(g, st);
     case 1: return launch<TA, float, false, OP_N, OP_N, EPI_CHEB, false, 4, 2, 2, 1, 2, 2>(g, st);
     case 2: return launch<TA, float, false, OP_N, OP_N, EPI_CHEB, false, 4, 2, 4, 2>(g, st);

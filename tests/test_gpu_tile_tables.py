@@ -6,7 +6,7 @@ Tolerances.  FP64: two steps; a product of length n errs by at most (n + 8) u
 of its terms' magnitudes, the three-product form by four times that, so 8 (n +
 8) u times the recurrence run on magnitudes covers both steps, entry by entry.
 FP32: rounding errors of random sign, 2^-24 sqrt(n) of a column's size in each
-step; 16 times that for both steps and the largest of up to 3e6 entries, where
+step; 16 times that for both steps and the largest of up to 8e6 entries, where
 one lost term of a product would be n^-1/2, hundreds of times more.  INT8: the
 FP64 bar of 1e-12 of a column's largest entry (integer forms of 46 bits and
 more).  QR: k u times a small constant per entry of Q^H Q."""
@@ -50,7 +50,7 @@ def _filter(pk, h, x, prec, **opts):
 
 
 @pytest.mark.parametrize("cplx", [True, False])
-@pytest.mark.parametrize("n,k", tt.SHAPES)
+@pytest.mark.parametrize("n,k", tt.SHAPES + tt.STAGED_SHAPES)
 def test_fp64_and_fp32_tiles(cplx, n, k):
     import paper_2205_02491_amd as pk
     announce(f"tile tables: n={n} k={k} cplx={cplx}")

@@ -10,6 +10,9 @@ NCU = 256
 SHAPES = [(65, 17), (371, 171), (515, 241), (629, 297), (707, 339), (713, 353), (803, 381),
           (821, 395), (1025, 493), (1121, 549), (1283, 577), (1475, 675), (1745, 871),
           (2435, 773), (3329, 899)]
+# FP32 products of the staged kernel: real and complex, with the FP32 copy of H
+# (columns off the cache lines, large blocks) and without
+STAGED_SHAPES = [(4001, 1001), (5003, 1201), (8001, 401), (9601, 801)]
 # the same for the INT8 products' column widths, 14 moduli
 INT8_SHAPES = [(33, 5), (257, 97), (393, 193), (521, 257), (769, 193), (769, 257), (1025, 385),
                (1161, 577), (1537, 513)]
