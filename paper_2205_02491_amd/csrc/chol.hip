@@ -196,7 +196,9 @@ __global__ __launch_bounds__(CT) void chol_panel_k(T* __restrict__ A, int64_t ld
   // column-oriented, in registers).  Lane q of a column's quad holds its rows q,
   // q + 4, ...; the finished row goes to the other three by a quad broadcast.
   // One thread per column spent 11 us on the 496 multiply-adds and factor reads
-  // of a column, the longest phase of the launch; a quad 3 us.
+  // of a column, the longest phase of the launch; a quad 3 us.  The last panel has
+  // none.
+  if (pc == 0) return;
   {
     const int c = tid / PQ, q = tid % PQ;
     T x[CB / PQ];
