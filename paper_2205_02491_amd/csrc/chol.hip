@@ -9,7 +9,7 @@
 //    LDS (the same arithmetic in each, so they agree bit for bit), then
 //    solves R11^H X = A12 for its own PC columns of the row panel, staged
 //    through LDS, each column held in the registers of a quad of lanes (forward
-//    substitution).  Workgroup 0 also stores R11.
+//    substitution).  The last workgroup to have read the block stores R11.
 //  - chol_update_k: A22 -= R12^H R12 on the upper triangle, in UT x UT
 //    tiles staged through LDS.
 // The order of a k x k factorisation is about k / CB panel steps; at the
@@ -132,6 +132,7 @@ __global__ __launch_bounds__(CT) void chol_panel_k(T* __restrict__ A, int64_t ld
   __shared__ T row[2][CB];     // the pivot row of the current and the next step
   __shared__ double piv[CB];   // pivots a_jj = r_jj^2
   __shared__ double rdg[CB];   // 1 / r_jj
+  __shared__ int last;         // this workgroup stores R11
   const int bad = *info;       // loaded with the tiles below, tested after them
   const int tid = threadIdx.x;
   const int ti = tid % CB, tg = tid / CB;
@@ -189,16 +190,27 @@ __global__ __launch_bounds__(CT) void chol_panel_k(T* __restrict__ A, int64_t ld
     if (tg == 0) rdg[ti] = rs;
   }
   __syncthreads();
-  if (blockIdx.x == 0 && ti < nb)
-    for (int c = tg; c < nb; c += CG)
-      if (ti <= c) A[(int64_t)(j0 + ti) + (int64_t)(j0 + c) * lda] = D[ti + c * CLD];
+  // The factor takes the diagonal block's place once every workgroup has read the
+  // block (all of its entries went into D by now): the one that counts last, in
+  // info[1], stores it.  Workgroup 0 storing it here could be ahead of one that
+  // has not begun, on a busy chip or with more workgroups than the chip holds.
+  int before = 0;
+  if (tid == 0 && gridDim.x > 1) before = atomicAdd(info + 1, 1);
+  auto store_factor = [&] {
+    if (ti < nb)
+      for (int c = tg; c < nb; c += CG)
+        if (ti <= c) A[(int64_t)(j0 + ti) + (int64_t)(j0 + c) * lda] = D[ti + c * CLD];
+  };
   // Row panel: column c of A12 becomes R11^{-H} a_c (forward substitution,
   // column-oriented, in registers).  Lane q of a column's quad holds its rows q,
   // q + 4, ...; the finished row goes to the other three by a quad broadcast.
   // One thread per column spent 11 us on the 496 multiply-adds and factor reads
   // of a column, the longest phase of the launch; a quad 3 us.  The last panel has
-  // none.
-  if (pc == 0) return;
+  // none, and one workgroup.
+  if (pc == 0) {
+    store_factor();
+    return;
+  }
   {
     const int c = tid / PQ, q = tid % PQ;
     T x[CB / PQ];
@@ -215,7 +227,12 @@ __global__ __launch_bounds__(CT) void chol_panel_k(T* __restrict__ A, int64_t ld
       for (int m = 0; m < CB / PQ; ++m) P[(m * PQ + q) * PLD + c] = x[m];
     }
   }
+  if (tid == 0) {
+    last = before == (int)gridDim.x - 1;
+    if (last && gridDim.x > 1) info[1] = 0;  // for the next panel
+  }
   __syncthreads();
+  if (last) store_factor();
   for (int c = tg; c < pc; c += CG) A[(int64_t)(j0 + ti) + (c0 + c) * lda] = P[ti * PLD + c];
 }
 
@@ -371,7 +388,7 @@ void cholesky_launch(T* A, int64_t lda, int k, int* info, hipStream_t st) {
 
 void cholesky_upper(bool cplx, void* A, int64_t lda, int k, int* d_info, hipStream_t st) {
   CHASE_REQUIRE(k >= 0 && lda >= std::max(1, k), "Cholesky: bad order or leading dimension");
-  fill_zero(d_info, sizeof(int), st);
+  fill_zero(d_info, 2 * sizeof(int), st);
   if (k == 0) return;
   if (cplx)
     cholesky_launch(static_cast<cd*>(A), lda, k, d_info, st);

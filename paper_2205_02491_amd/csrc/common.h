@@ -250,8 +250,9 @@ void crt_cheb(bool cplx, const GemmArgs& g, const CrtBasis& B, const void* hbuf,
 // ------------------------------------------------------------------ Cholesky
 // A = R^H R for the Hermitian positive definite k x k matrix A (ld lda,
 // upper triangle read and overwritten by R; the strict lower triangle is
-// left alone).  d_info (device) receives 0, or the 1-based order of the
-// first pivot that is not positive (then A holds partial results).
+// left alone).  d_info (device, two words) receives 0, or the 1-based order of
+// the first pivot that is not positive (then A holds partial results); the
+// second word counts workgroups.
 void cholesky_upper(bool cplx, void* A, int64_t lda, int k, int* d_info, hipStream_t st);
 
 // M = diag(d) R^{-1} (k x k, zeros below the diagonal) for the upper
