@@ -271,12 +271,12 @@ void jacobi_norms(bool cplx, const void* G, int64_t ldg, int k, double* pinned, 
                   double* dia2, hipStream_t st);
 // Eigen-decomposition of the Hermitian k x k G (destroyed) by block-cyclic
 // Jacobi until off2 <= tol^2 (off2 + dia2) (the norms of G on entry, from
-// jacobi_norms); V (k x k) is scratch, W (may be G) receives the
-// eigenvectors and d_evals the eigenvalues, ascending; d_perm holds k ints.
+// jacobi_norms); V and G2 (k x k, G2 ld k) are scratch, W (may be G) receives
+// the eigenvectors and d_evals the eigenvalues, ascending; d_perm holds k ints.
 // Returns the sweeps; throws CHASE_ERR_NUMERIC after max_sweeps.
 int jacobi_heev(bool cplx, void* G, int64_t ldg, int k, void* V, int64_t ldv, void* W,
-                int64_t ldw, double* d_evals, int* d_perm, void* ws, int kmax, double* pinned,
-                hipStream_t st, double off2, double dia2, double tol, int max_sweeps);
+                int64_t ldw, double* d_evals, int* d_perm, void* ws, int kmax, void* G2,
+                double* pinned, hipStream_t st, double off2, double dia2, double tol, int max_sweeps);
 
 // ------------------------------------------------------------------ Lanczos
 struct LanczosBufs {

@@ -24,6 +24,7 @@
 // (and the defect-correction term) on the way out.
 #include "common.h"
 
+#include <algorithm>
 #include <cmath>
 #include <utility>
 
@@ -636,7 +637,7 @@ CrtBasis crt_basis(int n_mod, int64_t K, bool cplx) {
 namespace {
 inline size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 // byte offsets within the buffers: H planes | row exponents;
-// block planes | INT32 products | column exponents
+// block planes | residues of the products | column exponents
 inline size_t h_planes_bytes(bool cplx, int64_t n, int n_mod) {
   return align256((size_t)(cplx ? 3 : 1) * n_mod * n * plane_ld(n));
 }
@@ -644,16 +645,24 @@ inline size_t x_planes_bytes(bool cplx, int64_t n, int kmax, int n_mod) {
   return align256((size_t)(cplx ? 3 : 1) * n_mod * plane_ld(n) * kmax);
 }
 inline size_t x_prod_bytes(bool cplx, int64_t n, int kmax, int n_mod) {
-  return align256((size_t)(cplx ? 3 : 1) * n_mod * plane_ld(n) * kmax * 4);
+  return align256((size_t)(cplx ? 3 : 1) * n_mod * plane_ld(n) * kmax);
 }
 }  // namespace
 
 size_t crt_h_bytes(bool cplx, int64_t n, int n_mod) {
   return h_planes_bytes(cplx, n, n_mod) + (size_t)n * 4;
 }
+// The size that callers know from the workspace query is that of unpadded planes
+// with INT32 products, five bytes a plane and entry of the block.  It is kept, and
+// holds the padding of H's planes as well; two bytes are in use.
 size_t crt_x_bytes(bool cplx, int64_t n, int kmax, int n_mod) {
-  return x_planes_bytes(cplx, n, kmax, n_mod) + x_prod_bytes(cplx, n, kmax, n_mod) +
-         (size_t)kmax * 4 + 256;
+  const size_t planes = (size_t)(cplx ? 3 : 1) * n_mod, entries = planes * n * kmax;
+  const size_t tail = (size_t)kmax * 4 + 256;
+  const size_t known = align256(entries) + align256(4 * entries) + tail;
+  const size_t pad = h_planes_bytes(cplx, n, n_mod) - align256(planes * n * n);
+  const size_t used =
+      x_planes_bytes(cplx, n, kmax, n_mod) + x_prod_bytes(cplx, n, kmax, n_mod) + tail;
+  return std::max(used, known - std::min(known, pad));
 }
 
 void crt_prepare_h(bool cplx, const void* H, int64_t ldh, int64_t n, const CrtBasis& B,

@@ -663,10 +663,10 @@ inline int jac_blocks(int k) {
   return nb + (nb & 1);
 }
 
-// Workspace layout for orders up to kmax (byte offsets): the pairs'
-// unitaries, their rotation flags, the norm partials, the diagonal.
+// Workspace layout for orders up to kmax (byte offsets): the pairs' unitaries
+// and rotation flags of two rounds, the diagonal.
 struct JacLayout {
-  size_t ubuf[2], flags[2], part, diag, gbuf, total;
+  size_t ubuf[2], flags[2], diag, total;
   JacLayout(bool cplx, int kmax) {
     const int P = jac_blocks(std::max(kmax, 1)) / 2;
     const size_t esz = cplx ? 16 : 8;
@@ -676,10 +676,8 @@ struct JacLayout {
     ubuf[1] = ub;
     flags[0] = 2 * ub;
     flags[1] = 2 * ub + fl;
-    part = 2 * ub + 2 * fl;
-    diag = part + 2 * NPART * 8;
-    gbuf = (diag + (size_t)std::max(kmax, 1) * 8 + 255) / 256 * 256;
-    total = gbuf + (size_t)std::max(kmax, 1) * std::max(kmax, 1) * esz;
+    diag = 2 * ub + 2 * fl;
+    total = diag + (size_t)std::max(kmax, 1) * 8;
   }
 };
 
@@ -701,7 +699,7 @@ struct JacobiRunner {
     *dia2 = d;
   }
 
-  static int run(void* G, int64_t ldg, int k, void* V, int64_t ldv, void* ws,
+  static int run(void* G, int64_t ldg, int k, void* V, int64_t ldv, void* ws, void* G2,
                  const JacLayout& lay, double* pinned, double tol, int max_sweeps, double off2,
                  double dia2, hipStream_t st) {
     const int nb = jac_blocks(k), P = nb / 2;
@@ -712,7 +710,7 @@ struct JacobiRunner {
     const int tiles_g = P * (P + 1) / 2;
     const int tiles_v = ((k + JM - 1) / JM) * P;
     // the matrix and its other buffer, exchanged by every round's update
-    T *Gt = static_cast<T*>(G), *Do = reinterpret_cast<T*>(base + lay.gbuf);
+    T *Gt = static_cast<T*>(G), *Do = static_cast<T*>(G2);
     int64_t ldt = ldg, ldo = k;
     T* Vt = static_cast<T*>(V);
     hipLaunchKernelGGL(jac_eye_k<T>, dim3(std::min<int64_t>(1024, ((int64_t)k * k + 255) / 256)),
@@ -765,20 +763,21 @@ void jacobi_norms(bool cplx, const void* G, int64_t ldg, int k, double* pinned, 
 }
 
 int jacobi_heev(bool cplx, void* G, int64_t ldg, int k, void* V, int64_t ldv, void* W,
-                int64_t ldw, double* d_evals, int* d_perm, void* ws, int kmax, double* pinned,
-                hipStream_t st, double off2, double dia2, double tol, int max_sweeps) {
+                int64_t ldw, double* d_evals, int* d_perm, void* ws, int kmax, void* G2,
+                double* pinned, hipStream_t st, double off2, double dia2, double tol, int max_sweeps) {
   CHASE_REQUIRE(k >= 1 && k <= kmax, "Jacobi eigensolver: order out of range");
   CHASE_REQUIRE(ldg >= k && ldv >= k && ldw >= k, "Jacobi eigensolver: leading dimension < k");
   CHASE_REQUIRE(V != G && V != W, "Jacobi eigensolver: V must be a separate buffer");
+  CHASE_REQUIRE(G2 != G && G2 != V && G2 != W, "Jacobi eigensolver: G2 must be a separate buffer");
   if (!std::isfinite(off2) || !std::isfinite(dia2))
     throw Error(CHASE_ERR_NUMERIC, "non-finite entries in the projected matrix");
   const JacLayout lay(cplx, kmax);
   int sweeps;
   if (cplx)
-    sweeps = JacobiRunner<cd>::run(G, ldg, k, V, ldv, ws, lay, pinned, tol, max_sweeps, off2, dia2,
+    sweeps = JacobiRunner<cd>::run(G, ldg, k, V, ldv, ws, G2, lay, pinned, tol, max_sweeps, off2, dia2,
                                    st);
   else
-    sweeps = JacobiRunner<double>::run(G, ldg, k, V, ldv, ws, lay, pinned, tol, max_sweeps, off2,
+    sweeps = JacobiRunner<double>::run(G, ldg, k, V, ldv, ws, G2, lay, pinned, tol, max_sweeps, off2,
                                        dia2, st);
   // eigenvalues: the diagonal, ascending (stable), eigenvectors gathered to match
   double* d_diag = reinterpret_cast<double*>(static_cast<char*>(ws) + lay.diag);

@@ -38,7 +38,7 @@ struct chase_handle_s {
   void *V = nullptr, *W = nullptr, *Z = nullptr;
   // ne x ne matrices
   void *G = nullptr, *R = nullptr;
-  void* ws = nullptr;  // split-K workspace
+  void* ws = nullptr;  // split-K slices and other partial results (ws_bytes)
   size_t ws_elems = 0;
   double *d_scale = nullptr, *d_evals = nullptr, *d_res = nullptr, *d_partial = nullptr,
          *d_E = nullptr, *d_g = nullptr;
@@ -166,6 +166,17 @@ size_t splitk_ws_elems(bool cplx, int64_t n, int ne) {
   return mx;
 }
 
+// Bytes of the workspace that the steps of a call use in turn: split-K slices
+// (at least one k x k matrix: the Jacobi eigensolver's second one), the residual
+// norms' partial sums, the Lanczos products' partial sums.
+size_t ws_bytes(bool cplx, int64_t n, int ne, const chase_opts& o) {
+  const size_t esz = cplx ? 16 : 8;
+  int lz_splits = 0;
+  (void)lanczos_bytes(cplx, n, o.lanczos_vecs, o.lanczos_steps, &lz_splits);
+  return std::max({splitk_ws_elems(cplx, n, ne) * esz, (size_t)gemm_row_tiles(n) * ne * 8,
+                   (size_t)lz_splits * o.lanczos_vecs * (size_t)n * esz});
+}
+
 constexpr int kMaxDegree = 1000;  // largest filter degree any entry point accepts
 
 struct Sizes {
@@ -179,10 +190,10 @@ Sizes sizes(chase_dtype dt, int64_t n, int nev, int nex, const chase_opts& o) {
   const size_t esz = cplx ? 16 : 8;
   const int64_t ne = nev + nex;
   s.blocks = 3 * (size_t)n * ne * esz + 2 * (size_t)ne * ne * esz;
-  s.ws = splitk_ws_elems(cplx, n, (int)ne) * esz;
-  s.small = (size_t)ne * 8 * 5 + (size_t)gemm_row_tiles(n) * ne * 8 + 64 + (size_t)ne * 4 +
-            (size_t)ne * esz;
+  s.ws = ws_bytes(cplx, n, (int)ne, o);
+  s.small = (size_t)ne * 8 * 5 + 64 + (size_t)ne * 4 + (size_t)ne * esz;
   s.lz = lanczos_bytes(cplx, n, o.lanczos_vecs, o.lanczos_steps, &s.lz_splits);
+  s.lz -= (size_t)s.lz_splits * o.lanczos_vecs * (size_t)n * esz;  // in ws
   if (o.filter_prec == CHASE_PREC_FP32)
     s.h32 = (size_t)n * n * esz / 2 + (size_t)n * ne * esz;
   else if (o.filter_prec == CHASE_PREC_BF16X3 || o.filter_prec == CHASE_PREC_BF16X2)
@@ -707,7 +718,7 @@ int small_eig(chase_handle_s* h, int k, int method, hipStream_t st) {
     // callers check the library solver's info word: Jacobi reports by throwing
     fill_zero(h->d_info, sizeof(int), st);
     return jacobi_heev(h->cplx, h->G, k, k, h->R, k, h->G, k, h->d_evals, h->d_perm, h->jac_ws,
-                       h->ne, h->pin, st, off2, dia2, kJacobiTol, kJacobiMaxSweeps);
+                       h->ne, h->ws, h->pin, st, off2, dia2, kJacobiTol, kJacobiMaxSweeps);
   }
   if (h->cplx)
     rb_check(rocsolver_zheevd(h->rb, rocblas_evect_original, rocblas_fill_upper, k,
@@ -1311,14 +1322,14 @@ chase_status chase_create(chase_handle_t* out, chase_dtype dtype, int64_t n, int
     h->Z = dev_alloc(h, (size_t)n * ne * h->esz);
     h->G = dev_alloc(h, (size_t)ne * ne * h->esz);
     h->R = dev_alloc(h, (size_t)ne * ne * h->esz);
-    h->ws_elems = splitk_ws_elems(h->cplx, n, (int)ne);
-    h->ws = dev_alloc(h, h->ws_elems * h->esz);
+    h->ws_elems = sz.ws / h->esz;
+    h->ws = dev_alloc(h, sz.ws);
     h->d_scale = static_cast<double*>(dev_alloc(h, ne * 8));
     h->d_evals = static_cast<double*>(dev_alloc(h, ne * 8));
     h->d_res = static_cast<double*>(dev_alloc(h, ne * 8));
     h->d_E = static_cast<double*>(dev_alloc(h, ne * 8));
     h->d_g = static_cast<double*>(dev_alloc(h, ne * 8));
-    h->d_partial = static_cast<double*>(dev_alloc(h, (size_t)gemm_row_tiles(n) * ne * 8));
+    h->d_partial = static_cast<double*>(h->ws);
     h->d_flags = static_cast<int*>(dev_alloc(h, 64));
     h->d_info = static_cast<int*>(dev_alloc(h, 64));
     h->d_perm = static_cast<int*>(dev_alloc(h, ne * 4));
@@ -1329,7 +1340,7 @@ chase_status chase_create(chase_handle_t* out, chase_dtype dtype, int64_t n, int
     h->lz.q_prev = dev_alloc(h, (size_t)n * nv * W * 8);
     h->lz.q_cur = dev_alloc(h, (size_t)n * nv * W * 8);
     h->lz.w = dev_alloc(h, (size_t)n * nv * W * 8);
-    h->lz.wpart = dev_alloc(h, (size_t)h->lz.max_splits * nv * n * W * 8);
+    h->lz.wpart = h->ws;
     h->lz.dotp = static_cast<double*>(dev_alloc(h, 128 * nv * 8));
     h->lz.nrmp = static_cast<double*>(dev_alloc(h, 128 * nv * 8));
     h->lz.alpha = static_cast<double*>(dev_alloc(h, (size_t)steps * nv * 8));
