@@ -51,7 +51,7 @@ enum Op { OP_N = 0, OP_C = 1 };
 enum Epi { EPI_STORE = 0, EPI_CHEB = 1, EPI_SPLITK = 2, EPI_RESID = 3, EPI_SHIFT = 4 };
 
 // Arithmetic of the products: FP64 (double MFMA), FP32 (float MFMA,
-// operands rounded to float when staged in LDS, FP32 accumulation) or split
+// operands rounded to float as they are read, FP32 accumulation) or split
 // BF16 (three BF16 MFMAs per real product on hi/lo splits of both operands,
 // FP32 accumulation; operands in the s8 layout below).
 enum Prec { PREC_F64 = 0, PREC_F32 = 1, PREC_BF16X3 = 2, PREC_BF16X2 = 3 };

@@ -91,7 +91,6 @@ constexpr int64_t plane_ld(int64_t n) { return (n + 15) / 16 * 16; }
 typedef int i4v __attribute__((ext_vector_type(4)));
 
 constexpr int GKC = 128;  // K chunk (bytes)
-constexpr int GPC = GKC / 16;
 constexpr int GTM = 256;  // rows of a tile
 constexpr int GNT = 512;
 
@@ -125,8 +124,8 @@ __global__ __launch_bounds__(GNT, 2) void crt_gemm_k(const int8_t* __restrict__ 
   const int8_t* B = Bp + (int64_t)plane * cols * ld;
   const int n0 = tn * BN;
 
-  // The piece a lane copies into its place (row lane / 4, slot lane % 4 of a
-  // block of 16 rows): piece p of a row sits in slot p ^ key, an involution.
+  // The piece a lane copies into its place (row lane / 8, slot lane % 8 of a
+  // block of 8 rows): piece p of a row sits in slot p ^ key, an involution.
   // Rows and columns past the end are clamped: their products are not stored.
   auto akey = [](int r) { return ((r >> 1) & 1) | ((r >> 3) & 6); };
   auto bkey = [](int r) { return (r >> 1) & 7; };

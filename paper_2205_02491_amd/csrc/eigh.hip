@@ -49,15 +49,6 @@ template <>
 __device__ __forceinline__ double from_real<double>(double a) { return a; }
 template <>
 __device__ __forceinline__ cd from_real<cd>(double a) { return {a, 0.0}; }
-// acc += a * b
-__device__ __forceinline__ void mac(double& acc, double a, double b) { acc = fma(a, b, acc); }
-__device__ __forceinline__ void mac(cd& acc, cd a, cd b) {
-  acc.x = fma(a.x, b.x, acc.x);
-  acc.x = fma(-a.y, b.y, acc.x);
-  acc.y = fma(a.x, b.y, acc.y);
-  acc.y = fma(a.y, b.x, acc.y);
-}
-
 // Round-robin tournament over m players (m even), rounds r = 0 .. m-2:
 // player 0 stays, the others rotate; pair t of round r is
 // (rr_player(m, r, t), rr_player(m, r, m - 1 - t)).  Over the m - 1 rounds

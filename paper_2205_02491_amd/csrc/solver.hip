@@ -1305,15 +1305,13 @@ chase_status chase_create(chase_handle_t* out, chase_dtype dtype, int64_t n, int
     size_t fr = 0, tot = 0;
     CHASE_HIP(hipMemGetInfo(&fr, &tot));
     const size_t h32_bytes = (size_t)n * n * h->esz / 2;
-    // the FP32 copy of H is optional (without it the FP32 products round H
-    // while staging it in LDS); the split-BF16 copies are required
+    // the FP32 copy of H is optional (without it the FP32 products round H as
+    // they read it); the split-BF16 copies are required
     const size_t need_min = sz.total - (o.filter_prec == CHASE_PREC_FP32 ? h32_bytes : 0);
     if (need_min > fr)
       throw Error(CHASE_ERR_NOMEM, "workspace of " + std::to_string(need_min) +
                                        " bytes exceeds free device memory (" +
                                        std::to_string(fr) + ")");
-    // the low-precision copy of H is optional: without it the FP32 products
-    // round H's entries while staging them in LDS
     const bool with_h32 = o.filter_prec == CHASE_PREC_FP32 &&
                           sz.total + ((size_t)1 << 30) <= fr;
     const int64_t ne = h->ne;
