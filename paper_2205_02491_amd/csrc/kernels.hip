@@ -336,10 +336,13 @@ __global__ __launch_bounds__(TPB) void max_defect_k(const double* __restrict__ A
 constexpr int LZ_COLS_STAGE = 64;
 
 // Rows of H per workgroup: two a thread, or one for matrices that would
-// otherwise give a few dozen workgroups (n=1000: 32 of them, 19 us a step;
-// with 256 rows and down to 32 columns each 128 of them, 13 us).
-constexpr int64_t LZ_SMALL_N = 4096;
-int lz_rows(int64_t n) { return n < LZ_SMALL_N ? TPB : 2 * TPB; }
+// otherwise give a few dozen workgroups (complex n=1000: 32 of them, 19 us a step;
+// with 256 rows and down to 32 columns each 128 of them, 13 us).  Runs of 25 steps
+// and four vectors with one / two, ms: complex n=1000 0.78 / 0.90, 2000 0.92 / 1.00,
+// 2300 1.13 / 1.09, 3500 1.80 / 1.42; real n=2000 0.62 / 0.80, 4000 1.02 / 1.06,
+// 4500 1.27 / 1.19.
+inline bool lz_small(bool cplx, int64_t n) { return n < (cplx ? 2200 : 4096); }
+inline int lz_rows(bool cplx, int64_t n) { return lz_small(cplx, n) ? TPB : 2 * TPB; }
 
 template <bool CPLX, int NV, int LZ_ROWS_PER_THREAD>
 __global__ __launch_bounds__(TPB) void lz_gemv_k(const double* __restrict__ H, int64_t ldh,
@@ -668,10 +671,10 @@ __global__ void sym_divdiff_k(const double* __restrict__ M, int64_t ldm,
 // 256-CU MI355X, all resident at once (each streams a long range of
 // columns).  Measured at n=20000 with nontemporal loads: 6.7-6.9 TB/s with
 // 480 workgroups, 5.9 TB/s with ~2048 (two rounds of resident workgroups).
-int lz_splits(int64_t n) {
-  const int64_t row_blocks = (n + lz_rows(n) - 1) / lz_rows(n);
+int lz_splits(bool cplx, int64_t n) {
+  const int64_t row_blocks = (n + lz_rows(cplx, n) - 1) / lz_rows(cplx, n);
   int64_t s = 512 / row_blocks;
-  const int64_t smax = n < LZ_SMALL_N ? (n + 31) / 32 : (n + 63) / 64;
+  const int64_t smax = lz_small(cplx, n) ? (n + 31) / 32 : (n + 63) / 64;
   if (s > smax) s = smax;
   if (s > 64) s = 64;
   if (s < 1) s = 1;
@@ -931,7 +934,7 @@ void sym_divdiff(bool cplx, const void* M, int64_t ldm, const double* lam, int64
 
 size_t lanczos_bytes(bool cplx, int64_t n, int nv, int steps, int* max_splits) {
   const int W = cplx ? 2 : 1;
-  const int s = lz_splits(n);
+  const int s = lz_splits(cplx, n);
   if (max_splits) *max_splits = s;
   size_t b = 0;
   b += 3 * (size_t)n * nv * W * 8;            // q_prev, q_cur, w
@@ -951,8 +954,8 @@ void lanczos_run(bool cplx, const void* Hv, int64_t ldh, int64_t n, const void* 
   double* part = static_cast<double*>(b.wpart);
   const int splits = b.max_splits;
   const int64_t cols_per = (n + splits - 1) / splits;
-  const bool small = n < LZ_SMALL_N;
-  const int row_blocks = (int)((n + lz_rows(n) - 1) / lz_rows(n));
+  const bool small = lz_small(cplx, n);
+  const int row_blocks = (int)((n + lz_rows(cplx, n) - 1) / lz_rows(cplx, n));
   const int vb = (int)std::min<int64_t>(LZ_VEC_BLOCKS, (n + TPB - 1) / TPB);
 
   // q_1 = s / ||s|| ; q_0 = 0
