@@ -66,11 +66,11 @@ KERNEL_NAME = {
 }
 
 # HBM bytes per filter launch from rocprofv3 PMC runs (FETCH_SIZE x 2.0 and
-# WRITE_SIZE x 1.0, calibrated on a 1 GiB copy), valid only for the GEMM
+# WRITE_SIZE x 1.0, calibrated on known reads and writes), valid only for the GEMM
 # source they were measured on (sha256 prefix of csrc/gemm.hip).
 MEASURED_TRAFFIC = {
-    ("geometric20k", "fp64"): {"fetch_gb": 54.55, "write_gb": 0.416, "columns": 1300,
-                               "gemm_sha256": "c0bdc1127171d3e2",
+    ("geometric20k", "fp64"): {"fetch_gb": 102.18, "write_gb": 0.416, "columns": 1300,
+                               "gemm_sha256": "ec95c7af3a40d879",
                                "source": "profiles/filter_fp64_geometric20k_hbm_traffic.md"},
 }
 
@@ -884,7 +884,7 @@ def main():
     r = results[main_prec]
     peak = PEAK_TFLOPS[main_prec]
     # dominant kernel: the Chebyshev-step GEMM of the filter (all filter
-    # launches of the timed solves; HIP events around each launch)
+    # launches of the timed solves; HIP events around each pass)
     roof = {"bound": "mfma", "achieved": r["filter_tflops"], "peak": peak, "unit": "TFLOP/s",
             "frac": r["filter_tflops"] / peak, "traffic": None,
             "kernel": KERNEL_NAME[main_prec] + "; executed MFMA FLOPs = %g x algorithmic"

@@ -84,7 +84,7 @@ constexpr int64_t plane_ld(int64_t n) { return (n + 15) / 16 * 16; }
 //
 // Bound by the rate at which a compute unit's tiles arrive (the planes of H
 // are beyond the caches), so the largest tile wins: 14 moduli, complex, n=4000
-// with 260 columns 309 us (1130 TOP/s; 480 us the library's batched GEMM, which
+// with 260 columns 274 us (1275 TOP/s; 480 us the library's batched GEMM, which
 // also wrote INT32), n=20000 with 1300 23.8 ms (1833 TOP/s).  Slower: half as
 // deep chunks in four stages (347 us: half cache lines), operands staged in
 // registers (396), H's fragments straight from memory (318 - 412).

@@ -19,11 +19,13 @@
 // The WK waves of a workgroup share one tile of C and deal the K range among
 // them (units of 128 contiguous bytes); their partial tiles meet in LDS at
 // the end.  Small tiles with the K range split inside the workgroup fill the
-// chip from blocks of a few columns on, and waste little on ragged edges.
+// chip from blocks of a few columns on, and waste little on ragged edges.  The
+// FP32 filter step has a second kernel, staged through LDS, for wide blocks of
+// matrices whose columns lie off the cache lines (staged_f32_kernel).
 //
 // Measured per filter step against the earlier kernel (128 x 64 and 128 x 128
 // tiles staged through double-buffered LDS, one K range per tile), complex:
-// n=20000, 1300 columns 54.7 -> 47.4 ms (88 TFLOP/s algorithmic, 84% of the
+// n=20000, 1300 columns 54.7 -> 46 ms (90 TFLOP/s algorithmic, 86% of the
 // three-product FP64 peak); 1000 x 140 220 -> 22 us; 256 x 16 57 -> 5 us; real:
 // 5003 x 173 798 -> 157 us.  At full size the clock is power limited: on
 // operands with 16-bit mantissas the same kernel reaches 95 TFLOP/s, and what
@@ -654,8 +656,9 @@ int pick(const Tile (&t)[N], int64_t M, int64_t N_, double* least = nullptr) {
 // Complex, three-product form.  Rates: TFLOP/s (algorithmic) on the 20000 x
 // 1300 filter step.  The smaller tiles earn their place where a dimension is
 // ragged or the chip is not full: 1000 x 140 takes 22 us with 48 x 16 (189
-// tiles), 28 with 32 x 32 (160) or 32 x 16 (288), 41 with 48 x 32 (105); 3000 x
-// 96 takes 92 us with 80 x 16 (228), 104 with 48 x 32 (189), 142 with 32 x 32.
+// tiles), 28 with 32 x 32 (160) or 32 x 16 (288), 41 with 48 x 32 (105).  80 x 16
+// against the best other tile: 3020 x 95 91 / 104 us, 2503 x 105 79 / 88, 1389 x
+// 195 47 / 53, 3473 x 172 211 / 223, 1862 x 310 117 / 118.
 // Splitting K over workgroups as well, the last one to arrive adding up the
 // partial tiles, took 2 to 4 times as long as the best of these: the
 // device-wide fences it needs write back the L2s.
@@ -694,7 +697,10 @@ inline bool rank_tile(const GemmArgs& g) {
 // workgroups a compute unit), fewer waves split K, so that more workgroups
 // overlap one's reduction and stores with another's products.  8000 x 260 x
 // 260: 87 us with 8, 78 with 4; rank-96 update of order 3000: 201 / 138 / 126
-// us with 8 / 4 / 2, rank-960: 1084 / 982 / 1005.
+// us with 8 / 4 / 2, rank-960: 1084 / 982 / 1005.  About the line, complex rank-k
+// updates with 4 / 2 waves, us: order 1100, rank 100 27 / 27, 192 37 / 42, 260 47 /
+// 54; 5000: 192 609 / 589, 260 790 / 780; 20000: 192 9470 / 9020, 500 22680 / 22500:
+// beyond it two waves cost a small order up to 15% and gain a large one 2%.
 inline int waves_of(const GemmArgs& g) {
   if (tiles_of(g.M, g.N, 32, 32) < 4 * NCU) return 8;
   return g.K <= 192 ? 2 : 4;
