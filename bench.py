@@ -70,7 +70,7 @@ KERNEL_NAME = {
 # source they were measured on (sha256 prefix of csrc/gemm.hip).
 MEASURED_TRAFFIC = {
     ("geometric20k", "fp64"): {"fetch_gb": 102.18, "write_gb": 0.416, "columns": 1300,
-                               "gemm_sha256": "ec95c7af3a40d879",
+                               "gemm_sha256": "ac25809b08600458",
                                "source": "profiles/filter_fp64_geometric20k_hbm_traffic.md"},
 }
 

@@ -998,8 +998,9 @@ void cheb_f32_real(const GemmArgs& g, hipStream_t st) {
                                {32, 32, 46},   {32, 16, 44},  {16, 16, 23}};
   static constexpr Tile t64[] = {{128, 128, 92}, {128, 64, 80}, {64, 32, 68},
                                  {32, 32, 44},   {32, 16, 42},  {16, 16, 22}};
-  static constexpr Tile tu[] = {{128, 128, 68}, {128, 64, 65}, {64, 32, 65},
-                                {32, 32, 38},   {32, 16, 36},  {16, 16, 20}};
+  static constexpr Tile tu[] = {{128, 128, 68}, {128, 64, 65},
+                                {64, 32, sizeof(TA) == 8 ? 60 : 65},
+                                {32, 32, 38}, {32, 16, 36}, {16, 16, 20}};
   const bool unaligned = f32_unaligned<TA, false>(g);
   double c;
   const int p = unaligned ? pick(tu, g.M, g.N, &c)
